@@ -19,8 +19,8 @@
  *     returns without waiting for it.
  *   - Logit arrays are row-major with the vocabulary axis contiguous, in the
  *     dtype given by `dtype` (OSD_F32: IEEE float; OSD_BF16: bfloat16 bit
- *     patterns).  Rows whose byte address and length are multiples of 16 take
- *     the vectorised path; others are accepted and read element by element.
+ *     patterns).  Rows may start at any element and have any length; reads
+ *     are fastest from rows whose byte addresses are multiples of 16.
  *   - Host-checkable mistakes (null required pointer, non-positive sizes,
  *     K > OSD_MAX_K, V above osd_max_vocab, NaN or out-of-range scalars, an
  *     unknown enum, a workspace that is too small) return a negative status
@@ -279,8 +279,8 @@ int osd_verify_distill_rejected(const void* target_logits, const void* draft_log
  *
  * N <= OSD_MAX_TREE_NODES; V up to 32768 (bf16) or 16384 (fp32), otherwise
  * OSD_ERR_UNSUPPORTED.  Every node's rows are read once, whether or not the
- * walk reaches it: one workgroup per (sequence, node), or, for 16-byte
- * aligned rows at T > 0, about one workgroup per CU walking the nodes.
+ * walk reaches it: at T > 0 about one workgroup per CU walks the nodes, at
+ * T == 0 there is one workgroup per (sequence, node).
  */
 #define OSD_MAX_TREE_NODES 64
 size_t osd_verify_tree_workspace_bytes(int B, int N);
@@ -320,10 +320,9 @@ int osd_verify_tree(const void* target_logits, const void* draft_logits, int dty
  *               16-byte aligned, zero before the first call; every call
  *               leaves it zero.  Calls that may overlap (other streams) need
  *               their own.  With a workspace, one-row sampling (T > 0, beta
- *               0 or 1) of fewer rows than two per CU, rows 16-byte aligned
- *               with 16-byte multiple strides and lengths, splits each row
- *               over several workgroups that exchange two words each through
- *               it; every other call (and every call without one) runs one
+ *               0 or 1) of fewer rows than two per CU splits each row over
+ *               several workgroups that exchange two words each through it;
+ *               every other call (and every call without one) runs one
  *               workgroup per row.  The token is the same rule's either way;
  *               the two can differ only where u * sum(pi) lies within fp32
  *               rounding of a boundary between tokens.
@@ -333,8 +332,6 @@ int osd_verify_tree(const void* target_logits, const void* draft_logits, int dty
  * NULL or a row stride < V; OSD_ERR_UNSUPPORTED for V > osd_max_vocab(dtype);
  * OSD_ERR_WORKSPACE for a workspace that is too small or misaligned;
  * OSD_ERR_DEVICE if the launch fails.  Nothing is enqueued on an error.
- * Rows that are 16-byte aligned with 16-byte multiple strides and lengths
- * take 16-byte loads.
  */
 size_t osd_sample_workspace_bytes(int N);
 int osd_sample(const void* p_logits, int64_t p_row_stride,

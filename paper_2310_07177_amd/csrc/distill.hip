@@ -9,16 +9,20 @@
 //        with m = beta p + (1-beta) q
 // and 0 log 0 = 0.  Rows with mask 0 get D = 0 and a zero gradient row.
 //
-// One workgroup per row.  Both rows are read from HBM once, 16 bytes per
-// load, into registers; the row maxima and sums of exponentials are reduced
-// across the workgroup, the divergence terms are accumulated in fp32 per
-// thread and in fp64 across threads, and the gradient is written with 16-byte
-// stores.  The scalar loss is reduced without floating-point atomics: each
-// row stores its D, the last row of every 64-row slab to arrive sums its slab
-// in a fixed order, and the last slab to arrive sums the slabs in a fixed
-// order -- the result is bitwise reproducible.
+// Rows longer than the streaming tiles (distill_stream.hip), split over
+// workgroups, and rows shorter than one 16-byte chunk.  The scalar loss is
+// reduced without floating-point atomics: each row stores its D, the last row
+// of every 64-row slab to arrive sums its slab in a fixed order, and the last
+// slab to arrive sums the slabs in a fixed order -- the result is bitwise
+// reproducible.
+#include <stdlib.h>
+
+#include <type_traits>
+
 #include "osd_device.hpp"
 #include "osd_internal.hpp"
+#include "stream_device.hpp"
+#include "distill_common.hpp"
 
 namespace osd {
 namespace {
@@ -42,42 +46,6 @@ struct DistillArgs {
     uint32_t* done_cnt;
     int nslabs;
 };
-
-template <typename Fmt>
-__device__ inline chunk_t pack_grad(const float (&g)[Fmt::kPerChunk]) {
-    if constexpr (Fmt::kPerChunk == 8) {
-        return chunk_t{pack_bf16x2(g[0], g[1]), pack_bf16x2(g[2], g[3]),
-                       pack_bf16x2(g[4], g[5]), pack_bf16x2(g[6], g[7])};
-    } else {
-        return chunk_t{__float_as_uint(g[0]), __float_as_uint(g[1]),
-                       __float_as_uint(g[2]), __float_as_uint(g[3])};
-    }
-}
-
-template <typename Fmt, int W, int CPT, bool VEC>
-__device__ inline void store_grad_chunk(void* row, int n, const chunk_t& c, int V) {
-    const int nchunks = (V + Fmt::kPerChunk - 1) / Fmt::kPerChunk;
-    const int ch = n * W + static_cast<int>(threadIdx.x);
-    if (ch >= nchunks) return;
-    if constexpr (VEC) {
-        __builtin_nontemporal_store(c, static_cast<chunk_t*>(row) + ch);
-    } else {
-        const int64_t first = int64_t(ch) * Fmt::kPerChunk;
-        if constexpr (Fmt::kPerChunk == 8) {
-            uint16_t* p = static_cast<uint16_t*>(row);
-            const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (first + e < V) p[first + e] = uint16_t((w[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
-        } else {
-            uint32_t* p = static_cast<uint32_t*>(row);
-            const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (first + e < V) p[first + e] = w[e];
-        }
-    }
-}
 
 // Wave-wide fp64 sum with a fixed butterfly: every lane ends with the same,
 // run-to-run reproducible value.
@@ -162,201 +130,13 @@ __device__ void reduce_loss(const DistillArgs& a, int n, double D) {
     if (lane == 0) take_u32(a.done_cnt);
 }
 
-// Largest finite fp32 magnitude used to stand in for log2(0) = -inf, so that
-// p * log2(p) stays 0 * finite = 0 for logits of -inf.
-constexpr float kLogFloor = -1.0e30f;
-
-template <typename Fmt, int W, int CPT, bool VEC, int KIND>
-__global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void distill_kernel(DistillArgs a) {
-    constexpr int NW = W / kWave;
-    constexpr int EPC = Fmt::kPerChunk;
-    __shared__ float s_max[2][NW];
-    __shared__ double s_sum[2][NW];
-
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
-    const int K = a.K, V = a.V;
-    const int n = blockIdx.x;
-    const int b = n / K, i = n - b * K;
-    const bool on = a.mask == nullptr || a.mask[n] != 0;
-    void* grow = a.grad_out ? static_cast<char*>(a.grad_out) + int64_t(n) * V * Fmt::kBytes : nullptr;
-    double D = 0.0;
-
-    if (!on) {
-        if (grow) {
-#pragma unroll
-            for (int c = 0; c < CPT; ++c)
-                store_grad_chunk<Fmt, W, CPT, VEC>(grow, c, chunk_t{0u, 0u, 0u, 0u}, V);
-        }
-    } else {
-        const char* trow = static_cast<const char*>(a.teacher) +
-                           (int64_t(b) * a.tstride + int64_t(i) * V) * Fmt::kBytes;
-        const char* srow = static_cast<const char*>(a.student) +
-                           (int64_t(b) * a.sstride + int64_t(i) * V) * Fmt::kBytes;
-        chunk_t tv[CPT], sv[CPT];
-        load_row<Fmt, W, CPT, VEC>(tv, trow, V);
-        load_row<Fmt, W, CPT, VEC>(sv, srow, V);
-        const float c2 = a.c2;
-
-        // Row statistics (K, S), folded in chunk by chunk as the loads land.
-        // FKL and RKL are first-order sensitive to the normaliser (an error s
-        // in S shifts every log-ratio by s), so they accumulate every term in
-        // fp64; JSD is not (the mixture absorbs a common scale error), so it
-        // sums pairwise in fp32 within a chunk.
-        float Kt = kNegInf, Ks = kNegInf;
-        {
-            double dt = 0.0, ds = 0.0;
-            if constexpr (KIND == 2) {
-                float ft = 0.0f, fs = 0.0f;
-                row_stats<Fmt, CPT>(tv, c2, Kt, ft);
-                row_stats<Fmt, CPT>(sv, c2, Ks, fs);
-                dt = ft;
-                ds = fs;
-            } else {
-                row_stats<Fmt, CPT>(tv, c2, Kt, dt);
-                row_stats<Fmt, CPT>(sv, c2, Ks, ds);
-            }
-            wave_merge_stats(Kt, dt);
-            wave_merge_stats(Ks, ds);
-            if (lane == 0) {
-                s_max[0][wid] = Kt;
-                s_max[1][wid] = Ks;
-                s_sum[0][wid] = dt;
-                s_sum[1][wid] = ds;
-            }
-        }
-        __syncthreads();
-        Kt = s_max[0][0];
-        Ks = s_max[1][0];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) {
-            Kt = fmaxf(Kt, s_max[0][w]);
-            Ks = fmaxf(Ks, s_max[1][w]);
-        }
-        double St = 0.0, Ss = 0.0;
-        for (int w = 0; w < NW; ++w) {
-            St += rescale(s_sum[0][w], s_max[0][w], Kt);
-            Ss += rescale(s_sum[1][w], s_max[1][w], Ks);
-        }
-        // log2 p_j = t_j c2 - (K_t + log2 S_t) and p_j = 2^(log2 p_j): one
-        // fma and one exponential per element; likewise for q.
-        const double ktd = double(Kt) + log2(St), ksd = double(Ks) + log2(Ss);
-        const float kt = float(ktd), ks = float(ksd);
-        // log2(p_j / q_j) = (t_j - s_j) c2 - (k_t - k_s): the difference of the
-        // two constants is taken in fp64, so the loss of FKL and RKL carries no
-        // rounding of the (much larger) constants themselves.
-        const float dk = float(ktd - ksd);
-        const float beta = a.beta, omb = 1.0f - a.beta;
-        const bool q_only = a.beta == 0.0f;  // JSD at beta = 0: m = q, log2(q/m) = 0
-        const float ln2 = float(kLn2);
-
-        // Divergence terms, in log2 units.
-        float kt_c = kt, ks_c = ks, dk_c = dk;
-        asm volatile("" : "+v"(kt_c), "+v"(ks_c), "+v"(dk_c));
-        opaque(tv);
-        opaque(sv);
-        float acc0 = 0.0f, acc1 = 0.0f;
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-            float c0 = 0.0f, c1 = 0.0f;
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const float t = Fmt::get(tv[c], e), sx = Fmt::get(sv[c], e);
-                if constexpr (KIND == 0 || KIND == 1) {
-                    // log2(p/q), clamped so that a zero probability times an
-                    // infinite log-ratio stays 0.
-                    const float lr = fmaxf(fminf(__builtin_fmaf(t - sx, c2, -dk_c), -kLogFloor), kLogFloor);
-                    if constexpr (KIND == 0) {
-                        const float p = exp2_fast(__builtin_fmaf(t, c2, -kt_c));
-                        c0 = __builtin_fmaf(p, lr, c0);
-                    } else {
-                        const float q = exp2_fast(__builtin_fmaf(sx, c2, -ks_c));
-                        c0 = __builtin_fmaf(-q, lr, c0);
-                    }
-                } else {
-                    const float lp = fmaxf(__builtin_fmaf(t, c2, -kt_c), kLogFloor);
-                    const float lq = fmaxf(__builtin_fmaf(sx, c2, -ks_c), kLogFloor);
-                    const float p = exp2_fast(lp), q = exp2_fast(lq);
-                    // log2 m = lp + L, the mixture's log relative to p (near 0
-                    // when p ~ q): its rounding does not bias a small JSD.
-                    const float d = __builtin_amdgcn_fmed3f(lq - lp, -126.0f, 126.0f);
-                    const float L = log2_fast(__builtin_fmaf(omb, exp2_fast(d), beta));
-                    c0 = __builtin_fmaf(p, -L, c0);
-                    c1 = __builtin_fmaf(q, q_only ? 0.0f : d - L, c1);  // log2(q/m); m = q at beta = 0
-                }
-                if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // 4 elements in flight
-            }
-            acc0 = acc0 + c0;
-            acc1 = acc1 + c1;
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        {
-            const double d0 = wave_sum(double(acc0));
-            const double d1 = wave_sum(double(acc1));
-            __syncthreads();  // s_sum is reused
-            if (lane == 0) {
-                s_sum[0][wid] = d0;
-                s_sum[1][wid] = d1;
-            }
-        }
-        __syncthreads();
-        double A0 = 0.0, A1 = 0.0;
-        for (int w = 0; w < NW; ++w) {
-            A0 += s_sum[0][w];
-            A1 += s_sum[1][w];
-        }
-        // Terms were accumulated in log2 units.
-        if constexpr (KIND == 2)
-            D = kLn2 * (double(a.beta) * A0 + (1.0 - double(a.beta)) * A1);
-        else
-            D = kLn2 * A0;
-
-        if (grow) {
-            // FKL: g = (q - p) / tau;  RKL: g = q (ln q - ln p - D) / tau;
-            // JSD: g = (1-beta) q (ln q - ln m - KL(q||m)) / tau.
-            const float shift = KIND == 1 ? float(D) : float(kLn2 * A1);
-            const float scale = (KIND == 2 ? omb : 1.0f) * a.inv_tau;
-            float kt_g = kt, ks_g = ks;
-            asm volatile("" : "+v"(kt_g), "+v"(ks_g));
-            opaque(tv);
-            opaque(sv);
-#pragma unroll
-            for (int c = 0; c < CPT; ++c) {
-                float g[EPC];
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) {
-                    const float lp = fmaxf(__builtin_fmaf(Fmt::get(tv[c], e), c2, -kt_g), kLogFloor);
-                    const float lq = fmaxf(__builtin_fmaf(Fmt::get(sv[c], e), c2, -ks_g), kLogFloor);
-                    const float q = exp2_fast(lq);
-                    if constexpr (KIND == 0) {
-                        g[e] = (q - exp2_fast(lp)) * scale;
-                    } else {
-                        float lr;
-                        if constexpr (KIND == 1) {
-                            lr = lq - lp;
-                        } else {
-                            // log2(q/m), as in the loss pass
-                            const float d = __builtin_amdgcn_fmed3f(lq - lp, -126.0f, 126.0f);
-                            lr = q_only ? 0.0f : d - log2_fast(__builtin_fmaf(omb, exp2_fast(d), beta));
-                        }
-                        g[e] = (q * scale) * __builtin_fmaf(lr, ln2, -shift);
-                    }
-                    if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-                }
-                store_grad_chunk<Fmt, W, CPT, VEC>(grow, c, pack_grad<Fmt>(g), V);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-
-    if (a.row_loss_out && tid == 0) a.row_loss_out[n] = float(D);
-    if (wid == 0) reduce_loss(a, n, D);
-}
-
-// Rows too long to hold (beyond 8 chunks per thread of 1024 threads) are
-// split into segments of kSegChunks chunks, one 256-thread workgroup each,
-// which keeps its segment of both rows in registers and cooperates with the
-// other segments of its row through device memory:
-//   1. each segment folds its (K, S) pair of both rows and publishes it;
+// A row is split into segments of 8192 logits, one 256-thread workgroup
+// each, which cooperate through device memory (a row of one segment alone
+// needs no exchange):
+//   1. each segment turns its chunks of both rows into the cached pairs of
+//      distill_common.hpp, held in registers for the rest of the row (two
+//      floats per element pair instead of the raw logits: no later pass takes
+//      the exponentials again), folds its (K, S) pairs and publishes them;
 //      every segment reads all the row's records and merges them in segment
 //      order (the same normalisers in every workgroup);
 //   2. each segment sums its divergence terms and publishes the partials;
@@ -379,10 +159,21 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void distill_kernel(
 // with the same thread layout and reduction order, so that the result is the
 // same bit for bit; it still publishes and arrives, so the row completes as
 // usual.
-// The formulas are distill_kernel's.
+//
+// Instruction issue bounds the kernel (a transcendental takes 8 cycles of a
+// SIMD, any other vector instruction 4): JSD takes 5 transcendentals per
+// element pair from the cache against 9 from the raw logits, RKL 3 against 4,
+// FKL 4 against 5.  512 rows of V = 128256 bf16: JSD 145.9 -> 118.9 us, FKL
+// 113.9 -> 95.4; 4000 rows of V = 50304: RKL 359.6 -> 319.2, FKL 357.0 -> 274.1;
+// 18 rows of V = 54016, JSD: 28.0 -> 11.9 (one 1024-thread workgroup per row
+// before, which was no faster at any number of rows).
 constexpr int kSegW = 256;
-constexpr int kSegCPT = 4;
-constexpr int kSegChunks = kSegW * kSegCPT;
+// Chunks per thread of a segment: 32 elements of each row either way, 8192 bf16
+// or fp32 logits per segment.  (Segments of 4096 fp32 logits took 28.2 us for
+// 256 rows of V = 32000, against 23.2: their 2048 workgroups just missed
+// fitting the chip at once.)
+template <typename Fmt>
+constexpr int kSegCPT = 32 / Fmt::kPerChunk;
 constexpr int kSplitPolls = 256;
 constexpr int kSegNW = kSegW / kWave;
 
@@ -392,7 +183,6 @@ struct SplitArgs {
     uint64_t* part;  // [rows, kMaxSplitSegments, 2]: ~A0, ~A1 (bits)
     uint32_t* cnt;   // [rows, 4]: arrivals (word 0)
     int nseg;
-    int nchunks;
     int polls;
 };
 
@@ -402,7 +192,10 @@ struct SegShared {
     float rk[kMaxSplitSegments][2];   // records merged by this workgroup
     double rs[kMaxSplitSegments][2];
     double pa[kMaxSplitSegments][2];  // partials
-    int flag;
+    RowPair row;
+    double total[2];                  // the row's partials, added
+    int flag;                         // the polls brought every record
+    int last;                         // this workgroup is the row's last arriver
 };
 
 __device__ inline bool row_on(const DistillArgs& a, int n) { return a.mask == nullptr || a.mask[n] != 0; }
@@ -413,69 +206,100 @@ __device__ inline const char* row_ptr(const void* base, int64_t stride, int n, i
     return static_cast<const char*>(base) + (int64_t(b) * stride + int64_t(i) * V) * Fmt::kBytes;
 }
 
-// Chunk r of this thread in segment s.
-__device__ inline int seg_chunk(int s, int r) { return s * kSegChunks + r * kSegW + int(threadIdx.x); }
+// Chunk r of this thread in segment s, and its round when the whole row is
+// cut into rounds of kSegW chunks.
+template <typename Fmt>
+__device__ inline int seg_round(int s, int r) { return s * kSegCPT<Fmt> + r; }
+template <typename Fmt>
+__device__ inline int seg_chunk(int s, int r) { return seg_round<Fmt>(s, r) * kSegW + opaque_tid(); }
 
-template <typename Fmt, bool VEC>
-__device__ inline void seg_load(chunk_t (&x)[kSegCPT], const char* row, int s, int nchunks, int V) {
-#pragma unroll
-    for (int r = 0; r < kSegCPT; ++r) x[r] = stream_chunk<Fmt, VEC>(row, seg_chunk(s, r), nchunks, V);
-}
+// The cached pairs of a thread's elements in one segment, their shifts and
+// sums.  Every kind takes the shift over all the thread's chunks, so no
+// exponent exceeds 0 and no sum leaves the fp32 range.
+template <typename Fmt>
+struct SegCache {
+    static constexpr int EPC = Fmt::kPerChunk;
+    float c0[kSegCPT<Fmt>][EPC], c1[kSegCPT<Fmt>][EPC];
+    float kt, ks;
+    double St, Ss;
+};
 
-template <typename Fmt, bool VEC>
-__device__ inline void put_chunk(void* row, int ch, int nchunks, const chunk_t& c, int V) {
-    if (ch >= nchunks) return;
-    if constexpr (VEC) {
-        __builtin_nontemporal_store(c, static_cast<chunk_t*>(row) + ch);
-    } else {
-        const int64_t first = int64_t(ch) * Fmt::kPerChunk;
-        const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-        if constexpr (Fmt::kPerChunk == 8) {
-            uint16_t* p = static_cast<uint16_t*>(row);
+template <typename Fmt, int KIND>
+__device__ inline void seg_build(SegCache<Fmt>& c, const char* trow, const char* srow, int s, int V, float c2) {
+    constexpr int EPC = Fmt::kPerChunk;
+    asm volatile("" : "+s"(V), "+s"(s));  // nothing derived from them is hoisted out of a loop over segments
+    const RowCut<Fmt> cut(V);
+    chunk_t xt[kSegCPT<Fmt>], xs[kSegCPT<Fmt>];
+    if (V >= EPC) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (first + e < V) p[first + e] = uint16_t((w[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
-        } else {
-            uint32_t* p = static_cast<uint32_t*>(row);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (first + e < V) p[first + e] = w[e];
+        for (int r = 0; r < kSegCPT<Fmt>; ++r) {
+            const int off = cut.off(seg_chunk<Fmt>(s, r));
+            xt[r] = load_off(trow, off);
+            xs[r] = load_off(srow, off);
         }
+        if (cut.template ragged<kSegW>(seg_round<Fmt>(s, kSegCPT<Fmt> - 1))) {  // the row's last segment
+#pragma unroll
+            for (int r = 0; r < kSegCPT<Fmt>; ++r) {
+                const int lead = cut.lead(seg_chunk<Fmt>(s, r));
+                xt[r] = pad_lead<Fmt>(xt[r], lead);
+                xs[r] = pad_lead<Fmt>(xs[r], lead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else {  // a row shorter than one chunk: its elements end thread 0's chunk
+#pragma unroll
+        for (int r = 0; r < kSegCPT<Fmt>; ++r) xt[r] = xs[r] = pad_chunk<Fmt>();
+        if (opaque_tid() == 0) {
+            xt[0] = load_short<Fmt>(trow, V);
+            xs[0] = load_short<Fmt>(srow, V);
+        }
+    }
+    const LastChunk whole{0, 0, false};  // the padding is in place
+    c.kt = shift_of_max(chunks_max<Fmt, kSegCPT<Fmt>>(xt, whole), c2);
+    c.ks = shift_of_max(chunks_max<Fmt, kSegCPT<Fmt>>(xs, whole), c2);
+#pragma unroll
+    for (int r = 0; r < kSegCPT<Fmt>; ++r) {
+        // JSD is not first-order sensitive to the normalisers (the mixture
+        // absorbs a common scale error): fp32 within a chunk.  FKL and RKL
+        // are (an error in S shifts every log-ratio): every term in fp64.
+        // (Two running sums per row: half the dependent additions.)
+        typedef typename std::conditional<KIND == 2, float, double>::type acc_t;
+        acc_t st[2], ss[2];
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            const float vt = __builtin_fmaf(Fmt::get(xt[r], e), c2, -c.kt);
+            const float vs = __builtin_fmaf(Fmt::get(xs[r], e), c2, -c.ks);
+            const float et = exp2_fast(vt), es = exp2_fast(vs);
+            st[e & 1] = e < 2 ? acc_t(et) : st[e & 1] + acc_t(et);
+            ss[e & 1] = e < 2 ? acc_t(es) : ss[e & 1] + acc_t(es);
+            if constexpr (KIND == 2) {
+                c.c0[r][e] = et;
+                c.c1[r][e] = es;
+            } else {
+                // Both exponents: each side's probability is rebuilt from its
+                // own exponent (one floor suffices: two -inf exponents give a
+                // finite difference, and a draft exponent of -inf still q = 0).
+                c.c0[r][e] = fmaxf(vt, kLogFloor);
+                c.c1[r][e] = vs;
+            }
+        }
+        const double ct = double(st[0] + st[1]), cs = double(ss[0] + ss[1]);
+        c.St = r == 0 ? ct : c.St + ct;
+        c.Ss = r == 0 ? cs : c.Ss + cs;
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// Segment statistics of both rows, reduced over the workgroup; slot `slot`
-// of sh.rk / sh.rs receives them.  Opens with a barrier (sh.k, sh.s reuse).
-// A segment's chunks come from a source: src(r, t, s) yields chunk r of
-// this thread for both rows (held in registers, or loaded on demand -- the
-// arithmetic is the same either way).
-template <typename Fmt, int KIND, typename Src>
-__device__ inline void seg_stats(Src src, float c2, SegShared& sh, int slot) {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
-    float Kt = kNegInf, Ks = kNegInf;
-    double dt = 0.0, ds = 0.0;
-    if constexpr (KIND == 2) {
-        float ft = 0.0f, fs = 0.0f;
-#pragma unroll
-        for (int r = 0; r < kSegCPT; ++r) {
-            chunk_t ct, cs;
-            src(r, ct, cs);
-            fold_chunk<Fmt>(ct, c2, Kt, ft);
-            fold_chunk<Fmt>(cs, c2, Ks, fs);
-        }
-        dt = ft;
-        ds = fs;
-    } else {
-#pragma unroll
-        for (int r = 0; r < kSegCPT; ++r) {
-            chunk_t ct, cs;
-            src(r, ct, cs);
-            fold_chunk<Fmt>(ct, c2, Kt, dt);
-            fold_chunk<Fmt>(cs, c2, Ks, ds);
-        }
-    }
-    wave_merge_stats(Kt, dt);
-    wave_merge_stats(Ks, ds);
+// The segment's (K, S) pairs, reduced over the workgroup into slot `slot` of
+// sh.rk / sh.rs (written by thread 0).  Opens with a barrier (sh.k, sh.s reuse).
+template <typename Fmt>
+__device__ inline void seg_stats(const SegCache<Fmt>& c, SegShared& sh, int slot) {
+    const int tid = opaque_tid(), lane = tid & (kWave - 1), wid = tid / kWave;
+    // (A thread without mass has no say in the row's shift.)
+    float Kt = c.St == 0.0 ? kNegInf : c.kt, Ks = c.Ss == 0.0 ? kNegInf : c.ks;
+    double dt = c.St, ds = c.Ss;
+    wave_merge_stats_u(Kt, dt);
+    wave_merge_stats_u(Ks, ds);
     __syncthreads();
     if (lane == 0) {
         sh.k[0][wid] = Kt;
@@ -484,163 +308,122 @@ __device__ inline void seg_stats(Src src, float c2, SegShared& sh, int slot) {
         sh.s[1][wid] = ds;
     }
     __syncthreads();
-    if (tid == 0) {  // one value at a time: few registers beside the held segment
-        float kt = sh.k[0][0], ks = sh.k[1][0];
-#pragma unroll 1
-        for (int w = 1; w < kSegNW; ++w) {
-            kt = fmaxf(kt, sh.k[0][w]);
-            ks = fmaxf(ks, sh.k[1][w]);
+    if (wid == 0) {
+        float k0 = lane < kSegNW ? sh.k[0][lane] : kNegInf, k1 = lane < kSegNW ? sh.k[1][lane] : kNegInf;
+        double t0 = lane < kSegNW ? sh.s[0][lane] : 0.0, t1 = lane < kSegNW ? sh.s[1][lane] : 0.0;
+        row0_merge_stats_u(k0, t0);
+        row0_merge_stats_u(k1, t1);
+        if (lane == 0) {
+            sh.rk[slot][0] = k0;
+            sh.rk[slot][1] = k1;
+            sh.rs[slot][0] = t0;
+            sh.rs[slot][1] = t1;
         }
-        double St = 0.0, Ss = 0.0;
-#pragma unroll 1
-        for (int w = 0; w < kSegNW; ++w) {
-            St += rescale(sh.s[0][w], sh.k[0][w], kt);
-            Ss += rescale(sh.s[1][w], sh.k[1][w], ks);
-        }
-        sh.rk[slot][0] = kt;
-        sh.rk[slot][1] = ks;
-        sh.rs[slot][0] = St;
-        sh.rs[slot][1] = Ss;
     }
 }
 
-// A value every thread of the workgroup holds alike, kept in a scalar register.
-__device__ inline float uniform_f32(float v) {
-    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
-}
-
-// The row's normalisers in the forms distill_kernel uses, from the records
-// in sh, merged in segment order.
-struct RowNorm {
-    float kt, ks, dk;
+// The segment's divergence partials from its cache (which it turns into the
+// gradient's terms), reduced over the workgroup into slot `slot` of sh.pa.
+struct SegScales {
+    PairScales k;
+    float at, as;
 };
-__device__ inline RowNorm merge_norm(const SegShared& sh, int nseg) {
-    float Kt = kNegInf, Ks = kNegInf;
-#pragma unroll 2
-    for (int s = 0; s < nseg; ++s) {
-        Kt = fmaxf(Kt, sh.rk[s][0]);
-        Ks = fmaxf(Ks, sh.rk[s][1]);
-    }
-    double St = 0.0, Ss = 0.0;
-#pragma unroll 2
-    for (int s = 0; s < nseg; ++s) {
-        St += rescale(sh.rs[s][0], sh.rk[s][0], Kt);
-        Ss += rescale(sh.rs[s][1], sh.rk[s][1], Ks);
-    }
-    const double ktd = double(Kt) + log2(St), ksd = double(Ks) + log2(Ss);
-    return RowNorm{uniform_f32(float(ktd)), uniform_f32(float(ksd)), uniform_f32(float(ktd - ksd))};
+template <typename Fmt>
+__device__ inline SegScales seg_scales(const SegCache<Fmt>& c, const RowPair& rp, float beta) {
+    SegScales z;
+    const float ct = float(double(rp.kt - c.kt) + rp.lt), cs = float(double(rp.ks - c.ks) + rp.ls);
+    const int nt = int(fmaxf(c.kt - rp.kt, -2048.0f)), ns = int(fmaxf(c.ks - rp.ks, -2048.0f));
+    // A thread without mass in a row has scale 0 there (its own shift may lie
+    // far above the row's), and any positive ratio serves its zeros.
+    const bool none = c.St == 0.0 || c.Ss == 0.0;
+    z.at = c.St == 0.0 ? 0.0f : float(__builtin_ldexp(rp.ist, nt));
+    z.as = c.Ss == 0.0 ? 0.0f : float(__builtin_ldexp(rp.iss, ns));
+    z.k = PairScales{none ? 1.0f : float(__builtin_ldexp(rp.st * rp.iss, ns - nt)), beta, 1.0f - beta, ct, cs,
+                     float(rp.dtd - double(c.kt - c.ks))};
+    return z;
 }
-
-// The row's divergence from the partials in sh, added in segment order.
-template <int KIND>
-__device__ inline double merge_divergence(const SegShared& sh, int nseg, float beta, double& A1) {
-    double A0 = 0.0;
-    A1 = 0.0;
-#pragma unroll 2
-    for (int s = 0; s < nseg; ++s) {
-        A0 += sh.pa[s][0];
-        A1 += sh.pa[s][1];
-    }
-    if constexpr (KIND == 2)
-        return kLn2 * (double(beta) * A0 + (1.0 - double(beta)) * A1);
-    else
-        return kLn2 * A0;
-}
-
-// The segment's divergence partials, reduced over the workgroup into slot
-// `slot` of sh.pa.
-template <typename Fmt, int KIND, typename Src>
-__device__ inline void seg_partial(Src src, const RowNorm& rn, const DistillArgs& a, SegShared& sh, int slot) {
+template <typename Fmt, int KIND>
+__device__ inline void seg_partial(SegCache<Fmt>& c, const SegScales& z, SegShared& sh, int slot) {
     constexpr int EPC = Fmt::kPerChunk;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
-    const float c2 = a.c2, beta = a.beta, omb = 1.0f - a.beta;
-    const bool q_only = a.beta == 0.0f;
+    const int tid = opaque_tid(), lane = tid & (kWave - 1), wid = tid / kWave;
     float acc0 = 0.0f, acc1 = 0.0f;
 #pragma unroll
-    for (int r = 0; r < kSegCPT; ++r) {
-        float c0 = 0.0f, c1 = 0.0f;
-        chunk_t ct, cs;
-        src(r, ct, cs);
+    for (int r = 0; r < kSegCPT<Fmt>; ++r) {
+        float a0 = 0.0f, a1 = 0.0f;
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const float t = Fmt::get(ct, e), sx = Fmt::get(cs, e);
-            if constexpr (KIND == 0 || KIND == 1) {
-                const float lr = fmaxf(fminf(__builtin_fmaf(t - sx, c2, -rn.dk), -kLogFloor), kLogFloor);
-                if constexpr (KIND == 0) {
-                    const float p = exp2_fast(__builtin_fmaf(t, c2, -rn.kt));
-                    c0 = __builtin_fmaf(p, lr, c0);
-                } else {
-                    const float q = exp2_fast(__builtin_fmaf(sx, c2, -rn.ks));
-                    c0 = __builtin_fmaf(-q, lr, c0);
-                }
-            } else {
-                const float lp = fmaxf(__builtin_fmaf(t, c2, -rn.kt), kLogFloor);
-                const float lq = fmaxf(__builtin_fmaf(sx, c2, -rn.ks), kLogFloor);
-                const float p = exp2_fast(lp), q = exp2_fast(lq);
-                const float d = __builtin_amdgcn_fmed3f(lq - lp, -126.0f, 126.0f);
-                const float L = log2_fast(__builtin_fmaf(omb, exp2_fast(d), beta));
-                c0 = __builtin_fmaf(p, -L, c0);
-                c1 = __builtin_fmaf(q, q_only ? 0.0f : d - L, c1);
-            }
-            if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // 4 elements in flight
-        }
-        acc0 = acc0 + c0;
-        acc1 = acc1 + c1;
+        for (int e = 0; e < EPC; ++e) loss_term<KIND>(c.c0[r][e], c.c1[r][e], z.k, a0, a1);
+        acc0 = acc0 + a0;
+        acc1 = acc1 + a1;
         __builtin_amdgcn_sched_barrier(0);
     }
-    const double d0 = wave_sum(double(acc0)), d1 = wave_sum(double(acc1));
+    double A0 = double(acc0), A1 = 0.0;
+    if constexpr (KIND == 2) {
+        A0 *= double(z.at);
+        A1 = double(acc1) * double(z.as);
+    }
+    A0 = wave_sum_u(A0);
+    if constexpr (KIND == 2) A1 = wave_sum_u(A1);
     __syncthreads();
     if (lane == 0) {
-        sh.s[0][wid] = d0;
-        sh.s[1][wid] = d1;
+        sh.s[0][wid] = A0;
+        sh.s[1][wid] = A1;
     }
     __syncthreads();
-    if (tid == 0) {
-        double A0 = 0.0, A1 = 0.0;
-#pragma unroll 1
-        for (int w = 0; w < kSegNW; ++w) {
-            A0 += sh.s[0][w];
-            A1 += sh.s[1][w];
+    if (wid == 0) {
+        A0 = row0_sum_u(lane < kSegNW ? sh.s[0][lane] : 0.0);
+        A1 = row0_sum_u(lane < kSegNW ? sh.s[1][lane] : 0.0);
+        if (lane == 0) {
+            sh.pa[slot][0] = A0;
+            sh.pa[slot][1] = A1;
         }
-        sh.pa[slot][0] = A0;
-        sh.pa[slot][1] = A1;
     }
 }
 
-template <typename Fmt, bool VEC, int KIND>
-__device__ inline void seg_grad(const chunk_t (&xt)[kSegCPT], const chunk_t (&xs)[kSegCPT], const RowNorm& rn,
-                                const DistillArgs& a, double D, double A1, void* grow, int s, int nchunks) {
+// Wave 0: the row's normalisers from the records in sh, merged in segment
+// order by one scan (lane j: segment j), into sh.row.
+__device__ inline void merge_records(SegShared& sh, int nseg) {
+    const int lane = opaque_tid() & (kWave - 1);
+    const bool mine = lane < nseg;
+    store_row_pair(mine ? sh.rk[lane][0] : kNegInf, mine ? sh.rs[lane][0] : 0.0, mine ? sh.rk[lane][1] : kNegInf,
+                   mine ? sh.rs[lane][1] : 0.0, lane, &sh.row);
+}
+
+// Wave 0: the row's partials in sh, added in segment order, into sh.total.
+__device__ inline void merge_partials(SegShared& sh, int nseg) {
+    const int lane = opaque_tid() & (kWave - 1);
+    const double A0 = row0_sum_u(lane < nseg ? sh.pa[lane][0] : 0.0);
+    const double A1 = row0_sum_u(lane < nseg ? sh.pa[lane][1] : 0.0);
+    if (lane == 0) {
+        sh.total[0] = A0;
+        sh.total[1] = A1;
+    }
+}
+
+// The row's divergence from its added partials.
+template <int KIND>
+__device__ inline double row_divergence(const SegShared& sh, float beta) {
+    if constexpr (KIND == 2)
+        return kLn2 * (double(beta) * sh.total[0] + (1.0 - double(beta)) * sh.total[1]);
+    else
+        return (KIND == 0 ? kLn2 : -kLn2) * sh.total[0];
+}
+
+template <typename Fmt, int KIND>
+__device__ inline void seg_grad(const SegCache<Fmt>& c, const SegScales& z, const DistillArgs& a, float shift, void* grow,
+                                int s, const RowCut<Fmt>& cut) {
     constexpr int EPC = Fmt::kPerChunk;
-    const float c2 = a.c2, beta = a.beta, omb = 1.0f - a.beta;
-    const bool q_only = a.beta == 0.0f;
     const float ln2 = float(kLn2);
-    const float shift = uniform_f32(KIND == 1 ? float(D) : float(kLn2 * A1));
-    const float scale = (KIND == 2 ? omb : 1.0f) * a.inv_tau;
+    const float scale = KIND == 0 ? a.inv_tau : (KIND == 2 ? z.as * (z.k.omb * ln2 * a.inv_tau) : ln2 * a.inv_tau);
+    RowWriter<Fmt> out(grow, cut);
 #pragma unroll
-    for (int r = 0; r < kSegCPT; ++r) {
+    for (int r = 0; r < kSegCPT<Fmt>; ++r) {
         float g[EPC];
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const float lp = fmaxf(__builtin_fmaf(Fmt::get(xt[r], e), c2, -rn.kt), kLogFloor);
-            const float lq = fmaxf(__builtin_fmaf(Fmt::get(xs[r], e), c2, -rn.ks), kLogFloor);
-            const float q = exp2_fast(lq);
-            if constexpr (KIND == 0) {
-                g[e] = (q - exp2_fast(lp)) * scale;
-            } else {
-                float lr;
-                if constexpr (KIND == 1) {
-                    lr = lq - lp;
-                } else {
-                    const float d = __builtin_amdgcn_fmed3f(lq - lp, -126.0f, 126.0f);
-                    lr = q_only ? 0.0f : d - log2_fast(__builtin_fmaf(omb, exp2_fast(d), beta));
-                }
-                g[e] = (q * scale) * __builtin_fmaf(lr, ln2, -shift);
-            }
-            if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-        put_chunk<Fmt, VEC>(grow, seg_chunk(s, r), nchunks, pack_grad<Fmt>(g), a.V);
+        for (int e = 0; e < EPC; ++e) g[e] = grad_term<KIND>(c.c0[r][e], c.c1[r][e], scale, shift);
+        out.put(seg_chunk<Fmt>(s, r), pack_grad<Fmt>(g));
         __builtin_amdgcn_sched_barrier(0);
     }
+    out.finish();
 }
 
 __device__ inline uint64_t load_u64(const uint64_t* p) {
@@ -656,35 +439,30 @@ __device__ inline uint64_t pack_k(float kt, float ks) {
 // Wave 0 polls the published words of the row's other segments: lane j < nseg
 // (j != s) reads the `words` words of segment j until every one is non-zero
 // or the polls run out.  On success, lane j leaves them (un-inverted) in
-// w[0..words).  Every thread gets the outcome.
+// w[0..words).
 template <int WORDS>
-__device__ inline bool poll_words(const uint64_t* base, int nseg, int s, int polls, uint64_t (&w)[WORDS],
-                                  SegShared& sh) {
-    const int tid = threadIdx.x;
-    if (tid < kWave) {
-        const bool mine = tid < nseg && tid != s;
-        bool ok = false;
-        for (int p = 0; p < polls; ++p) {
-            if (p > 0) __builtin_amdgcn_s_sleep(8);
-            bool ready = true;
-            if (mine) {
+__device__ inline bool poll_words(const uint64_t* base, int nseg, int s, int polls, uint64_t (&w)[WORDS]) {
+    const int lane = opaque_tid() & (kWave - 1);
+    const bool mine = lane < nseg && lane != s;
+    bool ok = false;
+    for (int p = 0; p < polls; ++p) {
+        if (p > 0) __builtin_amdgcn_s_sleep(4);
+        bool ready = true;
+        if (mine) {
 #pragma unroll
-                for (int k = 0; k < WORDS; ++k) {
-                    w[k] = load_u64(base + int64_t(tid) * WORDS + k);
-                    ready = ready && w[k] != 0;
-                }
-            }
-            if (__ballot(!ready) == 0) {
-                ok = true;
-                break;
+            for (int k = 0; k < WORDS; ++k) {
+                w[k] = load_u64(base + int64_t(lane) * WORDS + k);
+                ready = ready && w[k] != 0;
             }
         }
-#pragma unroll
-        for (int k = 0; k < WORDS; ++k) w[k] = ~w[k];
-        if (tid == 0) sh.flag = ok;
+        if (__ballot(!ready) == 0) {
+            ok = true;
+            break;
+        }
     }
-    __syncthreads();
-    return sh.flag != 0;
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) w[k] = ~w[k];
+    return ok;
 }
 
 // Arrival at the row's counter once this workgroup's published words are
@@ -694,18 +472,21 @@ __device__ inline uint32_t arrive_row(uint32_t* counter) {
     return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <typename Fmt, bool VEC, int KIND>
-__global__ __launch_bounds__(kSegW) void split_row_kernel(SplitArgs sa) {
+template <typename Fmt, int KIND>
+__global__ __launch_bounds__(kSegW, 4) void split_row_kernel(SplitArgs sa) {
     __shared__ SegShared sh;
     const DistillArgs& a = sa.d;
-    const int nseg = sa.nseg, nchunks = sa.nchunks, V = a.V;
+    const int nseg = sa.nseg, V = a.V;
+    const RowCut<Fmt> cut(V);
     const int n = blockIdx.x / nseg, s = blockIdx.x - n * nseg;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     void* grow = a.grad_out ? static_cast<char*>(a.grad_out) + int64_t(n) * V * Fmt::kBytes : nullptr;
     if (!row_on(a, n)) {
         if (grow) {
+            RowWriter<Fmt> out(grow, cut);
 #pragma unroll
-            for (int r = 0; r < kSegCPT; ++r) put_chunk<Fmt, VEC>(grow, seg_chunk(s, r), nchunks, chunk_t{0u, 0u, 0u, 0u}, V);
+            for (int r = 0; r < kSegCPT<Fmt>; ++r) out.put(seg_chunk<Fmt>(s, r), chunk_t{0u, 0u, 0u, 0u});
+            out.finish();
         }
         if (s == 0 && wid == 0) {
             if (a.row_loss_out && lane == 0) a.row_loss_out[n] = 0.0f;
@@ -720,122 +501,127 @@ __global__ __launch_bounds__(kSegW) void split_row_kernel(SplitArgs sa) {
     uint32_t* cnt = sa.cnt + int64_t(n) * 4;
     const float c2 = a.c2;
 
-    chunk_t xt[kSegCPT], xs[kSegCPT];
-    seg_load<Fmt, VEC>(xt, trow, s, nchunks, V);
-    seg_load<Fmt, VEC>(xs, srow, s, nchunks, V);
-    const auto held = [&](int r, chunk_t& ct, chunk_t& cs) {
-        ct = xt[r];
-        cs = xs[r];
-    };
-
     // 1. statistics
-    seg_stats<Fmt, KIND>(held, c2, sh, s);
-    if (tid == 0) {
-        store_u64(&rec[3 * s], ~uint64_t(__double_as_longlong(sh.rs[s][0])));
-        store_u64(&rec[3 * s + 1], ~uint64_t(__double_as_longlong(sh.rs[s][1])));
-        store_u64(&rec[3 * s + 2], ~pack_k(sh.rk[s][0], sh.rk[s][1]));
-    }
-    {
-        uint64_t w[3];
-        const bool ok = poll_words<3>(rec, nseg, s, sa.polls, w, sh);
-        if (ok) {
-            if (tid < nseg && tid != s) {
-                sh.rs[tid][0] = __longlong_as_double(w[0]);
-                sh.rs[tid][1] = __longlong_as_double(w[1]);
-                sh.rk[tid][0] = __uint_as_float(uint32_t(w[2]));
-                sh.rk[tid][1] = __uint_as_float(uint32_t(w[2] >> 32));
+    SegCache<Fmt> c;
+    seg_build<Fmt, KIND>(c, trow, srow, s, V, c2);
+    seg_stats<Fmt>(c, sh, s);
+    if (wid == 0) {
+        bool ok = true;
+        if (nseg > 1) {
+            if (lane == 0) {
+                store_u64(&rec[3 * s], ~uint64_t(__double_as_longlong(sh.rs[s][0])));
+                store_u64(&rec[3 * s + 1], ~uint64_t(__double_as_longlong(sh.rs[s][1])));
+                store_u64(&rec[3 * s + 2], ~pack_k(sh.rk[s][0], sh.rk[s][1]));
             }
-        } else {
-            for (int j = 0; j < nseg; ++j) {
-                if (j == s) continue;
-                const auto loaded = [&](int r, chunk_t& ct, chunk_t& cs) {
-                    ct = stream_chunk<Fmt, VEC>(trow, seg_chunk(j, r), nchunks, V);
-                    cs = stream_chunk<Fmt, VEC>(srow, seg_chunk(j, r), nchunks, V);
-                };
-                seg_stats<Fmt, KIND>(loaded, c2, sh, j);
+            uint64_t w[3];
+            ok = poll_words<3>(rec, nseg, s, sa.polls, w);
+            if (ok && lane < nseg && lane != s) {
+                sh.rs[lane][0] = __longlong_as_double(w[0]);
+                sh.rs[lane][1] = __longlong_as_double(w[1]);
+                sh.rk[lane][0] = __uint_as_float(uint32_t(w[2]));
+                sh.rk[lane][1] = __uint_as_float(uint32_t(w[2] >> 32));
             }
-            // the segment is read again rather than held across the loop above
-            seg_load<Fmt, VEC>(xt, trow, s, nchunks, V);
-            seg_load<Fmt, VEC>(xs, srow, s, nchunks, V);
         }
+        if (lane == 0) sh.flag = ok;
+        if (ok) merge_records(sh, nseg);
     }
     __syncthreads();
-    const RowNorm rn = merge_norm(sh, nseg);
-    opaque(xt);  // each pass unpacks the held chunks afresh (bounded VGPRs)
-    opaque(xs);
+    if (!sh.flag) {
+#pragma unroll 1
+        for (int j = 0; j < nseg; ++j) {
+            if (j == s) continue;
+            seg_build<Fmt, KIND>(c, trow, srow, j, V, c2);
+            seg_stats<Fmt>(c, sh, j);
+        }
+        seg_build<Fmt, KIND>(c, trow, srow, s, V, c2);
+        if (wid == 0) merge_records(sh, nseg);
+        __syncthreads();
+    }
+    const RowPair rp = sh.row;
 
     // 2. divergence
-    seg_partial<Fmt, KIND>(held, rn, a, sh, s);
-    if (tid == 0) {
-        store_u64(&part[2 * s], ~uint64_t(__double_as_longlong(sh.pa[s][0])));
-        store_u64(&part[2 * s + 1], ~uint64_t(__double_as_longlong(sh.pa[s][1])));
-    }
+    SegScales z = seg_scales<Fmt>(c, rp, a.beta);
+    seg_partial<Fmt, KIND>(c, z, sh, s);
     uint32_t prev = 0;
-    double D = 0.0, A1 = 0.0;
     if constexpr (KIND == 0) {
-        if (tid == 0) prev = arrive_row(&cnt[0]);
-        opaque(xt);
-        opaque(xs);
-        if (grow) seg_grad<Fmt, VEC, KIND>(xt, xs, rn, a, 0.0, 0.0, grow, s, nchunks);
+        if (tid == 0) {
+            if (nseg > 1) {
+                store_u64(&part[2 * s], ~uint64_t(__double_as_longlong(sh.pa[s][0])));
+                store_u64(&part[2 * s + 1], ~uint64_t(__double_as_longlong(sh.pa[s][1])));
+                prev = arrive_row(&cnt[0]);
+            }
+        }
+        if (grow) seg_grad<Fmt, KIND>(c, z, a, 0.0f, grow, s, cut);
     } else {
         // 3. gradient
-        uint64_t w[2];
-        const bool ok = poll_words<2>(part, nseg, s, sa.polls, w, sh);
-        if (ok) {
-            if (tid < nseg && tid != s) {
-                sh.pa[tid][0] = __longlong_as_double(w[0]);
-                sh.pa[tid][1] = __longlong_as_double(w[1]);
+        if (wid == 0) {
+            bool ok = true;
+            if (nseg > 1) {
+                if (lane == 0) {
+                    store_u64(&part[2 * s], ~uint64_t(__double_as_longlong(sh.pa[s][0])));
+                    store_u64(&part[2 * s + 1], ~uint64_t(__double_as_longlong(sh.pa[s][1])));
+                }
+                uint64_t w[2];
+                ok = poll_words<2>(part, nseg, s, sa.polls, w);
+                if (ok && lane < nseg && lane != s) {
+                    sh.pa[lane][0] = __longlong_as_double(w[0]);
+                    sh.pa[lane][1] = __longlong_as_double(w[1]);
+                }
             }
-        } else {
+            if (lane == 0) sh.flag = ok;
+            if (ok) merge_partials(sh, nseg);
+        }
+        __syncthreads();
+        if (!sh.flag) {
+#pragma unroll 1
             for (int j = 0; j < nseg; ++j) {
                 if (j == s) continue;
-                const auto loaded = [&](int r, chunk_t& ct, chunk_t& cs) {
-                    ct = stream_chunk<Fmt, VEC>(trow, seg_chunk(j, r), nchunks, V);
-                    cs = stream_chunk<Fmt, VEC>(srow, seg_chunk(j, r), nchunks, V);
-                };
-                seg_partial<Fmt, KIND>(loaded, rn, a, sh, j);
+                seg_build<Fmt, KIND>(c, trow, srow, j, V, c2);
+                z = seg_scales<Fmt>(c, rp, a.beta);
+                seg_partial<Fmt, KIND>(c, z, sh, j);
             }
-            seg_load<Fmt, VEC>(xt, trow, s, nchunks, V);
-            seg_load<Fmt, VEC>(xs, srow, s, nchunks, V);
+            seg_build<Fmt, KIND>(c, trow, srow, s, V, c2);
+            z = seg_scales<Fmt>(c, rp, a.beta);
+            seg_partial<Fmt, KIND>(c, z, sh, s);
+            if (wid == 0) merge_partials(sh, nseg);
+            __syncthreads();
         }
-        __syncthreads();
-        if (tid == 0) prev = arrive_row(&cnt[0]);
-        D = merge_divergence<KIND>(sh, nseg, a.beta, A1);
-        opaque(xt);
-        opaque(xs);
-        if (grow) seg_grad<Fmt, VEC, KIND>(xt, xs, rn, a, D, A1, grow, s, nchunks);
+        if (tid == 0 && nseg > 1) prev = arrive_row(&cnt[0]);
+        if (grow) seg_grad<Fmt, KIND>(c, z, a, float(sh.total[KIND == 2 ? 1 : 0]), grow, s, cut);
     }
-    if (tid == 0) sh.flag = prev == uint32_t(nseg - 1);
-    __syncthreads();
-    if (sh.flag == 0) return;
+    if (nseg > 1) {
+        if (tid == 0) sh.last = prev == uint32_t(nseg - 1);
+        __syncthreads();
+        if (sh.last == 0) return;
+    }
     // The row's last arriver: every segment has read what it needed.
+    if (wid != 0) return;
     if constexpr (KIND == 0) {
-        if (tid < nseg && tid != s) {
-            sh.pa[tid][0] = __longlong_as_double(~load_u64(&part[2 * tid]));
-            sh.pa[tid][1] = __longlong_as_double(~load_u64(&part[2 * tid + 1]));
+        if (lane < nseg && lane != s) {
+            sh.pa[lane][0] = __longlong_as_double(~load_u64(&part[2 * lane]));
+            sh.pa[lane][1] = __longlong_as_double(~load_u64(&part[2 * lane + 1]));
         }
-        __syncthreads();
-        D = merge_divergence<KIND>(sh, nseg, a.beta, A1);
+        merge_partials(sh, nseg);
     }
-    if (tid < nseg) {
-        store_u64(&rec[3 * tid], 0ull);
-        store_u64(&rec[3 * tid + 1], 0ull);
-        store_u64(&rec[3 * tid + 2], 0ull);
-        store_u64(&part[2 * tid], 0ull);
-        store_u64(&part[2 * tid + 1], 0ull);
+    if (nseg > 1) {
+        if (lane < nseg) {
+            store_u64(&rec[3 * lane], 0ull);
+            store_u64(&rec[3 * lane + 1], 0ull);
+            store_u64(&rec[3 * lane + 2], 0ull);
+            store_u64(&part[2 * lane], 0ull);
+            store_u64(&part[2 * lane + 1], 0ull);
+        }
+        if (lane == 0) __hip_atomic_store(&cnt[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (tid == 0) __hip_atomic_store(&cnt[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (wid == 0) {
-        if (a.row_loss_out && lane == 0) a.row_loss_out[n] = float(D);
-        reduce_loss(a, n, D);
-    }
+    const double D = row_divergence<KIND>(sh, a.beta);
+    if (a.row_loss_out && lane == 0) a.row_loss_out[n] = float(D);
+    reduce_loss(a, n, D);
 }
 
-template <typename Fmt, bool VEC, int KIND>
+template <typename Fmt, int KIND>
 hipError_t launch_split_kind(const DistillLaunch& L, const SplitArgs& sa) {
     const unsigned rows = unsigned(L.B) * unsigned(L.K);
-    return launch_kernel(&split_row_kernel<Fmt, VEC, KIND>, dim3(rows * unsigned(sa.nseg)), dim3(kSegW), 0, L.stream,
-                         sa);
+    return launch_kernel(&split_row_kernel<Fmt, KIND>, dim3(rows * unsigned(sa.nseg)), dim3(kSegW), 0, L.stream, sa);
 }
 
 // kSplitPolls, or the value of OSD_SPLIT_POLLS (read once; 0 makes every
@@ -850,12 +636,13 @@ int split_polls() {
     return v;
 }
 
-template <typename Fmt, bool VEC>
+template <typename Fmt>
 hipError_t launch_split(const DistillLaunch& L, const DistillArgs& a) {
     SplitArgs sa;
     sa.d = a;
-    sa.nchunks = (L.V + Fmt::kPerChunk - 1) / Fmt::kPerChunk;
-    sa.nseg = (sa.nchunks + kSegChunks - 1) / kSegChunks;
+    const int nchunks = (L.V + Fmt::kPerChunk - 1) / Fmt::kPerChunk;
+    const int seg_chunks = kSegW * kSegCPT<Fmt>;
+    sa.nseg = (nchunks + seg_chunks - 1) / seg_chunks;
     if (sa.nseg > kMaxSplitSegments) return hipErrorInvalidValue;
     const size_t rows = size_t(L.B) * size_t(L.K);
     char* w = static_cast<char*>(L.split_ws);
@@ -865,42 +652,9 @@ hipError_t launch_split(const DistillLaunch& L, const DistillArgs& a) {
     sa.polls = split_polls();
     if (rows * size_t(sa.nseg) > size_t(0x7FFFFFFF)) return hipErrorInvalidValue;
     switch (L.kind) {
-        case 0: return launch_split_kind<Fmt, VEC, 0>(L, sa);
-        case 1: return launch_split_kind<Fmt, VEC, 1>(L, sa);
-        default: return launch_split_kind<Fmt, VEC, 2>(L, sa);
-    }
-}
-
-template <typename Fmt, int W, int CPT, bool VEC>
-hipError_t launch_kind(const DistillLaunch& L, const DistillArgs& a) {
-    const dim3 grid(unsigned(L.B) * unsigned(L.K)), block(W);
-    hipError_t e;
-    switch (L.kind) {
-        case 0: e = launch_kernel(&distill_kernel<Fmt, W, CPT, VEC, 0>, grid, block, 0, L.stream, a); break;
-        case 1: e = launch_kernel(&distill_kernel<Fmt, W, CPT, VEC, 1>, grid, block, 0, L.stream, a); break;
-        default: e = launch_kernel(&distill_kernel<Fmt, W, CPT, VEC, 2>, grid, block, 0, L.stream, a); break;
-    }
-    return e;
-}
-
-template <typename Fmt, int W, int CPT>
-hipError_t launch_tile(const DistillLaunch& L, const DistillArgs& a) {
-    return L.vec ? launch_kind<Fmt, W, CPT, true>(L, a) : launch_kind<Fmt, W, CPT, false>(L, a);
-}
-
-template <typename Fmt>
-hipError_t launch_fmt(const DistillLaunch& L, const DistillArgs& a) {
-    RowTile t;
-    if (!pick_tile(L.V, Fmt::kPerChunk, &t))
-        return L.vec ? launch_split<Fmt, true>(L, a) : launch_split<Fmt, false>(L, a);
-    switch (t.W * 100 + t.CPT) {
-        case 25601: return launch_tile<Fmt, 256, 1>(L, a);
-        case 25602: return launch_tile<Fmt, 256, 2>(L, a);
-        case 25604: return launch_tile<Fmt, 256, 4>(L, a);
-        case 51204: return launch_tile<Fmt, 512, 4>(L, a);
-        case 51208: return launch_tile<Fmt, 512, 8>(L, a);
-        case 102408: return launch_tile<Fmt, 1024, 8>(L, a);
-        default: return hipErrorInvalidValue;
+        case 0: return launch_split_kind<Fmt, 0>(L, sa);
+        case 1: return launch_split_kind<Fmt, 1>(L, sa);
+        default: return launch_split_kind<Fmt, 2>(L, sa);
     }
 }
 
@@ -927,7 +681,7 @@ hipError_t launch_distill(const DistillLaunch& L) {
     a.slab_cnt = L.slab_counters;
     a.done_cnt = L.done_counter;
     a.nslabs = (L.B * L.K + kSlabRows - 1) / kSlabRows;
-    return L.dtype == 1 ? launch_fmt<BF16>(L, a) : launch_fmt<F32>(L, a);
+    return L.dtype == 1 ? launch_split<BF16>(L, a) : launch_split<F32>(L, a);
 }
 
 }  // namespace osd

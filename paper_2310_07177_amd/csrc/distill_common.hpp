@@ -51,6 +51,67 @@ __device__ inline float rescue_sum(double& S, VFn v) {
     return o;
 }
 
+// One element of the divergence (in log2 units) and of the gradient, from its
+// cached pair of floats (c0, c1) and the thread's scales.
+//   JSD      c0 = 2^(t c2 - k_t), c1 = 2^(s c2 - k_s); p = c0 at, q = c1 as;
+//            the loss term leaves (log2(q/m), c1)
+//   FKL/RKL  c0 = t c2 - k_t, c1 = s c2 - k_s; log2 p = c0 - ct, log2 q = c1 - cs;
+//            the loss term leaves (p, log2 q) and (log2(p/q), q)
+struct PairScales {
+    float ratio;       // JSD: as / at
+    float beta, omb;   // JSD: beta, 1 - beta
+    float ct, cs, dTk; // FKL/RKL: log2(p/q) = (c0 - c1) - dTk
+};
+// a0, a1 collect, per thread: JSD the sums of -c0 L and c1 x (times at and as:
+// the sums of p log2(p/m) and q log2(q/m)); FKL and RKL (in a0) the sums of
+// p log2(p/q) and q log2(p/q).
+template <int KIND>
+__device__ inline void loss_term(float& c0, float& c1, const PairScales& k, float& a0, float& a1) {
+    if constexpr (KIND == 2) {
+        // rho = q/p, clamped to 2^+-126 (both limits stay exact enough: the
+        // vanishing side carries no weight; 0/0 and inf*0 take the lower one).
+        // log2 m = log2 p + L, L = log2(beta + (1 - beta) rho): the mixture's
+        // log relative to p, a number near 0 when p ~ q, so the rounding of a
+        // log does not bias every term of a small divergence.  At beta = 0, L
+        // is d itself (the same log of the same value): x = 0.
+        const float rho = __builtin_amdgcn_fmed3f((c1 * k.ratio) * __builtin_amdgcn_rcpf(c0), 0x1p-126f, 0x1p126f);
+        const float d = log2_fast(rho);
+        const float L = log2_fast(__builtin_fmaf(k.omb, rho, k.beta));
+        const float x = d - L;  // log2(q/m)
+        a0 = __builtin_fmaf(c0, -L, a0);
+        a1 = __builtin_fmaf(c1, x, a1);
+        c0 = x;
+    } else {
+        // log2(p/q) from the difference of the two exponents, clamped so that
+        // a zero probability times an infinite log-ratio stays 0.
+        const float lr = fmaxf(fminf((c0 - c1) - k.dTk, -kLogFloor), kLogFloor);
+        if constexpr (KIND == 0) {
+            const float p = exp2_fast(c0 - k.ct);
+            a0 = __builtin_fmaf(p, lr, a0);
+            c0 = p;
+            c1 = c1 - k.cs;  // log2 q
+        } else {
+            const float q = exp2_fast(c1 - k.cs);
+            a0 = __builtin_fmaf(q, lr, a0);
+            c0 = lr;
+            c1 = q;
+        }
+    }
+}
+// The gradient of one element from what loss_term left: scale and shift are
+//   JSD  as (1-beta) ln2/tau and KL2 = KL(q || m) in log2 units: q (x - KL2)
+//   RKL  ln2/tau and the sum of q log2(p/q): q (shift - log2(p/q))
+//   FKL  1/tau: q - p
+template <int KIND>
+__device__ inline float grad_term(float c0, float c1, float scale, float shift) {
+    if constexpr (KIND == 0)
+        return (exp2_fast(c1) - c0) * scale;
+    else if constexpr (KIND == 2)
+        return (c1 * scale) * (c0 - shift);
+    else
+        return (c1 * scale) * (shift - c0);
+}
+
 // A row pair's merged softmax statistics and the row-uniform values derived
 // from them (fp64), computed once per row pair by wave 0 and read from LDS by
 // every thread: K, S of each row, T_t - T_s (T = K + log2 S, the log2
@@ -59,6 +120,34 @@ struct RowPair {
     float kt, ks;
     double st, ss, dtd, ist, iss, lt, ls;
 };
+
+// Wave 0: merge the (K, S) pairs that lanes 0..15 hold (identity elsewhere) of
+// both rows and store the row values.
+__device__ inline void store_row_pair(float k0, double t0, float k1, double t1, int lane, RowPair* s_r) {
+    row0_merge_stats_u(k0, t0);
+    row0_merge_stats_u(k1, t1);
+    // The three quotients and the three logarithms are taken side by side in
+    // lanes 0-2 (one division and one log2_pos in sequence instead of three and
+    // three): lane 0 t0/t1, lane 1 1/t0, lane 2 1/t1, then the log2 of t0/t1, t0
+    // and t1.  Each value is the one the scalar formula gives.
+    const double qv = (lane == 0 ? t0 : 1.0) / (lane == 1 ? t0 : t1);
+    const double lv = log2_pos(lane == 0 ? qv : (lane == 1 ? t0 : t1));
+    const double l_q = readlane_f64(lv, 0), l_t = readlane_f64(lv, 1), l_s = readlane_f64(lv, 2);
+    const double i_t = readlane_f64(qv, 1), i_s = readlane_f64(qv, 2);
+    if (lane == 0) {
+        RowPair r;
+        r.kt = k0;
+        r.ks = k1;
+        r.st = t0;
+        r.ss = t1;
+        r.dtd = double(k0 - k1) + (t0 == t1 ? 0.0 : l_q);
+        r.ist = i_t;
+        r.iss = i_s;
+        r.lt = l_t;
+        r.ls = l_s;
+        *s_r = r;
+    }
+}
 
 // Every wave merges its lanes' (K, S) pairs and posts them; after one
 // barrier wave 0 merges the waves' pairs and derives the row values; after a
@@ -87,35 +176,11 @@ __device__ inline RowPair merge_row_pair(float Kt, double St, float Ks, double S
             t0 = s_s[lane];
             t1 = s_s[NW + lane];
         }
-        row0_merge_stats_u(k0, t0);
-        row0_merge_stats_u(k1, t1);
-        // The three quotients and the three logarithms are taken side by side
-        // in lanes 0-2 (one division and one log2_pos in sequence instead of
-        // three and three): lane 0 t0/t1, lane 1 1/t0, lane 2 1/t1, then the
-        // log2 of t0/t1, t0 and t1.  Each value is the one the scalar formula
-        // gives.
-        const double qv = (lane == 0 ? t0 : 1.0) / (lane == 1 ? t0 : t1);
-        const double lv = log2_pos(lane == 0 ? qv : (lane == 1 ? t0 : t1));
-        const double l_q = readlane_f64(lv, 0), l_t = readlane_f64(lv, 1), l_s = readlane_f64(lv, 2);
-        const double i_t = readlane_f64(qv, 1), i_s = readlane_f64(qv, 2);
-        if (lane == 0) {
-            RowPair r;
-            r.kt = k0;
-            r.ks = k1;
-            r.st = t0;
-            r.ss = t1;
-            r.dtd = double(k0 - k1) + (t0 == t1 ? 0.0 : l_q);
-            r.ist = i_t;
-            r.iss = i_s;
-            r.lt = l_t;
-            r.ls = l_s;
-            *s_r = r;
-        }
+        store_row_pair(k0, t0, k1, t1, lane, s_r);
     }
     __syncthreads();
     return *s_r;
 }
-
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // The LDS half of the cache: element e of chunk r of this thread, in float4

@@ -54,7 +54,6 @@ struct StreamDistillArgs {
     uint32_t* done;     // workgroups finished, zero between calls
     float* loss_out;    // {masked mean, masked sum}
     int nrows;
-    int nchunks;
     uint32_t row_bytes;
     int G;  // workgroups in the grid
 };
@@ -100,11 +99,11 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
     asm volatile("" ::"s"(a.teacher), "s"(a.tstride), "s"(a.student), "s"(a.sstride), "s"(a.B), "s"(a.K), "s"(a.V),
                  "s"(a.mask), "s"(a.beta), "s"(a.c2), "s"(a.inv_tau));
     asm volatile("" ::"s"(a.row_loss_out), "s"(a.grad_out), "s"(a.row_ws), "s"(a.done), "s"(a.loss_out), "s"(a.nrows),
-                 "s"(a.nchunks), "s"(a.row_bytes), "s"(a.G));
+                 "s"(a.row_bytes), "s"(a.G));
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int G = a.G;
     const float c2 = a.c2;
-    const bool last_ok = (CPT - 1) * W + tid < a.nchunks;
+    const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
     const float beta = a.beta, omb = 1.0f - a.beta;
 
     chunk_t rt[CPT], rs[CPT];
@@ -160,8 +159,8 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
             // shift k is taken over all its chunks: every cached value is at
             // most 1 and no sum leaves the fp32 range.
             if (live) {
-                const float mt = chunks_max<Fmt, CPT>(rt, !last_ok);
-                const float ms = chunks_max<Fmt, CPT>(rs, !last_ok);
+                const float mt = chunks_max<Fmt, CPT>(rt, last);
+                const float ms = chunks_max<Fmt, CPT>(rs, last);
                 kc_t = shift_of_max(mt, c2);
                 kc_s = shift_of_max(ms, c2);
             }
@@ -170,9 +169,9 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
         for (int r = 0; r < CPT; ++r) {
             if (live) {
                 chunk_t xt = rt[r], xs = rs[r];
-                if (r == CPT - 1 && !last_ok) {
-                    xt = pad_chunk<Fmt>();
-                    xs = pad_chunk<Fmt>();
+                if (r == CPT - 1 && last.ragged) {
+                    xt = pad_lead<Fmt>(xt, last.lead);
+                    xs = pad_lead<Fmt>(xs, last.lead);
                 }
                 if (!XV && r == 0) {
                     kc_t = first_chunk_shift<Fmt>(xt, c2);
@@ -215,8 +214,8 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
                 S_t = r == 0 ? double(st) : S_t + double(st);
                 S_s = r == 0 ? double(ss) : S_s + double(ss);
             }
-            rt[r] = load_chunk<W>(ntr, r);
-            rs[r] = load_chunk<W>(nsr, r);
+            rt[r] = load_round<W, CPT>(ntr, r, last);
+            rs[r] = load_round<W, CPT>(nsr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (k < 0) {  // step -1: stage the mask flags
@@ -226,7 +225,7 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
         if (!live) {
             if (a.grad_out && has_row) {
 #pragma unroll
-                for (int r = 0; r < CPT; ++r) store_chunk<W>(gr, r, chunk_t{0u, 0u, 0u, 0u});
+                for (int r = 0; r < CPT; ++r) store_round<Fmt, W, CPT>(gr, r, chunk_t{0u, 0u, 0u, 0u}, last);
             }
         } else {
             // Exponent range exceeded by an element far above the first
@@ -341,7 +340,7 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
                                 g[e] = (c1[r][e] * scale) * (shift - c0v[j]);
                         }
                     }
-                    store_chunk<W>(gr, r, pack_grad<Fmt>(g));
+                    store_round<Fmt, W, CPT>(gr, r, pack_grad<Fmt>(g), last);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -405,11 +404,12 @@ hipError_t launch_fmt(const DistillLaunch& L, const StreamDistillArgs& a) {
 
 }  // namespace
 
-// Streaming tiles, smallest first: up to 32768 bf16 or 16384 fp32 logits per
-// row.  Registers hold the raw chunks in flight (and, in the distillation
+// Streaming tiles, smallest first: one chunk to 32768 bf16 or 16384 fp32
+// logits per row.  A row of the tile's range fills every round but the last.  Registers hold the raw chunks in flight (and, in the distillation
 // kernel, one float per element); the rest of a row's state lives in LDS.
 bool pick_stream_tile(int V, int per_chunk, RowTile* t) {
     static const RowTile tiles[] = {{256, 1}, {512, 1}, {1024, 1}, {1024, 2}, {1024, 3}, {1024, 4}};
+    if (V < per_chunk) return false;
     for (const RowTile& c : tiles)
         if (int64_t(V) <= int64_t(c.W) * c.CPT * per_chunk) {
             *t = c;
@@ -438,7 +438,6 @@ hipError_t launch_distill_stream(const DistillLaunch& L) {
     a.loss_out = L.loss_out;
     a.nrows = L.B * L.K;
     const int eb = L.dtype == 1 ? 2 : 4;
-    a.nchunks = int((int64_t(L.V) * eb) / 16);
     a.row_bytes = uint32_t(int64_t(L.V) * eb);
     return L.dtype == 1 ? launch_fmt<BF16>(L, a) : launch_fmt<F32>(L, a);
 }

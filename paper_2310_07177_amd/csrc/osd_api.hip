@@ -15,10 +15,7 @@ constexpr size_t kAlign = 256;
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 int per_chunk(int dtype) { return dtype == OSD_BF16 ? 8 : (dtype == OSD_F32 ? 4 : 0); }
-int elem_bytes(int dtype) { return dtype == OSD_BF16 ? 2 : 4; }
 
 // Counters and records of the row-resident kernel, then the argmax partials
 // of the segmented greedy kernels.  Every call leaves all of it zero.
@@ -172,13 +169,11 @@ int osd_verify(const void* target_logits, const void* draft_logits, int dtype, i
     L.records = reinterpret_cast<uint32_t*>(w + ws.records);
     L.counters = reinterpret_cast<uint32_t*>(w + ws.counters);
     L.seg_stats = reinterpret_cast<osd::SegStats*>(w + ws.stats);
-    L.vec = (int64_t(V) * elem_bytes(dtype)) % 16 == 0 && aligned16(target_logits) &&
-            (greedy || aligned16(draft_logits));
     L.stream = static_cast<hipStream_t>(stream);
     // Greedy: segmented kernels (balanced over every CU).  Sampling: the
     // row-resident kernel, which draws from rows it already holds.
     int nseg = 0;
-    const bool segmented = greedy && L.vec && osd::greedy_segments(V, per_chunk(dtype), &nseg);
+    const bool segmented = greedy && osd::greedy_segments(V, per_chunk(dtype), &nseg);
     const hipError_t e = segmented ? osd::launch_verify_greedy(L) : osd::launch_verify(L);
     return e == hipSuccess ? OSD_OK : OSD_ERR_DEVICE;
 }
@@ -231,14 +226,10 @@ int osd_distill_loss_grad(const void* teacher_logits, int64_t teacher_batch_stri
     L.slab_ws = reinterpret_cast<double*>(w + ws.slabs);
     L.slab_counters = reinterpret_cast<uint32_t*>(w + ws.slab_cnt);
     L.done_counter = reinterpret_cast<uint32_t*>(w + ws.done);
-    const int eb = elem_bytes(dtype);
-    L.vec = (int64_t(V) * eb) % 16 == 0 && (teacher_batch_stride * eb) % 16 == 0 &&
-            (student_batch_stride * eb) % 16 == 0 && aligned16(teacher_logits) &&
-            aligned16(student_logits) && (grad_out == nullptr || aligned16(grad_out));
     L.stream = static_cast<hipStream_t>(stream);
     L.cus = device_cus(L.stream);
     osd::RowTile t;
-    const bool streaming = L.vec && osd::pick_stream_tile(V, per_chunk(dtype), &t);
+    const bool streaming = osd::pick_stream_tile(V, per_chunk(dtype), &t);
     const hipError_t e = streaming ? osd::launch_distill_stream(L) : osd::launch_distill(L);
     return e == hipSuccess ? OSD_OK : OSD_ERR_DEVICE;
 }
@@ -274,10 +265,8 @@ int verify_distill_impl(const void* target_logits, const void* draft_logits, int
     if (!workspace || workspace_bytes < ws.total || (reinterpret_cast<uintptr_t>(workspace) & 15u))
         return OSD_ERR_WORKSPACE;
     char* w = static_cast<char*>(workspace);
-    const int eb = elem_bytes(dtype);
     osd::RowTile t;
-    const bool fused = (int64_t(V) * eb) % 16 == 0 && aligned16(target_logits) && aligned16(draft_logits) &&
-                       (grad_out == nullptr || aligned16(grad_out)) && osd::pick_stream_tile(V, per_chunk(dtype), &t);
+    const bool fused = osd::pick_stream_tile(V, per_chunk(dtype), &t);
     if (!fused) {  // the two calls, each on its own part of the workspace
         const VerifyWs vw = verify_layout(B, K);
         const DistillWs dw = distill_layout(B, K);
@@ -379,7 +368,6 @@ int osd_sample(const void* p_logits, int64_t p_row_stride, const void* q_logits,
     if (workspace && (workspace_bytes < osd_sample_workspace_bytes(N) ||
                       (reinterpret_cast<uintptr_t>(workspace) & 15u)))
         return OSD_ERR_WORKSPACE;
-    const int64_t eb = elem_bytes(dtype);
     osd::SampleLaunch L;
     L.p = use_p ? p_logits : nullptr;
     L.p_stride = use_p ? p_row_stride : 0;
@@ -393,8 +381,6 @@ int osd_sample(const void* p_logits, int64_t p_row_stride, const void* q_logits,
     L.u = u;
     L.out = out_tokens;
     L.workspace = workspace;
-    L.vec = (int64_t(V) * eb) % 16 == 0 && (!use_p || (aligned16(p_logits) && (p_row_stride * eb) % 16 == 0)) &&
-            (!use_q || (aligned16(q_logits) && (q_row_stride * eb) % 16 == 0));
     L.stream = static_cast<hipStream_t>(stream);
     L.cus = device_cus(L.stream);
     return osd::launch_sample(L) == hipSuccess ? OSD_OK : OSD_ERR_DEVICE;
@@ -438,8 +424,6 @@ osd::ShardLaunch shard_launch(int phase, const void* target, const void* draft, 
     L.tokens = tokens;
     L.draft_len = draft_len;
     L.temperature = temperature;
-    L.vec = (int64_t(V_shard) * elem_bytes(dtype)) % 16 == 0 && aligned16(target) &&
-            (L.draft == nullptr || aligned16(L.draft));
     L.stream = static_cast<hipStream_t>(stream);
     return L;
 }
@@ -636,8 +620,6 @@ int osd_verify_tree(const void* target_logits, const void* draft_logits, int dty
     char* w = static_cast<char*>(workspace);
     L.counters = reinterpret_cast<uint32_t*>(w + ws.counters);
     L.records = reinterpret_cast<uint32_t*>(w + ws.records);
-    L.vec = (int64_t(V) * elem_bytes(dtype)) % 16 == 0 && aligned16(target_logits) &&
-            (greedy || aligned16(draft_logits));
     L.stream = static_cast<hipStream_t>(stream);
     L.cus = device_cus(L.stream);
     return osd::launch_verify_tree(L) == hipSuccess ? OSD_OK : OSD_ERR_DEVICE;

@@ -5,6 +5,15 @@
 // threads holds a row in registers as CPT chunks per thread: chunk n*W + tid
 // for round n, so each round is one fully coalesced sweep over W*16 bytes and
 // token ids grow with (round, thread, element).
+//
+// A row may start at any element and have any length of at least one chunk
+// (RowCut): 16-byte loads from addresses that are not 16-byte multiples are
+// part of the gfx950 memory model.  A read of 8192 rows of V = 32003 bf16 logits
+// that way runs at 5.0 TB/s (rows on 4-byte boundaries 6.3, on 16-byte ones
+// 6.7).  Element by element, verification of B = 32, K = 8, V = 32003 took
+// 38.6 us and takes 18.9, verification and distillation of B = 32, K = 6,
+// V = 50257 89.5 and 51.5.  Only rows shorter than one chunk are read element
+// by element (VEC = false).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -90,70 +99,151 @@ __device__ inline chunk_t pad_chunk() {
         return chunk_t{0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u};
 }
 
-// Load the CPT chunks of one row owned by this thread.  VEC: the row is
-// 16-byte aligned and V is a multiple of the chunk size.
-// VEC loads are issued without branches (a chunk past the row reloads the
-// row's last chunk and is replaced by padding): with every load in one basic
-// block the compiler waits for exactly the chunk a sweep consumes next, so
-// the statistics fold in as the loads land instead of after the last one.
-template <typename Fmt, int W, int CPT, bool VEC>
-__device__ inline void load_row(chunk_t (&c)[CPT], const void* row, int V) {
-    const int nchunks = (V + Fmt::kPerChunk - 1) / Fmt::kPerChunk;
+// How a row of V elements (at least one chunk) is cut into chunks.  Chunk ch
+// starts at element ch*kPerChunk, except that the last chunk of a row whose
+// length is not a whole number of chunks is moved back to end with the row:
+// its first `dup` elements belong to the chunk before it and count as
+// padding.  Chunks past the row re-read the last one and are all padding.  (In
+// a row shorter than one chunk the only chunk starts before the row: its
+// elements are loaded one by one, load_short.)
+template <typename Fmt>
+struct RowCut {
+    int nchunks;   // chunks that hold elements of the row
+    int nfull;     // chunks before the first one with any padding
+    int dup;       // padding elements at the head of the last chunk
+    int last_off;  // byte offset of the last chunk
+    __device__ explicit RowCut(int V) {
+        constexpr int EPC = Fmt::kPerChunk;
+        nchunks = (V + EPC - 1) / EPC;
+        dup = nchunks * EPC - V;
+        nfull = dup ? nchunks - 1 : nchunks;
+        last_off = (V - EPC) * Fmt::kBytes;
+    }
+    __device__ int off(int ch) const { return min(ch * 16, last_off); }
+    // Leading elements of chunk ch that are padding.
+    __device__ int lead(int ch) const { return ch < nfull ? 0 : (ch < nchunks ? dup : Fmt::kPerChunk); }
+    // The token id of element e of chunk ch, given as ch*kPerChunk + e.
+    __device__ int token(int t) const { return t >= nfull * Fmt::kPerChunk ? t - dup : t; }
+    // Whether round n of a workgroup of W threads holds any padding (uniform).
+    template <int W>
+    __device__ bool ragged(int n) const { return (n + 1) * W > nfull; }
+};
+
+// A 16-byte load from any element of a row.
+typedef chunk_t chunk_any_t __attribute__((aligned(2)));
+__device__ inline chunk_t load_off(const void* row, int off) {
+    return __builtin_nontemporal_load(reinterpret_cast<const chunk_any_t*>(static_cast<const char*>(row) + off));
+}
+
+// The chunk with its first `lead` elements replaced by padding.  (An opaque
+// copy of lead: its comparisons, needed by one wave per row, would otherwise be
+// hoisted out of a row loop and held in scalar registers.)
+template <typename Fmt>
+__device__ inline chunk_t pad_lead(const chunk_t& c, int lead) {
+    asm volatile("" : "+v"(lead));
+    const chunk_t pad = pad_chunk<Fmt>();
+    if constexpr (Fmt::kPerChunk == 8) {
+        const auto w = [lead](uint32_t x, int e) {
+            const uint32_t p = 0xFF80u;
+            return lead > e + 1 ? (p | (p << 16)) : (lead > e ? (x & 0xFFFF0000u) | p : x);
+        };
+        return chunk_t{w(c.x, 0), w(c.y, 2), w(c.z, 4), w(c.w, 6)};
+    } else {
+        return chunk_t{lead > 0 ? pad.x : c.x, lead > 1 ? pad.y : c.y, lead > 2 ? pad.z : c.z, lead > 3 ? pad.w : c.w};
+    }
+}
+
+// The only chunk of a row of V < kPerChunk elements (they end the chunk).
+template <typename Fmt>
+__device__ inline chunk_t load_short(const void* row, int V) {
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int n = 0; n < CPT; ++n) {
-        const int ch = n * W + static_cast<int>(threadIdx.x);
-        if constexpr (VEC) {
-            const bool in = ch < nchunks;
-            const chunk_t v = __builtin_nontemporal_load(static_cast<const chunk_t*>(row) + (in ? ch : nchunks - 1));
-            const chunk_t pad = pad_chunk<Fmt>();
-            c[n] = chunk_t{in ? v.x : pad.x, in ? v.y : pad.y, in ? v.z : pad.z, in ? v.w : pad.w};
-        } else {
-            c[n] = ch < nchunks ? Fmt::load_scalar(row, int64_t(ch) * Fmt::kPerChunk, V) : pad_chunk<Fmt>();
+    for (int e = 0; e < Fmt::kPerChunk; ++e) {
+        const int j = e - (Fmt::kPerChunk - V);
+        if constexpr (Fmt::kPerChunk == 8)
+            w[e >> 1] |= (j >= 0 ? Fmt::load_raw(row, j) : uint32_t(Fmt::kPad)) << (16 * (e & 1));
+        else
+            w[e] = j >= 0 ? Fmt::load_raw(row, j) : 0xFF800000u;
+    }
+    return chunk_t{w[0], w[1], w[2], w[3]};
+}
+
+// Writes a thread's chunks of a row back: 16-byte stores, except that the last
+// chunk, when it shares elements with the chunk before it, is kept until
+// finish() stores its own elements one by one (one copy of that code, outside
+// the unrolled rounds).
+template <typename Fmt>
+struct RowWriter {
+    char* row;
+    const RowCut<Fmt>& cut;
+    chunk_t tail = chunk_t{0u, 0u, 0u, 0u};
+    bool has_tail = false;
+    __device__ RowWriter(void* r, const RowCut<Fmt>& c) : row(static_cast<char*>(r)), cut(c) {}
+    __device__ void put(int ch, const chunk_t& c) {
+        if (ch < cut.nfull) {
+            __builtin_nontemporal_store(c, reinterpret_cast<chunk_any_t*>(row + ch * 16));
+        } else if (ch < cut.nchunks) {
+            tail = c;
+            has_tail = true;
         }
     }
-}
+    __device__ void finish() {
+        if (!has_tail) return;
+        const uint32_t w[4] = {tail.x, tail.y, tail.z, tail.w};
+#pragma unroll
+        for (int e = 0; e < Fmt::kPerChunk; ++e) {
+            if (e < cut.dup) continue;
+            if constexpr (Fmt::kPerChunk == 8)
+                reinterpret_cast<uint16_t*>(row + cut.last_off)[e] = uint16_t(w[e >> 1] >> (16 * (e & 1)));
+            else
+                reinterpret_cast<uint32_t*>(row + cut.last_off)[e] = w[e];
+        }
+    }
+};
 
-// The loads of load_row<VEC> without the padding: a chunk past the row
-// re-reads the row's last chunk and stays as loaded.  Consumers apply the
-// padding where they use a chunk (row_stats_tail, pad_row_tail), so no
-// instruction right after the loads needs their data and each sweep waits
-// only for the chunk it takes next.
-template <int W, int CPT>
-__device__ inline void load_row_clamped(chunk_t (&c)[CPT], const void* row, int nchunks) {
+// Load the CPT chunks of one row owned by this thread, as loaded: the
+// padding is applied where a chunk is first used (row_stats, pad_row_tail), so
+// no instruction right after the loads needs their data and each sweep waits
+// only for the chunk it takes next.  VEC = false: a row shorter than one
+// chunk, element by element, padded.
+template <typename Fmt, int W, int CPT, bool VEC>
+__device__ inline void load_row(chunk_t (&c)[CPT], const void* row, const RowCut<Fmt>& cut, int V) {
 #pragma unroll
     for (int n = 0; n < CPT; ++n) {
         const int ch = n * W + static_cast<int>(threadIdx.x);
-        c[n] = __builtin_nontemporal_load(static_cast<const chunk_t*>(row) + (ch < nchunks ? ch : nchunks - 1));
+        if constexpr (VEC)
+            c[n] = load_off(row, cut.off(ch));
+        else
+            c[n] = ch == 0 ? Fmt::load_scalar(row, 0, V) : pad_chunk<Fmt>();
     }
 }
 
-// Two rows loaded as load_row_clamped loads each, chunk by chunk in turn
-// (a0, b0, a1, b1, ...), the order in which row_stats2_tail takes them.
-template <int W, int CPT>
-__device__ inline void load_rows_interleaved(chunk_t (&a)[CPT], chunk_t (&b)[CPT], const void* ra, const void* rb,
-                                             int nchunks) {
-#pragma unroll
-    for (int n = 0; n < CPT; ++n) {
-        const int ch = n * W + static_cast<int>(threadIdx.x);
-        const int cl = ch < nchunks ? ch : nchunks - 1;
-        a[n] = __builtin_nontemporal_load(static_cast<const chunk_t*>(ra) + cl);
-        b[n] = __builtin_nontemporal_load(static_cast<const chunk_t*>(rb) + cl);
-    }
-}
-
-// Chunk n of this thread, or padding if it lies past the row.
-template <typename Fmt, int W>
-__device__ inline chunk_t chunk_or_pad(const chunk_t& c, int n, int nchunks) {
-    const bool in = n * W + static_cast<int>(threadIdx.x) < nchunks;
-    const chunk_t pad = pad_chunk<Fmt>();
-    return chunk_t{in ? c.x : pad.x, in ? c.y : pad.y, in ? c.z : pad.z, in ? c.w : pad.w};
-}
-
-// Replace the chunks of load_row_clamped that lie past the row by padding.
+// Two rows loaded as load_row loads each, chunk by chunk in turn (a0, b0,
+// a1, b1, ...), the order in which row_stats2 takes them.
 template <typename Fmt, int W, int CPT>
-__device__ inline void pad_row_tail(chunk_t (&c)[CPT], int nchunks) {
+__device__ inline void load_rows_interleaved(chunk_t (&a)[CPT], chunk_t (&b)[CPT], const void* ra, const void* rb,
+                                             const RowCut<Fmt>& cut) {
 #pragma unroll
-    for (int n = 0; n < CPT; ++n) c[n] = chunk_or_pad<Fmt, W>(c[n], n, nchunks);
+    for (int n = 0; n < CPT; ++n) {
+        const int off = cut.off(n * W + static_cast<int>(threadIdx.x));
+        a[n] = load_off(ra, off);
+        b[n] = load_off(rb, off);
+    }
+}
+
+// Chunk n of this thread as loaded by load_row<VEC>, with its padding.
+// Rounds before the row's end take no instruction for it.
+template <typename Fmt, int W>
+__device__ inline chunk_t chunk_or_pad(const chunk_t& c, int n, const RowCut<Fmt>& cut) {
+    if (!cut.template ragged<W>(n)) return c;
+    return pad_lead<Fmt>(c, cut.lead(n * W + static_cast<int>(threadIdx.x)));
+}
+
+// Apply the padding to every chunk of load_row<VEC>.
+template <typename Fmt, int W, int CPT>
+__device__ inline void pad_row_tail(chunk_t (&c)[CPT], const RowCut<Fmt>& cut) {
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) c[n] = chunk_or_pad<Fmt, W>(c[n], n, cut);
 }
 
 // Make register-resident chunks opaque to the optimiser at the start of a
@@ -301,96 +391,17 @@ __device__ inline double rescale(double S, float from, float to) {
     return __builtin_ldexp(S, int(fmaxf(from - to, -2048.0f)));
 }
 
-// fp32 accumulation, pairwise within a chunk.
-template <typename Fmt, int CPT>
-__device__ inline void row_stats(const chunk_t (&c)[CPT], float c2, float& K, float& S) {
-    constexpr int EPC = Fmt::kPerChunk;
-#pragma unroll
-    for (int n = 0; n < CPT; ++n) {
-        const float kn = fmaxf(K, ceilf(chunk_max<Fmt>(c[n]) * c2));
-        S = rescale(S, K, kn);
-        K = kn;
-        // While K is still -inf every element seen is -inf: a finite stand-in
-        // keeps 2^(x c2 - K) at 2^-inf = 0 instead of -inf + inf = NaN.
-        const float kx = fmaxf(K, -3.0e38f);
-        float e8[EPC];
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) e8[e] = exp2_fast(__builtin_fmaf(Fmt::get(c[n], e), c2, -kx));
-#pragma unroll
-        for (int w = 1; w < EPC; w <<= 1)
-#pragma unroll
-            for (int e = 0; e < EPC; e += 2 * w) e8[e] = e8[e] + e8[e + w];
-        S = S + e8[0];
-        __builtin_amdgcn_sched_barrier(0);  // one chunk in flight: bounded VGPRs
-    }
-}
-
-// row_stats over chunks from load_row_clamped: each chunk is padded as the
-// sweep takes it (after its load has landed).
-template <typename Fmt, int W, int CPT>
-__device__ inline void row_stats_tail(const chunk_t (&c)[CPT], int nchunks, float c2, float& K, float& S) {
-    constexpr int EPC = Fmt::kPerChunk;
-#pragma unroll
-    for (int n = 0; n < CPT; ++n) {
-        const chunk_t x = chunk_or_pad<Fmt, W>(c[n], n, nchunks);
-        const float kn = fmaxf(K, ceilf(chunk_max<Fmt>(x) * c2));
-        S = rescale(S, K, kn);
-        K = kn;
-        const float kx = fmaxf(K, -3.0e38f);  // see row_stats
-        float e8[EPC];
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) e8[e] = exp2_fast(__builtin_fmaf(Fmt::get(x, e), c2, -kx));
-#pragma unroll
-        for (int w = 1; w < EPC; w <<= 1)
-#pragma unroll
-            for (int e = 0; e < EPC; e += 2 * w) e8[e] = e8[e] + e8[e + w];
-        S = S + e8[0];
-        __builtin_amdgcn_sched_barrier(0);  // one chunk in flight: bounded VGPRs
-    }
-}
-
-// Two rows from load_rows_interleaved swept together: chunk n of both rows
-// in iteration n, in the order the loads were issued, each row folded exactly
-// as row_stats_tail folds it.  With second == false only the first row is
-// folded (its partner's loads are ignored).
-template <typename Fmt, int W, int CPT>
-__device__ inline void row_stats2_tail(const chunk_t (&a)[CPT], const chunk_t (&b)[CPT], int nchunks, float c2,
-                                       bool second, float& Ka, float& Sa, float& Kb, float& Sb) {
-    constexpr int EPC = Fmt::kPerChunk;
-#pragma unroll
-    for (int n = 0; n < CPT; ++n) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            if (r == 1 && !second) continue;
-            const chunk_t x = chunk_or_pad<Fmt, W>(r == 0 ? a[n] : b[n], n, nchunks);
-            float& K = r == 0 ? Ka : Kb;
-            float& S = r == 0 ? Sa : Sb;
-            const float kn = fmaxf(K, ceilf(chunk_max<Fmt>(x) * c2));
-            S = rescale(S, K, kn);
-            K = kn;
-            const float kx = fmaxf(K, -3.0e38f);  // see row_stats
-            float e8[EPC];
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) e8[e] = exp2_fast(__builtin_fmaf(Fmt::get(x, e), c2, -kx));
-#pragma unroll
-            for (int w = 1; w < EPC; w <<= 1)
-#pragma unroll
-                for (int e = 0; e < EPC; e += 2 * w) e8[e] = e8[e] + e8[e + w];
-            S = S + e8[0];
-        }
-        __builtin_amdgcn_sched_barrier(0);  // one chunk pair in flight: bounded VGPRs
-    }
-}
-
-// Fold one chunk into a thread's (K, S) exactly as row_stats does for each
-// of its chunks (for rows streamed from memory rather than held).
+// Fold one chunk into a thread's (K, S): fp32 accumulation, pairwise within
+// the chunk.
 template <typename Fmt>
 __device__ inline void fold_chunk(const chunk_t& x, float c2, float& K, float& S) {
     constexpr int EPC = Fmt::kPerChunk;
     const float kn = fmaxf(K, ceilf(chunk_max<Fmt>(x) * c2));
     S = rescale(S, K, kn);
     K = kn;
-    const float kx = fmaxf(K, -3.0e38f);  // see row_stats
+    // While K is still -inf every element seen is -inf: a finite stand-in
+    // keeps 2^(x c2 - K) at 2^-inf = 0 instead of -inf + inf = NaN.
+    const float kx = fmaxf(K, -3.0e38f);
     float e8[EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) e8[e] = exp2_fast(__builtin_fmaf(Fmt::get(x, e), c2, -kx));
@@ -401,7 +412,8 @@ __device__ inline void fold_chunk(const chunk_t& x, float c2, float& K, float& S
     S = S + e8[0];
 }
 
-// fold_chunk with every term accumulated in fp64 (as the fp64 row_stats).
+// The same with every term accumulated in fp64 (for quantities first-order
+// sensitive to the normaliser).
 template <typename Fmt>
 __device__ inline void fold_chunk(const chunk_t& x, float c2, float& K, double& S) {
     constexpr int EPC = Fmt::kPerChunk;
@@ -418,41 +430,42 @@ __device__ inline void fold_chunk(const chunk_t& x, float c2, float& K, double& 
     S += s0 + s1;
 }
 
-// Chunk ch of a row streamed from memory, or padding past its end.  VEC:
-// a 16-byte load (a chunk past the row re-reads the last one, replaced by
-// padding); otherwise element loads.
-template <typename Fmt, bool VEC>
-__device__ inline chunk_t stream_chunk(const void* row, int ch, int nchunks, int V) {
-    if constexpr (VEC) {
-        const bool in = ch < nchunks;
-        const chunk_t v = __builtin_nontemporal_load(static_cast<const chunk_t*>(row) + (in ? ch : nchunks - 1));
-        const chunk_t pad = pad_chunk<Fmt>();
-        return chunk_t{in ? v.x : pad.x, in ? v.y : pad.y, in ? v.z : pad.z, in ? v.w : pad.w};
-    } else {
-        return ch < nchunks ? Fmt::load_scalar(row, int64_t(ch) * Fmt::kPerChunk, V) : pad_chunk<Fmt>();
+// A row's statistics over chunks from load_row, in its precision Acc.  VEC:
+// each chunk is padded, in place, as the sweep takes it (after its load has
+// landed).
+template <typename Fmt, int W, int CPT, bool VEC, typename Acc>
+__device__ inline void row_stats(chunk_t (&c)[CPT], const RowCut<Fmt>& cut, float c2, float& K, Acc& S) {
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) {
+        if constexpr (VEC) c[n] = chunk_or_pad<Fmt, W>(c[n], n, cut);
+        fold_chunk<Fmt>(c[n], c2, K, S);
+        __builtin_amdgcn_sched_barrier(0);  // one chunk in flight: bounded VGPRs
     }
 }
 
-// fp64 accumulation of every term (for quantities first-order sensitive to
-// the normaliser).
-template <typename Fmt, int CPT>
-__device__ inline void row_stats(const chunk_t (&c)[CPT], float c2, float& K, double& S) {
-    constexpr int EPC = Fmt::kPerChunk;
+// Two rows from load_rows_interleaved swept together: chunk n of both rows
+// in iteration n, in the order the loads were issued, each row folded exactly
+// as row_stats folds it.  With second == false only the first row is folded
+// (its partner's loads are ignored).
+template <typename Fmt, int W, int CPT>
+__device__ inline void row_stats2(chunk_t (&a)[CPT], chunk_t (&b)[CPT], const RowCut<Fmt>& cut, float c2, bool second,
+                                  float& Ka, float& Sa, float& Kb, float& Sb) {
 #pragma unroll
     for (int n = 0; n < CPT; ++n) {
-        const float kn = fmaxf(K, ceilf(chunk_max<Fmt>(c[n]) * c2));
-        S = rescale(S, K, kn);
-        K = kn;
-        const float kx = fmaxf(K, -3.0e38f);  // see the fp32 version
-        double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-        for (int e = 0; e < EPC; e += 2) {
-            s0 += double(exp2_fast(__builtin_fmaf(Fmt::get(c[n], e), c2, -kx)));
-            s1 += double(exp2_fast(__builtin_fmaf(Fmt::get(c[n], e + 1), c2, -kx)));
+        a[n] = chunk_or_pad<Fmt, W>(a[n], n, cut);
+        fold_chunk<Fmt>(a[n], c2, Ka, Sa);
+        if (second) {
+            b[n] = chunk_or_pad<Fmt, W>(b[n], n, cut);
+            fold_chunk<Fmt>(b[n], c2, Kb, Sb);
         }
-        S += s0 + s1;
-        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);  // one chunk pair in flight: bounded VGPRs
     }
+}
+
+// Chunk n*W + tid of a row streamed from memory, padded.
+template <typename Fmt, int W>
+__device__ inline chunk_t stream_chunk(const void* row, int n, const RowCut<Fmt>& cut) {
+    return chunk_or_pad<Fmt, W>(load_off(row, cut.off(n * W + static_cast<int>(threadIdx.x))), n, cut);
 }
 
 // Merge (K, S) across the wave; every lane returns the wave's pair.

@@ -63,7 +63,6 @@ struct VerifyLaunch {
     uint32_t* records;   // [B*(K+1)] zero on entry and exit
     uint32_t* counters;  // [B]       zero on entry and exit
     SegStats* seg_stats;  // [B*(K+1)*kMaxSeg] greedy argmax partials, zero on entry and exit
-    bool vec;            // rows 16-byte aligned
     hipStream_t stream;
 };
 
@@ -85,7 +84,6 @@ struct DistillLaunch {
     double* slab_ws;           // [nslabs]
     uint32_t* slab_counters;   // [nslabs] zero on entry and exit
     uint32_t* done_counter;    // [1]      zero on entry and exit
-    bool vec;
     int cus;
     hipStream_t stream;
 };
@@ -107,8 +105,8 @@ bool pick_tile(int V, int per_chunk, RowTile* t);
 hipError_t launch_verify(const VerifyLaunch& L);
 hipError_t launch_distill(const DistillLaunch& L);
 
-// Segmented greedy verification: rows whose byte length and base are
-// 16-byte multiples.  Segments per row for V (false: V too large).
+// Segmented greedy verification (rows of at least one chunk).  Segments per
+// row for V (false: V out of range).
 bool greedy_segments(int V, int per_chunk, int* nseg);
 hipError_t launch_verify_greedy(const VerifyLaunch& L);
 
@@ -160,7 +158,6 @@ struct TreeLaunch {
     int32_t* path_nodes;
     uint32_t* records;   // [B*N] zero on entry and exit
     uint32_t* counters;  // [B]   zero on entry and exit
-    bool vec;
     int cus;  // compute units of the device
     hipStream_t stream;
 };
@@ -181,7 +178,6 @@ struct SampleLaunch {
     float beta;
     const float* u;
     int32_t* out;
-    bool vec;  // every row 16-byte aligned and V a whole number of chunks
     int cus;
     void* workspace;  // null, or sample_workspace_bytes(N) zeroed bytes: rows split over workgroups
     hipStream_t stream;
@@ -191,8 +187,8 @@ hipError_t launch_sample(const SampleLaunch& L);
 // and a 16-byte counter slot.
 constexpr size_t kSampleWsPerRow = 16 * 16 + 16;
 
-// Streaming (persistent-workgroup) distillation: rows whose byte length and
-// base are 16-byte multiples and whose V fits one of the streaming tiles.
+// Streaming (persistent-workgroup) distillation: rows of at least one chunk
+// whose V fits one of the streaming tiles.
 bool pick_stream_tile(int V, int per_chunk, RowTile* t);
 hipError_t launch_distill_stream(const DistillLaunch& L);
 
@@ -216,7 +212,6 @@ struct ShardLaunch {
     int32_t* accepted_len;
     int32_t* out_tokens;
     uint8_t* reject_mask;
-    bool vec;
     hipStream_t stream;
 };
 hipError_t launch_verify_shard(const ShardLaunch& L);

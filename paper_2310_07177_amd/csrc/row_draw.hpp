@@ -32,8 +32,8 @@ struct DrawShared {
 // nstar has masses m[] (sum s, added left to right from 0); target is the
 // point's offset inside the wave's cell.  The lanes' fixed-point chunk sums
 // are scanned to find the lane holding the target, which walks its elements
-// with the same left-to-right fp32 sums.  Returns the token on that lane and
-// -1 on the others.
+// with the same left-to-right fp32 sums.  Returns the element's place (chunk *
+// EPC + e; RowCut::token gives its id) on that lane and -1 on the others.
 template <int SH, int W, int EPC>
 __device__ inline int walk_chunk(const float (&m)[EPC], float s, uint64_t target, int nstar) {
     const int tid = threadIdx.x;
@@ -72,8 +72,8 @@ __device__ inline int walk_chunk(const float (&m)[EPC], float s, uint64_t target
 
 // Inverse-CDF draw over a register-resident row pair.  mass(t, d, e) returns
 // the non-negative fp32 mass of element e of the chunks t, d (0 for padding).
-// Returns the drawn token on exactly one thread and -1 on every other thread;
-// *z_zero is set (uniformly) when the total mass is zero.  The point drawn is
+// Returns the drawn element's place (chunk * EPC + e) on exactly one thread and
+// -1 on every other thread; *z_zero is set (uniformly) when the total mass is zero.  The point drawn is
 // floor(u * Z) in fixed point, or, when c_given >= 0, c_given itself (a point
 // already chosen in a larger CDF of which this row is one part); either is
 // clamped to Z - 1.
@@ -173,7 +173,7 @@ constexpr int kMaxStreamRounds = 16;
 // pass B, and must return the same values both times.  Cells are (round,
 // wave); chunk masses are summed left to right in fp32 and converted exactly
 // to 2^-SH fixed point, as in draw_inverse_cdf, so the CDF cells partition
-// [0, Z) exactly.  Returns the token on one thread and -1 on the others;
+// [0, Z) exactly.  Returns the element's place on one thread and -1 on the others;
 // *z_zero is set (uniformly) when the total mass is zero.  s_tot holds
 // R * (W / 64) cells.  All threads call it.
 template <int SH, int W, int EPC, typename MassFn>

@@ -56,23 +56,21 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(S
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int n = blockIdx.x;
     chunk_t tv[CPT], dv[CPT];
-    // Sampling from 16-byte rows: loads without padding (a row pair
-    // interleaved chunk by chunk), so that the statistics fold in as they
-    // land; the register copy is padded afterwards for the draw.
-    constexpr bool kFold = VEC && MODE != kModeGreedy;
-    const int nchunks = (a.V + EPC - 1) / EPC;
-    if constexpr (kFold && MIX) {
-        load_rows_interleaved<W, CPT>(tv, dv, a.p + int64_t(n) * a.p_stride, a.q + int64_t(n) * a.q_stride, nchunks);
-    } else if constexpr (kFold) {
-        load_row_clamped<W, CPT>(tv, a.p + int64_t(n) * a.p_stride, nchunks);
+    // The rows are loaded without padding (a row pair interleaved chunk by
+    // chunk) and the statistics pad each chunk as they take it, so they fold
+    // in as the loads land.
+    const RowCut<Fmt> cut(a.V);
+    if constexpr (VEC && MIX) {
+        load_rows_interleaved<Fmt, W, CPT>(tv, dv, a.p + int64_t(n) * a.p_stride, a.q + int64_t(n) * a.q_stride, cut);
     } else {
-        load_row<Fmt, W, CPT, VEC>(tv, a.p + int64_t(n) * a.p_stride, a.V);
-        if constexpr (MIX) load_row<Fmt, W, CPT, VEC>(dv, a.q + int64_t(n) * a.q_stride, a.V);
+        load_row<Fmt, W, CPT, VEC>(tv, a.p + int64_t(n) * a.p_stride, cut, a.V);
+        if constexpr (MIX) load_row<Fmt, W, CPT, VEC>(dv, a.q + int64_t(n) * a.q_stride, cut, a.V);
     }
 
     if constexpr (MODE == kModeGreedy) {
         // Argmax, lowest index on ties: within a thread indices grow with
         // (round, element), so a strict ">" keeps the first maximum.
+        if constexpr (VEC) pad_row_tail<Fmt, W, CPT>(tv, cut);
         float best = kNegInf;
         int bi = 0x7FFFFFFF;
 #pragma unroll
@@ -99,7 +97,7 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(S
                     bv = s_max[0][w];
                     g = s_idx[w];
                 }
-            a.out[n] = (bv > kNegInf && bv < -kNegInf) ? g : -1;
+            a.out[n] = (bv > kNegInf && bv < -kNegInf) ? (VEC ? cut.token(g) : g) : -1;
         }
         return;
     } else {
@@ -107,16 +105,11 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(S
         float Kp = kNegInf, Kq = kNegInf;
         {
             float sp = 0.0f, sq = 0.0f;
-            if constexpr (kFold && MIX) {
-                row_stats2_tail<Fmt, W, CPT>(tv, dv, nchunks, c2, true, Kp, sp, Kq, sq);
-                pad_row_tail<Fmt, W, CPT>(tv, nchunks);
-                pad_row_tail<Fmt, W, CPT>(dv, nchunks);
-            } else if constexpr (kFold) {
-                row_stats_tail<Fmt, W, CPT>(tv, nchunks, c2, Kp, sp);
-                pad_row_tail<Fmt, W, CPT>(tv, nchunks);
+            if constexpr (VEC && MIX) {
+                row_stats2<Fmt, W, CPT>(tv, dv, cut, c2, true, Kp, sp, Kq, sq);
             } else {
-                row_stats<Fmt, CPT>(tv, c2, Kp, sp);
-                if constexpr (MIX) row_stats<Fmt, CPT>(dv, c2, Kq, sq);
+                row_stats<Fmt, W, CPT, VEC>(tv, cut, c2, Kp, sp);
+                if constexpr (MIX) row_stats<Fmt, W, CPT, VEC>(dv, cut, c2, Kq, sq);
             }
             double dp = sp, dq = sq;
             wave_merge_stats(Kp, dp);
@@ -166,23 +159,17 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(S
             }
         };
         bool z_zero = false;
-        const int tok = draw_inverse_cdf<MIX ? kShiftMix : kShiftOne, W, CPT, EPC>(
+        const int at = draw_inverse_cdf<MIX ? kShiftMix : kShiftOne, W, CPT, EPC>(
             tv, dv, mass, a.u[n], s_tot, &s_draw, s_stage, &z_zero);
-        if (tok >= 0) s_tok = tok;
+        if (at >= 0) s_tok = VEC ? cut.token(at) : at;
         __syncthreads();
         if (tid == 0) a.out[n] = s_tok;  // -1 when no element carries mass
     }
 }
 
-template <typename Fmt, int W, int CPT, int MODE>
+template <typename Fmt, int W, int CPT, bool VEC, int MODE>
 hipError_t launch_mode(const SampleLaunch& L, const SampleArgs& a) {
-    const dim3 grid(unsigned(L.N)), block(W);
-    hipError_t e;
-    if (L.vec)
-        e = launch_kernel(&sample_kernel<Fmt, W, CPT, true, MODE>, grid, block, 0, L.stream, a);
-    else
-        e = launch_kernel(&sample_kernel<Fmt, W, CPT, false, MODE>, grid, block, 0, L.stream, a);
-    return e;
+    return launch_kernel(&sample_kernel<Fmt, W, CPT, VEC, MODE>, dim3(unsigned(L.N)), dim3(W), 0, L.stream, a);
 }
 
 // A mixture of rows too long to hold as a pair (beyond 8 chunks per thread of
@@ -191,7 +178,7 @@ hipError_t launch_mode(const SampleLaunch& L, const SampleArgs& a) {
 constexpr int kLongW = 1024;
 constexpr int kLongUnroll = 4;
 
-template <typename Fmt, bool VEC>
+template <typename Fmt>
 __global__ __launch_bounds__(kLongW, 1) void sample_mix_long_kernel(SampleArgs a) {
     constexpr int W = kLongW, NW = W / kWave, EPC = Fmt::kPerChunk, U = kLongUnroll;
     __shared__ float s_max[2][NW];
@@ -205,21 +192,22 @@ __global__ __launch_bounds__(kLongW, 1) void sample_mix_long_kernel(SampleArgs a
     const int V = a.V;
     const char* prow = a.p + int64_t(n) * a.p_stride;
     const char* qrow = a.q + int64_t(n) * a.q_stride;
-    const int nchunks = (V + EPC - 1) / EPC;
-    const int R = (nchunks + W - 1) / W;
+    const RowCut<Fmt> cut(V);
+    const int R = (cut.nchunks + W - 1) / W;
     const float c2 = a.c2;
     float Kp = kNegInf, Kq = kNegInf, sp = 0.0f, sq = 0.0f;
     for (int r0 = 0; r0 < R; r0 += U) {
         chunk_t xp[U], xq[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            xp[u] = stream_chunk<Fmt, VEC>(prow, (r0 + u) * W + tid, nchunks, V);
-            xq[u] = stream_chunk<Fmt, VEC>(qrow, (r0 + u) * W + tid, nchunks, V);
+            const int off = cut.off((r0 + u) * W + tid);
+            xp[u] = load_off(prow, off);
+            xq[u] = load_off(qrow, off);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            fold_chunk<Fmt>(xp[u], c2, Kp, sp);
-            fold_chunk<Fmt>(xq[u], c2, Kq, sq);
+            fold_chunk<Fmt>(chunk_or_pad<Fmt, W>(xp[u], r0 + u, cut), c2, Kp, sp);
+            fold_chunk<Fmt>(chunk_or_pad<Fmt, W>(xq[u], r0 + u, cut), c2, Kq, sq);
         }
     }
     {
@@ -256,9 +244,8 @@ __global__ __launch_bounds__(kLongW, 1) void sample_mix_long_kernel(SampleArgs a
     const float wp = float(double(a.beta) / Sp), wq = float((1.0 - double(a.beta)) / Sq);
     const float kp = Kp, kq = Kq;
     auto masses = [&](int r, float (&m)[EPC]) {
-        const int ch = r * W + tid;
-        const chunk_t tc = stream_chunk<Fmt, VEC>(prow, ch, nchunks, V);
-        const chunk_t dc = stream_chunk<Fmt, VEC>(qrow, ch, nchunks, V);
+        const chunk_t tc = stream_chunk<Fmt, W>(prow, r, cut);
+        const chunk_t dc = stream_chunk<Fmt, W>(qrow, r, cut);
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
             const float et = exp2_fast(__builtin_fmaf(Fmt::get(tc, e), c2, -kp));
@@ -267,8 +254,8 @@ __global__ __launch_bounds__(kLongW, 1) void sample_mix_long_kernel(SampleArgs a
         }
     };
     bool z_zero = false;
-    const int tok = draw_inverse_cdf_streamed<kShiftMix, W, EPC>(R, masses, a.u[n], s_tot, &s_draw, &z_zero);
-    if (tok >= 0) s_tok = tok;
+    const int at = draw_inverse_cdf_streamed<kShiftMix, W, EPC>(R, masses, a.u[n], s_tot, &s_draw, &z_zero);
+    if (at >= 0) s_tok = cut.token(at);
     __syncthreads();
     if (tid == 0) a.out[n] = s_tok;
 }
@@ -304,7 +291,7 @@ constexpr int kSamplePolls = 256;
 struct SplitSampleArgs {
     const char* row;   // row 0 of the sampled rows
     int64_t stride;    // bytes between rows
-    int N, V, nchunks, S, polls;
+    int N, V, S, polls;
     float c2;
     const float* u;
     int32_t* out;
@@ -386,9 +373,12 @@ __global__ __launch_bounds__(kSegSampleW) void sample_split_kernel(SplitSampleAr
     // The row's uniform is read with the chunks (a load after the exchange
     // would wait for the exchange's own memory operations).
     const float un = a.u[n];
+    const RowCut<Fmt> cut(a.V);
     chunk_t x[CPT];
 #pragma unroll
-    for (int r = 0; r < CPT; ++r) x[r] = stream_chunk<Fmt, true>(row, s * SEG + r * W + tid, a.nchunks, a.V);
+    for (int r = 0; r < CPT; ++r) x[r] = load_off(row, cut.off(s * SEG + r * W + tid));
+#pragma unroll
+    for (int r = 0; r < CPT; ++r) x[r] = chunk_or_pad<Fmt, W>(x[r], s * CPT + r, cut);
     if (tid == 0) s_tok = -1;  // ordered before the walk by the statistics' barriers
     float k;
     double T;
@@ -438,7 +428,7 @@ __global__ __launch_bounds__(kSegSampleW) void sample_split_kernel(SplitSampleAr
             if (j == s) continue;
             chunk_t y[CPT];
 #pragma unroll
-            for (int r = 0; r < CPT; ++r) y[r] = stream_chunk<Fmt, true>(row, j * SEG + r * W + tid, a.nchunks, a.V);
+            for (int r = 0; r < CPT; ++r) y[r] = stream_chunk<Fmt, W>(row, j * CPT + r, cut);
             float kj;
             double Tj;
             bool ej;
@@ -515,7 +505,7 @@ __global__ __launch_bounds__(kSegSampleW) void sample_split_kernel(SplitSampleAr
                     if (pick < 0 && fixed40(racc) > want) pick = e;
                 }
                 if (pick < 0) pick = last_pos >= 0 ? last_pos : 0;
-                s_tok = ((s * SEG + r * W + tid) * EPC) + pick;
+                s_tok = cut.token(((s * SEG + r * W + tid) * EPC) + pick);
             }
         }
     }
@@ -537,13 +527,12 @@ int sample_polls() {
 }
 
 template <typename Fmt, int CPT>
-hipError_t launch_split(const SampleLaunch& L, const SampleArgs& a, int nchunks, int S) {
+hipError_t launch_split(const SampleLaunch& L, const SampleArgs& a, int S) {
     SplitSampleArgs sa{};
     sa.row = a.p;
     sa.stride = a.p_stride;
     sa.N = a.N;
     sa.V = a.V;
-    sa.nchunks = nchunks;
     sa.S = S;
     sa.polls = sample_polls();
     sa.c2 = a.c2;
@@ -556,35 +545,36 @@ hipError_t launch_split(const SampleLaunch& L, const SampleArgs& a, int nchunks,
                          L.stream, sa);
 }
 
-// The split applies to one-row sampling (T > 0, beta 0 or 1) of 16-byte rows
-// when one workgroup per row would leave most CUs idle.
+// The split applies to one-row sampling (T > 0, beta 0 or 1) when one
+// workgroup per row would leave most CUs idle.
 template <typename Fmt>
 bool try_split(const SampleLaunch& L, const SampleArgs& a, hipError_t* e) {
-    if (!L.workspace || !L.vec || !(L.temperature > 0.0f) || (L.beta > 0.0f && L.beta < 1.0f)) return false;
+    if (!L.workspace || !(L.temperature > 0.0f) || (L.beta > 0.0f && L.beta < 1.0f)) return false;
     if (L.N >= 2 * L.cus) return false;
     const int nchunks = (L.V + Fmt::kPerChunk - 1) / Fmt::kPerChunk;
     const int s2 = (nchunks + 2 * kSegSampleW - 1) / (2 * kSegSampleW);
     const int s4 = (nchunks + 4 * kSegSampleW - 1) / (4 * kSegSampleW);
     if (s2 >= 2 && s2 <= kMaxSampleSegments && int64_t(L.N) * s2 <= 4 * int64_t(L.cus)) {
-        *e = launch_split<Fmt, 2>(L, a, nchunks, s2);
+        *e = launch_split<Fmt, 2>(L, a, s2);
         return true;
     }
     if (s4 >= 2 && s4 <= kMaxSampleSegments && int64_t(L.N) * s4 <= 4 * int64_t(L.cus)) {
-        *e = launch_split<Fmt, 4>(L, a, nchunks, s4);
+        *e = launch_split<Fmt, 4>(L, a, s4);
         return true;
     }
     return false;
 }
 
-template <typename Fmt, int W, int CPT>
+template <typename Fmt, int W, int CPT, bool VEC>
 hipError_t launch_tile(const SampleLaunch& L, const SampleArgs& a) {
-    if (L.temperature == 0.0f) return launch_mode<Fmt, W, CPT, kModeGreedy>(L, a);
-    if (L.beta > 0.0f && L.beta < 1.0f) return launch_mode<Fmt, W, CPT, kModeMix>(L, a);
-    return launch_mode<Fmt, W, CPT, kModeOne>(L, a);
+    if (L.temperature == 0.0f) return launch_mode<Fmt, W, CPT, VEC, kModeGreedy>(L, a);
+    if (L.beta > 0.0f && L.beta < 1.0f) return launch_mode<Fmt, W, CPT, VEC, kModeMix>(L, a);
+    return launch_mode<Fmt, W, CPT, VEC, kModeOne>(L, a);
 }
 
 template <typename Fmt>
 hipError_t launch_fmt(const SampleLaunch& L, const SampleArgs& a) {
+    if (L.V < Fmt::kPerChunk) return launch_tile<Fmt, 256, 1, false>(L, a);  // shorter than one chunk
     hipError_t se;
     if (try_split<Fmt>(L, a, &se)) return se;
     RowTile t;
@@ -592,12 +582,10 @@ hipError_t launch_fmt(const SampleLaunch& L, const SampleArgs& a) {
         // Longer rows: a mixture streams its row pair; one row (or an
         // argmax) fits the resident 1024 x 16 tile without spilling.
         const bool mix = L.temperature > 0.0f && L.beta > 0.0f && L.beta < 1.0f;
-        const dim3 grid(unsigned(L.N)), block(kLongW);
         if (mix)
-            return L.vec ? launch_kernel(&sample_mix_long_kernel<Fmt, true>, grid, block, 0, L.stream, a)
-                         : launch_kernel(&sample_mix_long_kernel<Fmt, false>, grid, block, 0, L.stream, a);
-        if (L.temperature == 0.0f) return launch_mode<Fmt, 1024, 16, kModeGreedy>(L, a);
-        return launch_mode<Fmt, 1024, 16, kModeOne>(L, a);
+            return launch_kernel(&sample_mix_long_kernel<Fmt>, dim3(unsigned(L.N)), dim3(kLongW), 0, L.stream, a);
+        if (L.temperature == 0.0f) return launch_mode<Fmt, 1024, 16, true, kModeGreedy>(L, a);
+        return launch_mode<Fmt, 1024, 16, true, kModeOne>(L, a);
     }
     // Fewer rows than two per CU: the rows' latency is the cost, so each row
     // gets the widest workgroup (half the elements per thread).
@@ -606,14 +594,14 @@ hipError_t launch_fmt(const SampleLaunch& L, const SampleArgs& a) {
         t = RowTile{1024, L.V <= 2 * per ? 2 : (L.V <= 4 * per ? 4 : 8)};
     }
     switch (t.W * 100 + t.CPT) {
-        case 102402: return launch_tile<Fmt, 1024, 2>(L, a);
-        case 102404: return launch_tile<Fmt, 1024, 4>(L, a);
-        case 25601: return launch_tile<Fmt, 256, 1>(L, a);
-        case 25602: return launch_tile<Fmt, 256, 2>(L, a);
-        case 25604: return launch_tile<Fmt, 256, 4>(L, a);
-        case 51204: return launch_tile<Fmt, 512, 4>(L, a);
-        case 51208: return launch_tile<Fmt, 512, 8>(L, a);
-        case 102408: return launch_tile<Fmt, 1024, 8>(L, a);
+        case 102402: return launch_tile<Fmt, 1024, 2, true>(L, a);
+        case 102404: return launch_tile<Fmt, 1024, 4, true>(L, a);
+        case 25601: return launch_tile<Fmt, 256, 1, true>(L, a);
+        case 25602: return launch_tile<Fmt, 256, 2, true>(L, a);
+        case 25604: return launch_tile<Fmt, 256, 4, true>(L, a);
+        case 51204: return launch_tile<Fmt, 512, 4, true>(L, a);
+        case 51208: return launch_tile<Fmt, 512, 8, true>(L, a);
+        case 102408: return launch_tile<Fmt, 1024, 8, true>(L, a);
         default: return hipErrorInvalidValue;
     }
 }

@@ -31,25 +31,63 @@ __device__ inline rsrc_t make_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kRsrcWord3);
 }
 
-// Chunk n of this thread (byte offset (n*W + tid)*16).  Out-of-range chunks
-// read as zeros.
-template <int W>
-__device__ inline chunk_t load_chunk(rsrc_t r, int n) {
-    const int off = (n * W + static_cast<int>(threadIdx.x)) * 16;
+// The streaming tiles are chosen so that only the last of a row's CPT rounds
+// holds padding (RowCut); rows need not be aligned beyond their elements.
+// This thread's chunk of that round: its leading padding elements and its
+// byte offset in the row (past the row's end if it is all padding).  ragged
+// says whether any lane of the wave holds padding: the other waves skip its
+// handling on one scalar branch (lane by lane it cost the fused kernel 2 %).
+struct LastChunk {
+    int lead, off;
+    bool ragged;
+};
+template <typename Fmt, int W, int CPT>
+__device__ inline LastChunk last_chunk(int V) {
+    const RowCut<Fmt> cut(V);
+    const int ch = (CPT - 1) * W + static_cast<int>(threadIdx.x);
+    const int lead = cut.lead(ch);
+    return LastChunk{lead, ch == cut.nchunks - 1 ? int(cut.last_off) : ch * 16, __ballot(lead != 0) != 0};
+}
+
+// Chunk of round n of this thread; chunks past the row read as zeros.
+template <int W, int CPT>
+__device__ inline chunk_t load_round(rsrc_t r, int n, const LastChunk& last) {
+    const int off = n == CPT - 1 ? last.off : (n * W + static_cast<int>(threadIdx.x)) * 16;
     return __builtin_bit_cast(chunk_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kStreamAux));
 }
 
-template <int W>
-__device__ inline void store_chunk(rsrc_t r, int n, const chunk_t& c) {
-    const int off = (n * W + static_cast<int>(threadIdx.x)) * 16;
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) int, c),
-                                           r, off, 0, kStreamAux);
+template <typename Fmt, int W, int CPT>
+__device__ inline void store_round(rsrc_t r, int n, const chunk_t& c, const LastChunk& last) {
+    const int off = n == CPT - 1 ? last.off : (n * W + static_cast<int>(threadIdx.x)) * 16;
+    if (n < CPT - 1 || !last.ragged || last.lead == 0) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) int, c), r, off,
+                                               0, kStreamAux);
+    } else if (last.lead < Fmt::kPerChunk) {  // the last chunk's own elements
+        const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+        int lead = last.lead;
+        asm volatile("" : "+v"(lead));  // compared here, not hoisted (see pad_lead)
+#pragma unroll
+        for (int e = 0; e < Fmt::kPerChunk; ++e) {
+            if (e < lead) continue;
+            const int eoff = off + e * Fmt::kBytes;
+            if constexpr (Fmt::kPerChunk == 8)
+                __builtin_amdgcn_raw_buffer_store_b16(static_cast<unsigned short>(w[e >> 1] >> (16 * (e & 1))), r, eoff,
+                                                      0, 0);
+            else
+                __builtin_amdgcn_raw_buffer_store_b32(w[e], r, eoff, 0, 0);
+        }
+    }
 }
 
-// Chunk c of a row, whoever holds it (byte offset c*16).
-__device__ inline void store_chunk_at(rsrc_t r, int c, const chunk_t& v) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) int, v), r, c * 16,
-                                           0, kStreamAux);
+// Zeros over a whole row, by W threads.
+template <int W>
+__device__ inline void zero_row(rsrc_t r, uint32_t row_bytes, int tid) {
+    typedef int int4_t __attribute__((ext_vector_type(4)));
+    const int whole = int(row_bytes & ~15u);
+    for (int off = tid * 16; off < whole; off += W * 16)
+        __builtin_amdgcn_raw_buffer_store_b128(int4_t{0, 0, 0, 0}, r, off, 0, kStreamAux);
+    for (int off = whole + tid * 2; off < int(row_bytes); off += W * 2)
+        __builtin_amdgcn_raw_buffer_store_b16(static_cast<unsigned short>(0), r, off, 0, 0);
 }
 
 // Uniform (scalar-cache) loads of small per-row arguments.  The address must
@@ -65,18 +103,6 @@ __device__ inline uint32_t scalar_load_u8(const uint8_t* base, int64_t i) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(base) + uintptr_t(i);
     const uint32_t w = scalar_load(reinterpret_cast<const uint32_t*>(a & ~uintptr_t(3)));
     return (w >> (8 * (a & 3))) & 0xFFu;
-}
-
-// Element j of a logit row as fp32, through the aligned dword that holds it
-// (the row itself is 16-byte aligned on the streaming path).
-template <typename Fmt>
-__device__ inline float scalar_load_logit(const void* row, int j) {
-    if constexpr (Fmt::kBytes == 2) {
-        const uint32_t w = scalar_load(static_cast<const uint32_t*>(row) + (j >> 1));
-        return (j & 1) ? __uint_as_float(w & 0xFFFF0000u) : __uint_as_float(w << 16);
-    } else {
-        return scalar_load(static_cast<const float*>(row) + j);
-    }
 }
 
 // The per-thread shift of a row: the whole number ceil(max * c2) over the
@@ -95,14 +121,13 @@ __device__ inline float first_chunk_shift(const chunk_t& c, float c2) {
     return shift_of_max(chunk_max<Fmt>(c), c2);
 }
 
-// The largest element of a thread's CPT chunks of one row (pad_last: the
-// last chunk is padding), element by element.
+// The largest element of a thread's CPT chunks of one row, element by element.
 template <typename Fmt, int CPT>
-__device__ inline float chunks_max_exact(const chunk_t (&x)[CPT], bool pad_last) {
+__device__ inline float chunks_max_exact(const chunk_t (&x)[CPT], int lead) {
     float m = kNegInf;
 #pragma unroll
     for (int r = 0; r < CPT; ++r) {
-        const chunk_t c = (r == CPT - 1 && pad_last) ? pad_chunk<Fmt>() : x[r];
+        const chunk_t c = (r == CPT - 1 && lead != 0) ? pad_lead<Fmt>(x[r], lead) : x[r];
         m = fmaxf(m, chunk_max<Fmt>(c));
     }
     return m;
@@ -115,10 +140,11 @@ __device__ inline float chunks_max_exact(const chunk_t (&x)[CPT], bool pad_last)
 // magnitudes below 2^121, and the winning pattern is the bf16 maximum.  The
 // f16 maximum propagates NaN, so a thread holding a pattern outside that
 // range (an infinity, a NaN, a magnitude of 2^121 or more) or only padding
-// (f16 -inf) gets an unusable result and is decided element by element.
-// Either way the value is the exact maximum.
+// (f16 -inf) gets an unusable result and is decided element by element, as is
+// the thread whose last chunk is part padding.  Either way the value is the
+// exact maximum.
 template <typename Fmt, int CPT>
-__device__ inline float chunks_max(const chunk_t (&x)[CPT], bool pad_last) {
+__device__ inline float chunks_max(const chunk_t (&x)[CPT], const LastChunk& last) {
     if constexpr (Fmt::kPerChunk == 8) {
         typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
         constexpr uint32_t kNegInfPair = 0xFC00FC00u;  // f16 -inf in both halves
@@ -128,15 +154,16 @@ __device__ inline float chunks_max(const chunk_t (&x)[CPT], bool pad_last) {
 #pragma unroll
         for (int r = 0; r < CPT - 1; ++r)
             m = mx(mx(mx(m, H(x[r].x)), mx(H(x[r].y), H(x[r].z))), H(x[r].w));
-        // The last chunk joins unless it is padding (one select).
+        // The last chunk joins unless it holds padding (one select).
         const chunk_t& l = x[CPT - 1];
         const h2_t ml = mx(mx(mx(m, H(l.x)), mx(H(l.y), H(l.z))), H(l.w));
-        m = pad_last ? m : ml;
+        if (!last.ragged || last.lead == 0) m = ml;
         const uint32_t b = __builtin_bit_cast(uint32_t, m);
         const float lo = __uint_as_float(b << 16), hi = __uint_as_float(b & 0xFFFF0000u);
-        if (__builtin_fabsf(lo) < 0x1p121f && __builtin_fabsf(hi) < 0x1p121f) return fmaxf(lo, hi);
+        const bool part = last.ragged && last.lead != 0 && last.lead != Fmt::kPerChunk;
+        if (__builtin_fabsf(lo) < 0x1p121f && __builtin_fabsf(hi) < 0x1p121f && !part) return fmaxf(lo, hi);
     }
-    return chunks_max_exact<Fmt, CPT>(x, pad_last);
+    return chunks_max_exact<Fmt, CPT>(x, last.lead);
 }
 
 // The thread index through an opaque copy: lane and wave numbers derived from

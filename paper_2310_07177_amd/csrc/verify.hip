@@ -222,15 +222,14 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void verify_kernel(V
         dy_raw = Fmt::load_raw(drow, bonus ? 0 : y);
     }
     __builtin_amdgcn_sched_barrier(0);
-    // Sampling with 16-byte rows: the rows are loaded without padding and the
-    // statistics pad each chunk as they take it, so they fold in as the
-    // loads land; the register copy is padded afterwards for the draw.
-    constexpr bool kFold = VEC && !GREEDY;
-    const int nchunks = (V + EPC - 1) / EPC;
+    // The rows are loaded without padding and the statistics pad each chunk
+    // as they take it, so they fold in as the loads land.
+    const RowCut<Fmt> cut(V);
     chunk_t tv[CPT];
-    if constexpr (!kFold) load_row<Fmt, W, CPT, VEC>(tv, trow, V);
 
     if constexpr (GREEDY) {
+        static_assert(!VEC, "rows of a chunk or more take the segmented greedy kernels");
+        load_row<Fmt, W, CPT, VEC>(tv, trow, cut, V);
         // Target argmax, lowest index on ties: within a thread indices grow
         // with (n, e), so a strict ">" keeps the first maximum.
         float best = kNegInf;
@@ -273,22 +272,22 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void verify_kernel(V
         const float c2 = a.c2;
         // The draft row is read only for proposal rows.
         chunk_t dv[CPT];
-        if constexpr (kFold)
-            load_rows_interleaved<W, CPT>(tv, dv, trow, drow, nchunks);
-        else
-            load_row<Fmt, W, CPT, VEC>(dv, drow, V);
+        if constexpr (VEC) {
+            load_rows_interleaved<Fmt, W, CPT>(tv, dv, trow, drow, cut);
+        } else {
+            load_row<Fmt, W, CPT, VEC>(tv, trow, cut, V);
+            load_row<Fmt, W, CPT, VEC>(dv, drow, cut, V);
+        }
 
         // Row statistics (K, S), folded in chunk by chunk as the loads land.
         float Kt = kNegInf, Kd = kNegInf;
         {
             float st = 0.0f, sd = 0.0f;
-            if constexpr (kFold) {
-                row_stats2_tail<Fmt, W, CPT>(tv, dv, nchunks, c2, !bonus, Kt, st, Kd, sd);
-                pad_row_tail<Fmt, W, CPT>(tv, nchunks);
-                pad_row_tail<Fmt, W, CPT>(dv, nchunks);
+            if constexpr (VEC) {
+                row_stats2<Fmt, W, CPT>(tv, dv, cut, c2, !bonus, Kt, st, Kd, sd);
             } else {
-                row_stats<Fmt, CPT>(tv, c2, Kt, st);
-                if (!bonus) row_stats<Fmt, CPT>(dv, c2, Kd, sd);
+                row_stats<Fmt, W, CPT, false>(tv, cut, c2, Kt, st);
+                if (!bonus) row_stats<Fmt, W, CPT, false>(dv, cut, c2, Kd, sd);
             }
             double dt = st, dd = sd;
             wave_merge_stats(Kt, dt);
@@ -388,8 +387,8 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void verify_kernel(V
                 return fmaxf(__builtin_fmaf(-qt, rho, pt), 0.0f);
             };
             bool z_zero = false;
-            const int tok = draw_inverse_cdf<kFixedShift, W, CPT, EPC>(tv, dv, mass, u, s_tot, &s_draw, s_stage, &z_zero);
-            if (tok >= 0) s_tok = tok;
+            const int at = draw_inverse_cdf<kFixedShift, W, CPT, EPC>(tv, dv, mass, u, s_tot, &s_draw, s_stage, &z_zero);
+            if (at >= 0) s_tok = VEC ? cut.token(at) : at;
             if (!z_zero || use_p) break;
             use_p = true;
         }
@@ -416,7 +415,7 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void verify_kernel(V
 constexpr int kLongW = 1024;
 constexpr int kLongUnroll = 4;
 
-template <typename Fmt, bool VEC>
+template <typename Fmt>
 __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
     constexpr int W = kLongW, NW = W / kWave, EPC = Fmt::kPerChunk, U = kLongUnroll;
     __shared__ float s_max[2][NW];
@@ -470,8 +469,8 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
         dy_raw = Fmt::load_raw(drow, y);
     }
     const float c2 = a.c2;
-    const int nchunks = (V + EPC - 1) / EPC;
-    const int R = (nchunks + W - 1) / W;
+    const RowCut<Fmt> cut(V);
+    const int R = (cut.nchunks + W - 1) / W;
 
     // Statistics, U rounds of loads at a time.
     float Kt = kNegInf, Kd = kNegInf, st = 0.0f, sd = 0.0f;
@@ -479,14 +478,14 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
         chunk_t xt[U], xd[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int ch = (r0 + u) * W + tid;
-            xt[u] = stream_chunk<Fmt, VEC>(trow, ch, nchunks, V);
-            if (!bonus) xd[u] = stream_chunk<Fmt, VEC>(drow, ch, nchunks, V);
+            const int off = cut.off((r0 + u) * W + tid);
+            xt[u] = load_off(trow, off);
+            if (!bonus) xd[u] = load_off(drow, off);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            fold_chunk<Fmt>(xt[u], c2, Kt, st);
-            if (!bonus) fold_chunk<Fmt>(xd[u], c2, Kd, sd);
+            fold_chunk<Fmt>(chunk_or_pad<Fmt, W>(xt[u], r0 + u, cut), c2, Kt, st);
+            if (!bonus) fold_chunk<Fmt>(chunk_or_pad<Fmt, W>(xd[u], r0 + u, cut), c2, Kd, sd);
         }
     }
     {
@@ -563,9 +562,8 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
         const bool p_only = use_p;
         const float kt = Kt, kd = Kd;
         auto masses = [&](int r, float (&m)[EPC]) {
-            const int ch = r * W + tid;
-            const chunk_t tc = stream_chunk<Fmt, VEC>(trow, ch, nchunks, V);
-            const chunk_t dc = p_only ? tc : stream_chunk<Fmt, VEC>(drow, ch, nchunks, V);
+            const chunk_t tc = stream_chunk<Fmt, W>(trow, r, cut);
+            const chunk_t dc = p_only ? tc : stream_chunk<Fmt, W>(drow, r, cut);
 #pragma unroll
             for (int e = 0; e < EPC; ++e) {
                 const float pt = exp2_fast(__builtin_fmaf(Fmt::get(tc, e), c2, -kt));
@@ -578,8 +576,8 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
             }
         };
         bool z_zero = false;
-        const int tok = draw_inverse_cdf_streamed<kFixedShift, W, EPC>(R, masses, u, s_tot, &s_draw, &z_zero);
-        if (tok >= 0) s_tok = tok;
+        const int at = draw_inverse_cdf_streamed<kFixedShift, W, EPC>(R, masses, u, s_tot, &s_draw, &z_zero);
+        if (at >= 0) s_tok = cut.token(at);
         if (!z_zero || use_p) break;
         use_p = true;
         __syncthreads();  // s_tot and s_draw are reused
@@ -591,44 +589,26 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
     }
 }
 
-template <typename Fmt>
-hipError_t launch_long(const VerifyLaunch& L, const VerifyArgs& a) {
-    const dim3 grid(unsigned(L.B) * unsigned(L.K + 1)), block(kLongW);
-    return L.vec ? launch_kernel(&verify_long_kernel<Fmt, true>, grid, block, 0, L.stream, a)
-                 : launch_kernel(&verify_long_kernel<Fmt, false>, grid, block, 0, L.stream, a);
-}
-
 template <typename Fmt, int W, int CPT>
 hipError_t launch_tile(const VerifyLaunch& L, const VerifyArgs& a) {
     const dim3 grid(unsigned(L.B) * unsigned(L.K + 1)), block(W);
-    const bool greedy = L.temperature == 0.0f;
-    hipError_t e;
-    if (L.vec) {
-        if (greedy)
-            e = launch_kernel(&verify_kernel<Fmt, W, CPT, true, true>, grid, block, 0, L.stream, a);
-        else
-            e = launch_kernel(&verify_kernel<Fmt, W, CPT, true, false>, grid, block, 0, L.stream, a);
-    } else {
-        if (greedy)
-            e = launch_kernel(&verify_kernel<Fmt, W, CPT, false, true>, grid, block, 0, L.stream, a);
-        else
-            e = launch_kernel(&verify_kernel<Fmt, W, CPT, false, false>, grid, block, 0, L.stream, a);
-    }
-    return e;
+    return launch_kernel(&verify_kernel<Fmt, W, CPT, true, false>, grid, block, 0, L.stream, a);
 }
 
 template <typename Fmt>
 hipError_t launch_fmt(const VerifyLaunch& L, const VerifyArgs& a) {
+    const dim3 grid(unsigned(L.B) * unsigned(L.K + 1));
+    if (L.V < Fmt::kPerChunk) {  // rows shorter than one chunk, element by element
+        return L.temperature == 0.0f
+                   ? launch_kernel(&verify_kernel<Fmt, 256, 1, false, true>, grid, dim3(256), 0, L.stream, a)
+                   : launch_kernel(&verify_kernel<Fmt, 256, 1, false, false>, grid, dim3(256), 0, L.stream, a);
+    }
+    if (!(L.temperature > 0.0f)) return hipErrorInvalidValue;  // the segmented greedy kernels take these
     RowTile t;
     if (!pick_tile(L.V, Fmt::kPerChunk, &t)) {
         if (L.V > max_vocab_for(Fmt::kPerChunk)) return hipErrorInvalidValue;
-        // Rows longer than the largest resident tile: streamed (sampling).
-        // Greedy rows of that length take the resident 1024 x 16 tile, which
-        // holds one row per thread without spilling.
-        if (L.temperature > 0.0f) return launch_long<Fmt>(L, a);
-        const dim3 grid(unsigned(L.B) * unsigned(L.K + 1)), block(1024);
-        return L.vec ? launch_kernel(&verify_kernel<Fmt, 1024, 16, true, true>, grid, block, 0, L.stream, a)
-                     : launch_kernel(&verify_kernel<Fmt, 1024, 16, false, true>, grid, block, 0, L.stream, a);
+        // Rows longer than the largest resident tile: streamed.
+        return launch_kernel(&verify_long_kernel<Fmt>, grid, dim3(kLongW), 0, L.stream, a);
     }
     switch (t.W * 100 + t.CPT) {
         case 25601: return launch_tile<Fmt, 256, 1>(L, a);

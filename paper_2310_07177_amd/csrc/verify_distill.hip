@@ -88,7 +88,6 @@ struct FusedArgs {
     int B, K, V;
     int G;                     // workgroups in the grid
     int nitems;                // B*K + B
-    int nchunks;
     uint32_t row_bytes;
     int seq_step;              // items k and k - seq_step of a workgroup share a sequence
     int erridx;                // distil the first rejected row of each sequence (not `mask`)
@@ -405,7 +404,6 @@ __device__ inline void finish_fused(const FusedTail& a, const double* s_part) {
     const int per_pass = W / seg;
     const int j = tid & (seg - 1), base = lane & ~(seg - 1);
     const uint64_t segmask = (seg == 32 ? 0xFFFFFFFFull : 0xFFFFull) << base;
-    const int nchunks = int(a.row_bytes / 16);
     // The loss partials and the mask are requested before the records, so
     // that one round trip brings all of them.
     double sm = 0.0, cn = 0.0;
@@ -463,7 +461,7 @@ __device__ inline void finish_fused(const FusedTail& a, const double* s_part) {
                 for (int e = 0; e < n; ++e) {
                     const rsrc_t gr =
                         make_rsrc(static_cast<char*>(a.grad_out) + int64_t(s_extra[e]) * a.row_bytes, a.row_bytes);
-                    for (int c = tid; c < nchunks; c += W) store_chunk_at(gr, c, chunk_t{0u, 0u, 0u, 0u});
+                    zero_row<W>(gr, a.row_bytes, tid);
                 }
             }
             __syncthreads();
@@ -523,7 +521,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
     // (about a microsecond), and no argument is read again later.
     asm volatile("" ::"s"(a.target), "s"(a.draft), "s"(a.tokens), "s"(a.draft_len), "s"(a.u_accept),
                  "s"(a.u_resample), "s"(a.mask));
-    asm volatile("" ::"s"(a.B), "s"(a.K), "s"(a.V), "s"(a.G), "s"(a.nitems), "s"(a.nchunks), "s"(a.row_bytes),
+    asm volatile("" ::"s"(a.B), "s"(a.K), "s"(a.V), "s"(a.G), "s"(a.nitems), "s"(a.row_bytes),
                  "s"(a.seq_step), "s"(a.erridx), "s"(a.max_polls), "s"(a.c2), "s"(a.inv_tau), "s"(a.beta));
     asm volatile("" ::"s"(a.c2d), "s"(a.betad), "s"(a.ombd), "s"(a.records), "s"(a.dec), "s"(a.row_loss_out),
                  "s"(a.grad_out), "s"(a.part_ws));
@@ -531,7 +529,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
     const int tid = threadIdx.x;
     const int G = a.G;
     const float c2 = a.c2;
-    const bool last_ok = (CPT - 1) * W + tid < a.nchunks;
+    const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
     const float beta = a.beta, omb = 1.0f - a.beta;
 
     chunk_t rt[CPT], rs[CPT];
@@ -589,8 +587,8 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
             make_rsrc(fload && first.drow ? first.drow : a.target, fload && first.drow ? a.row_bytes : 0u);
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
-            rt[r] = load_chunk<W>(ftr, r);
-            rs[r] = load_chunk<W>(fsr, r);
+            rt[r] = load_round<W, CPT>(ftr, r, last);
+            rs[r] = load_round<W, CPT>(fsr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (t < nk) s_items[t] = encode_item<Fmt>(a, sc, t, finish_meta(a, ml));
@@ -666,8 +664,8 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
             // shift k is taken over all its chunks: every cached value is at
             // most 1 and no sum leaves the fp32 range.
             if (live) {
-                const float mt = chunks_max<Fmt, CPT>(rt, !last_ok);
-                const float ms = chunks_max<Fmt, CPT>(rs, !last_ok);
+                const float mt = chunks_max<Fmt, CPT>(rt, last);
+                const float ms = chunks_max<Fmt, CPT>(rs, last);
                 kc_t = shift_of_max(mt, c2);
                 kc_s = shift_of_max(ms, c2);
             }
@@ -676,13 +674,14 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
         for (int r = 0; r < CPT; ++r) {
             if (live) {
                 chunk_t xt = rt[r], xs = rs[r];
-                if (r == CPT - 1 && !last_ok) {
-                    xt = pad_chunk<Fmt>();
-                    xs = pad_chunk<Fmt>();
+                if (r == CPT - 1 && last.ragged) {
+                    xt = pad_lead<Fmt>(xt, last.lead);
+                    xs = pad_lead<Fmt>(xs, last.lead);
                 }
                 if (vlive && !cur.bonus && r * W + tid == ychunk) {
-                    s_y[k & 1][0] = Fmt::get(xt, cur.y - ychunk * EPC);
-                    s_y[k & 1][1] = Fmt::get(xs, cur.y - ychunk * EPC);
+                    const int ye = cur.y - (r == CPT - 1 ? last.off / Fmt::kBytes : ychunk * EPC);
+                    s_y[k & 1][0] = Fmt::get(xt, ye);
+                    s_y[k & 1][1] = Fmt::get(xs, ye);
                 }
                 if (!XV && r == 0) {
                     kc_t = first_chunk_shift<Fmt>(xt, c2);
@@ -724,8 +723,8 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
                 S_t = r == 0 ? double(st) : S_t + double(st);
                 S_s = r == 0 ? double(ss) : S_s + double(ss);
             }
-            rt[r] = load_chunk<W>(ntr, r);
-            rs[r] = load_chunk<W>(nsr, r);
+            rt[r] = load_round<W, CPT>(ntr, r, last);
+            rs[r] = load_round<W, CPT>(nsr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
         // The record of an item that is not tested (a proposal outside the
@@ -747,7 +746,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
         if (!live) {
             if (cur.grow >= 0 && a.grad_out) {
 #pragma unroll
-                for (int r = 0; r < CPT; ++r) store_chunk<W>(gr, r, chunk_t{0u, 0u, 0u, 0u});
+                for (int r = 0; r < CPT; ++r) store_round<Fmt, W, CPT>(gr, r, chunk_t{0u, 0u, 0u, 0u}, last);
             }
             __syncthreads();  // every item has a barrier (the live ones: the merge)
         } else {
@@ -877,6 +876,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
                     if (tok < 0)
                         tok = draw_cached<W, CPT, EPC, false>(mass(kTarget{}), mass_at(kTarget{}), cur.u_res,
                                                               s_cell, &s_z, &s_tok);
+                    if (tok >= 0) tok = RowCut<Fmt>(a.V).token(tok);
                     if (tok < 0 || tok >= a.V)
                         record = make_rec(kRecBadRow, 0);
                     else
@@ -978,14 +978,14 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
                                     g[e] = (c1[r][e] * scale) * (shift - c0v[j]);
                             }
                         }
-                        store_chunk<W>(gr, r, pack_grad<Fmt>(g));
+                        store_round<Fmt, W, CPT>(gr, r, pack_grad<Fmt>(g), last);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
             if (!distilled && cur.grow >= 0 && a.grad_out) {
 #pragma unroll
-                for (int r = 0; r < CPT; ++r) store_chunk<W>(gr, r, chunk_t{0u, 0u, 0u, 0u});
+                for (int r = 0; r < CPT; ++r) store_round<Fmt, W, CPT>(gr, r, chunk_t{0u, 0u, 0u, 0u}, last);
             }
             release_rows = a.erridx && spec && distilled;
         }
@@ -1113,7 +1113,6 @@ hipError_t launch_verify_distill(const FusedLaunch& L) {
     a.loss_out = L.loss_out;
     a.nitems = L.B * L.K + L.B;
     const int eb = L.dtype == 1 ? 2 : 4;
-    a.nchunks = int((int64_t(L.V) * eb) / 16);
     a.row_bytes = uint32_t(int64_t(L.V) * eb);
     a.seq_step = 1;
     return L.dtype == 1 ? launch_fmt<BF16>(L, a) : launch_fmt<F32>(L, a);

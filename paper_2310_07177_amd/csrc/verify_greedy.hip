@@ -34,8 +34,6 @@ struct SegArgs {
     const int32_t* tokens;     // [B, K]
     const int32_t* draft_len;  // [B] or null
     int nseg;                  // segments per row
-    int nchunks;               // 16-byte chunks per row
-    uint32_t row_bytes;
     int64_t first;             // first work unit of this launch
     SegStats* stats;           // [B*(K+1), kMaxSeg] argmax partials, zero between calls
     int32_t* accepted_len;
@@ -43,31 +41,13 @@ struct SegArgs {
     uint8_t* reject_mask;
 };
 
-// Load this thread's chunks of segment `s` of a row (zeros past the end of
-// the row: the caller pads them).  A null row issues loads of 0 bytes.
-template <int CPT>
-__device__ inline void load_segment(chunk_t (&x)[CPT], const char* row, const SegArgs& a, int s) {
-    const uint32_t off = uint32_t(s) * uint32_t(kW * CPT * 16);
-    const rsrc_t r = make_rsrc(row ? row + off : static_cast<const char*>(a.target), row ? a.row_bytes - off : 0u);
-#pragma unroll
-    for (int n = 0; n < CPT; ++n) x[n] = load_chunk<kW>(r, n);
-}
-
-// Chunks past the end of the row become -inf (zero probability).
-template <typename Fmt, int CPT>
-__device__ inline void pad_segment(chunk_t (&x)[CPT], const SegArgs& a, int s) {
-#pragma unroll
-    for (int n = 0; n < CPT; ++n)
-        if (s * kW * CPT + n * kW + int(threadIdx.x) >= a.nchunks) x[n] = pad_chunk<Fmt>();
-}
-
 __device__ inline int seq_k(const SegArgs& a, int b) { return a.draft_len ? scalar_load(a.draft_len + b) : a.K; }
 
 // Every argument word, requested together on entry: each dependent request
 // would cost a round trip to the argument buffer (about a microsecond).
 __device__ inline void request_args(const SegArgs& a) {
     asm volatile("" ::"s"(a.target), "s"(a.B), "s"(a.K), "s"(a.V), "s"(a.tokens), "s"(a.draft_len), "s"(a.nseg),
-                 "s"(a.nchunks), "s"(a.row_bytes), "s"(a.first), "s"(a.stats));
+                 "s"(a.first), "s"(a.stats));
     asm volatile("" ::"s"(a.accepted_len), "s"(a.out_tokens), "s"(a.reject_mask));
 }
 
@@ -88,9 +68,13 @@ __global__ __launch_bounds__(kW) void verify_greedy_stats(SegArgs a) {
     if (kb < 1 || kb > a.K || i > kb) return;  // invalid k_b (reported later) or a padding row
 
     const char* trow = static_cast<const char*>(a.target) + pair * int64_t(a.V) * Fmt::kBytes;
+    // Segment s holds rounds s*CPT .. s*CPT + CPT - 1 of the row.
+    const RowCut<Fmt> cut(a.V);
     chunk_t xt[CPT];
-    load_segment<CPT>(xt, trow, a, s);
-    pad_segment<Fmt, CPT>(xt, a, s);
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) xt[n] = load_off(trow, cut.off((s * CPT + n) * kW + tid));
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) xt[n] = chunk_or_pad<Fmt, kW>(xt[n], s * CPT + n, cut);
     const int c0 = s * kW * CPT + tid;  // this thread's first chunk in the row
     // Within a thread indices grow with (n, e): a strict ">" keeps the first
     // maximum.
@@ -125,7 +109,7 @@ __global__ __launch_bounds__(kW) void verify_greedy_stats(SegArgs a) {
         r.st = 0.0;
         r.sd = 0.0;
         r.kt = bv;
-        r.kd = __int_as_float(bx);
+        r.kd = __int_as_float(bx == 0x7FFFFFFF ? bx : cut.token(bx));
         a.stats[pair * kMaxSeg + s] = r;
     }
 }
@@ -227,9 +211,10 @@ hipError_t launch_fmt(const VerifyLaunch& L, SegArgs a) {
 
 }  // namespace
 
-// Segments of a row for greedy verification: kW threads x 4 chunks each
-// (8192 bf16 or 4096 fp32 logits), at most kMaxSeg of them.
+// Segments of a row of at least one chunk for greedy verification: kW threads
+// x 4 chunks each (8192 bf16 or 4096 fp32 logits), at most kMaxSeg of them.
 bool greedy_segments(int V, int per_chunk, int* nseg) {
+    if (V < per_chunk) return false;
     const int64_t nchunks = (int64_t(V) + per_chunk - 1) / per_chunk;
     const int64_t n = (nchunks + int64_t(kW) * 4 - 1) / (int64_t(kW) * 4);
     if (n > kMaxSeg) return false;
@@ -245,9 +230,6 @@ hipError_t launch_verify_greedy(const VerifyLaunch& L) {
     a.V = L.V;
     a.tokens = L.tokens;
     a.draft_len = L.draft_len;
-    const int eb = L.dtype == 1 ? 2 : 4;
-    a.nchunks = int((int64_t(L.V) * eb) / 16);
-    a.row_bytes = uint32_t(int64_t(L.V) * eb);
     a.first = 0;
     a.stats = L.seg_stats;
     a.accepted_len = L.accepted_len;

@@ -105,13 +105,15 @@ __global__ __launch_bounds__(W, 4) void shard_stats_kernel(StatsArgs a) {
         }
     }
     const char* trow = static_cast<const char*>(a.target) + (int64_t(b) * (K + 1) + i) * int64_t(Vs) * Fmt::kBytes;
+    const RowCut<Fmt> cut(Vs);
     chunk_t tv[CPT];
-    load_row<Fmt, W, CPT, VEC>(tv, trow, Vs);
+    load_row<Fmt, W, CPT, VEC>(tv, trow, cut, Vs);
     osd_shard_row_stats* out = a.stats + int64_t(b) * (K + 1) + i;
 
     if constexpr (GREEDY) {
         // Slice argmax, lowest index on ties (indices grow with (n, e) in a
         // thread, so a strict ">" keeps the first maximum).
+        if constexpr (VEC) pad_row_tail<Fmt, W, CPT>(tv, cut);
         float best = kNegInf;
         int bi = 0x7FFFFFFF;
 #pragma unroll
@@ -141,7 +143,7 @@ __global__ __launch_bounds__(W, 4) void shard_stats_kernel(StatsArgs a) {
             osd_shard_row_stats r = {};
             r.k_target = bv;
             r.k_draft = kNegInf;
-            r.argmax = bv > kNegInf ? a.v_begin + g : -1;
+            r.argmax = bv > kNegInf ? a.v_begin + (VEC ? cut.token(g) : g) : -1;
             r.flags = flags;
             *out = r;
         }
@@ -149,11 +151,11 @@ __global__ __launch_bounds__(W, 4) void shard_stats_kernel(StatsArgs a) {
         const float c2 = a.c2;
         chunk_t dv[CPT];
         const char* drow = static_cast<const char*>(a.draft) + (int64_t(b) * K + i) * int64_t(Vs) * Fmt::kBytes;
-        if (!bonus) load_row<Fmt, W, CPT, VEC>(dv, drow, Vs);
+        if (!bonus) load_row<Fmt, W, CPT, VEC>(dv, drow, cut, Vs);
         float Kt = kNegInf, Kd = kNegInf;
         float st = 0.0f, sd = 0.0f;
-        row_stats<Fmt, CPT>(tv, c2, Kt, st);
-        if (!bonus) row_stats<Fmt, CPT>(dv, c2, Kd, sd);
+        row_stats<Fmt, W, CPT, VEC>(tv, cut, c2, Kt, st);
+        if (!bonus) row_stats<Fmt, W, CPT, VEC>(dv, cut, c2, Kd, sd);
         double dt = st, dd = sd;
         wave_merge_stats(Kt, dt);
         wave_merge_stats(Kd, dd);
@@ -341,9 +343,14 @@ __global__ __launch_bounds__(W, 4) void shard_mass_kernel(MassArgs a) {
         const bool p_only = d.acc == kb;
         const char* trow = static_cast<const char*>(a.target) + (int64_t(b) * (K + 1) + d.acc) * int64_t(Vs) * Fmt::kBytes;
         const char* drow = static_cast<const char*>(a.draft) + (int64_t(b) * K + d.acc) * int64_t(Vs) * Fmt::kBytes;
+        const RowCut<Fmt> cut(Vs);
         chunk_t tv[CPT], dv[CPT];
-        load_row<Fmt, W, CPT, VEC>(tv, trow, Vs);
-        if (!p_only) load_row<Fmt, W, CPT, VEC>(dv, drow, Vs);
+        load_row<Fmt, W, CPT, VEC>(tv, trow, cut, Vs);
+        if (!p_only) load_row<Fmt, W, CPT, VEC>(dv, drow, cut, Vs);
+        if constexpr (VEC) {
+            pad_row_tail<Fmt, W, CPT>(tv, cut);
+            if (!p_only) pad_row_tail<Fmt, W, CPT>(dv, cut);
+        }
         const SliceMass<Fmt> mass{a.c2, d.kt, d.kd, p_only ? 0.0f : float(d.st / d.sd), p_only};
         const SliceMass<Fmt> pmass{a.c2, d.kt, d.kd, 0.0f, true};
 #pragma unroll
@@ -474,10 +481,13 @@ __global__ __launch_bounds__(W, 4) void shard_draw_kernel(DrawArgs a) {
         const bool p_only = pl.p_only || acc == kb;
         const char* trow = static_cast<const char*>(a.target) + (int64_t(b) * (K + 1) + acc) * int64_t(Vs) * Fmt::kBytes;
         const char* drow = static_cast<const char*>(a.draft) + (int64_t(b) * K + acc) * int64_t(Vs) * Fmt::kBytes;
+        const RowCut<Fmt> cut(Vs);
         chunk_t tv[CPT], dv[CPT];
-        load_row<Fmt, W, CPT, VEC>(tv, trow, Vs);
+        load_row<Fmt, W, CPT, VEC>(tv, trow, cut, Vs);
+        if constexpr (VEC) pad_row_tail<Fmt, W, CPT>(tv, cut);
         if (!p_only) {
-            load_row<Fmt, W, CPT, VEC>(dv, drow, Vs);
+            load_row<Fmt, W, CPT, VEC>(dv, drow, cut, Vs);
+            if constexpr (VEC) pad_row_tail<Fmt, W, CPT>(dv, cut);
         } else {
 #pragma unroll
             for (int n = 0; n < CPT; ++n) dv[n] = pad_chunk<Fmt>();
@@ -487,7 +497,7 @@ __global__ __launch_bounds__(W, 4) void shard_draw_kernel(DrawArgs a) {
         bool z_zero = false;
         const int t = draw_inverse_cdf<kFixedShift, W, CPT, EPC>(tv, dv, mass, 0.0f, s_tot, &s_draw, s_stage,
                                                                  &z_zero, pl.c);
-        if (t >= 0) s_tok = a.v_begin + t;
+        if (t >= 0) s_tok = a.v_begin + (VEC ? cut.token(t) : t);
         __syncthreads();
     }
 
@@ -537,17 +547,18 @@ hipError_t launch_tile(const ShardLaunch& L) {
     return e;
 }
 
-template <typename Fmt, bool VEC>
+template <typename Fmt>
 hipError_t launch_fmt(const ShardLaunch& L) {
     RowTile t;
+    if (L.Vs < Fmt::kPerChunk) return launch_tile<Fmt, 256, 1, false>(L);
     if (!pick_tile(L.Vs, Fmt::kPerChunk, &t)) return hipErrorInvalidValue;
     switch (t.W * 100 + t.CPT) {
-        case 25601: return launch_tile<Fmt, 256, 1, VEC>(L);
-        case 25602: return launch_tile<Fmt, 256, 2, VEC>(L);
-        case 25604: return launch_tile<Fmt, 256, 4, VEC>(L);
-        case 51204: return launch_tile<Fmt, 512, 4, VEC>(L);
-        case 51208: return launch_tile<Fmt, 512, 8, VEC>(L);
-        case 102408: return launch_tile<Fmt, 1024, 8, VEC>(L);
+        case 25601: return launch_tile<Fmt, 256, 1, true>(L);
+        case 25602: return launch_tile<Fmt, 256, 2, true>(L);
+        case 25604: return launch_tile<Fmt, 256, 4, true>(L);
+        case 51204: return launch_tile<Fmt, 512, 4, true>(L);
+        case 51208: return launch_tile<Fmt, 512, 8, true>(L);
+        case 102408: return launch_tile<Fmt, 1024, 8, true>(L);
         default: return hipErrorInvalidValue;
     }
 }
@@ -555,8 +566,7 @@ hipError_t launch_fmt(const ShardLaunch& L) {
 }  // namespace
 
 hipError_t launch_verify_shard(const ShardLaunch& L) {
-    if (L.dtype == 1) return L.vec ? launch_fmt<BF16, true>(L) : launch_fmt<BF16, false>(L);
-    return L.vec ? launch_fmt<F32, true>(L) : launch_fmt<F32, false>(L);
+    return L.dtype == 1 ? launch_fmt<BF16>(L) : launch_fmt<F32>(L);
 }
 
 }  // namespace osd

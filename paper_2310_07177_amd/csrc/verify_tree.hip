@@ -28,8 +28,8 @@
 // outputs.  Nodes off the accepted path are computed too: the price of not
 // waiting for the path.
 //
-// Rows with 16-byte alignment at T > 0 take the streaming layout instead
-// (tree_stream_kernel, below): about one workgroup per CU walks its node
+// Rows of at least one 16-byte chunk take the streaming layout instead at
+// T > 0 (tree_stream_kernel, below): about one workgroup per CU walks its node
 // items while the next item's rows are in flight.
 #include "osd_device.hpp"
 #include "osd_internal.hpp"
@@ -67,7 +67,6 @@ struct TreeArgs {
     // streaming layout only
     int G;               // workgroups in the grid
     int nitems;          // B * N
-    int nchunks;         // 16-byte chunks per row
     uint32_t row_bytes;  // bytes per row
 };
 
@@ -185,29 +184,18 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void tree_node_kerne
     const char* trow = static_cast<const char*>(a.target) + (int64_t(b) * N + n) * int64_t(V) * Fmt::kBytes;
     const char* drow = (GREEDY || leaf) ? trow
                                         : static_cast<const char*>(a.draft) + (int64_t(b) * N + n) * int64_t(V) * Fmt::kBytes;
-    const int nchunks = (V + EPC - 1) / EPC;
+    const RowCut<Fmt> cut(V);
     chunk_t tv[CPT], dv[CPT];
     // A leaf (and greedy verification) reads the target row alone.
-    const bool pair = !GREEDY && !leaf;
-    if constexpr (VEC) {
-        if (pair) {
-            load_rows_interleaved<W, CPT>(tv, dv, trow, drow, nchunks);
-        } else {
-            load_row_clamped<W, CPT>(tv, trow, nchunks);
+    load_row<Fmt, W, CPT, VEC>(tv, trow, cut, V);
+    if (!GREEDY && !leaf)
+        load_row<Fmt, W, CPT, VEC>(dv, drow, cut, V);
+    else
 #pragma unroll
-            for (int r = 0; r < CPT; ++r) dv[r] = pad_chunk<Fmt>();
-        }
-    } else {
-        load_row<Fmt, W, CPT, VEC>(tv, trow, V);
-        if (pair)
-            load_row<Fmt, W, CPT, VEC>(dv, drow, V);
-        else
-#pragma unroll
-            for (int r = 0; r < CPT; ++r) dv[r] = pad_chunk<Fmt>();
-    }
+        for (int r = 0; r < CPT; ++r) dv[r] = pad_chunk<Fmt>();
 
     if constexpr (GREEDY) {
-        if constexpr (VEC) pad_row_tail<Fmt, W, CPT>(tv, nchunks);
+        if constexpr (VEC) pad_row_tail<Fmt, W, CPT>(tv, cut);
         (void)drow;
         float best = kNegInf;
         int bi = 0x7FFFFFFF;
@@ -235,6 +223,7 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void tree_node_kerne
                     bv = s_max[0][w];
                     g = s_idx[w];
                 }
+            if (VEC) g = cut.token(g);  // (unused where the row has no finite logit)
             uint32_t rec;
             if (!(bv > kNegInf) || bv == -kNegInf) {
                 rec = node_rec(kNodeBad, 0);
@@ -247,18 +236,13 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void tree_node_kerne
         }
         return;
     } else {
+        static_assert(!VEC, "rows of a chunk or more take the streaming layout");
         const float c2 = a.c2;
         float Kt = kNegInf, Kd = kNegInf;
         {
             float st = 0.0f, sd = 0.0f;
-            if constexpr (VEC) {
-                row_stats2_tail<Fmt, W, CPT>(tv, dv, nchunks, c2, !leaf, Kt, st, Kd, sd);
-                pad_row_tail<Fmt, W, CPT>(tv, nchunks);
-                pad_row_tail<Fmt, W, CPT>(dv, nchunks);
-            } else {
-                row_stats<Fmt, CPT>(tv, c2, Kt, st);
-                if (!leaf) row_stats<Fmt, CPT>(dv, c2, Kd, sd);
-            }
+            row_stats<Fmt, W, CPT, false>(tv, cut, c2, Kt, st);
+            if (!leaf) row_stats<Fmt, W, CPT, false>(dv, cut, c2, Kd, sd);
             double dt = st, dd = sd;
             wave_merge_stats(Kt, dt);
             wave_merge_stats(Kd, dd);
@@ -392,7 +376,7 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void tree_node_kerne
 }
 
 // ---------------------------------------------------------------------------
-// Streaming layout (16-byte rows, T > 0).  About one workgroup per CU walks
+// Streaming layout (rows of a chunk or more, T > 0).  About one workgroup per CU walks
 // the node items j = g, g + G, ... (item j is node j / B of sequence j % B,
 // so the roots come first).  While an item is computed the next item's rows
 // are in flight: each register chunk is reloaded with the same chunk of the
@@ -480,11 +464,11 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
     asm volatile("" ::"s"(a.target), "s"(a.draft), "s"(a.B), "s"(a.N), "s"(a.V), "s"(a.parent), "s"(a.node_tokens),
                  "s"(a.u_accept), "s"(a.u_resample), "s"(a.c2));
     asm volatile("" ::"s"(a.accepted_len), "s"(a.out_tokens), "s"(a.path_nodes), "s"(a.records), "s"(a.counters),
-                 "s"(a.G), "s"(a.nitems), "s"(a.nchunks), "s"(a.row_bytes));
+                 "s"(a.G), "s"(a.nitems), "s"(a.row_bytes));
     const int tid = threadIdx.x;
     const int g = blockIdx.x, G = a.G, B = a.B, N = a.N;
     const float c2 = a.c2;
-    const bool last_ok = (CPT - 1) * W + tid < a.nchunks;
+    const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
     const int nk = g < a.nitems ? (a.nitems - 1 - g) / G + 1 : 0;  // <= kMaxTreeItems (launch)
     const char* const tbase = static_cast<const char*>(a.target);
     const char* const dbase = static_cast<const char*>(a.draft);
@@ -501,8 +485,8 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
         const rsrc_t dr = make_rsrc(on ? dbase + row * a.row_bytes : tbase, on ? a.row_bytes : 0u);
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
-            rt[r] = load_chunk<W>(tr, r);
-            rs[r] = load_chunk<W>(dr, r);
+            rt[r] = load_round<W, CPT>(tr, r, last);
+            rs[r] = load_round<W, CPT>(dr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -561,16 +545,16 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
         float kc_t = 0.0f, kc_s = 0.0f;
         double S_t = 0.0, S_s = 0.0;
         if (live) {
-            kc_t = shift_of_max(chunks_max<Fmt, CPT>(rt, !last_ok), c2);
-            if (!leaf) kc_s = shift_of_max(chunks_max<Fmt, CPT>(rs, !last_ok), c2);
+            kc_t = shift_of_max(chunks_max<Fmt, CPT>(rt, last), c2);
+            if (!leaf) kc_s = shift_of_max(chunks_max<Fmt, CPT>(rs, last), c2);
         }
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
             if (live) {
                 chunk_t xt = rt[r], xs = rs[r];
-                if (r == CPT - 1 && !last_ok) {
-                    xt = pad_chunk<Fmt>();
-                    xs = pad_chunk<Fmt>();
+                if (r == CPT - 1 && last.ragged) {
+                    xt = pad_lead<Fmt>(xt, last.lead);
+                    xs = pad_lead<Fmt>(xs, last.lead);
                 }
                 float st = 0.0f, ss = 0.0f;
 #pragma unroll
@@ -592,8 +576,8 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
                 S_t = r == 0 ? double(st) : S_t + double(st);
                 S_s = r == 0 ? double(ss) : S_s + double(ss);
             }
-            rt[r] = load_chunk<W>(ntr, r);
-            rs[r] = load_chunk<W>(nsr, r);
+            rt[r] = load_round<W, CPT>(ntr, r, last);
+            rs[r] = load_round<W, CPT>(nsr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (opaque_tid() < kWave) {
@@ -628,8 +612,9 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
                     const int y = __builtin_amdgcn_readfirstlane(s_ktok[par][c]);
                     {
                         // The holder of y posts R(y) and Q(y).
-                        const int ch = y / EPC, ey = y - ch * EPC, rr = ch / W, th = ch - rr * W;
+                        const int ch = y / EPC, rr = ch / W, th = ch - rr * W;
                         if (opaque_tid() == th) {
+                            const int ey = y - (rr == CPT - 1 ? last.off / Fmt::kBytes : ch * EPC);
                             float ev = 0.0f;
 #pragma unroll
                             for (int r = 0; r < CPT; ++r)
@@ -710,6 +695,7 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
                         m = at;
                         tok = draw_cached<W, CPT, EPC, false>(mass, mass_at, ures, s_cell, &s_dz, &s_tok);
                     }
+                    if (tok >= 0) tok = RowCut<Fmt>(a.V).token(tok);
                     rec = (tok >= 0 && tok < a.V) ? node_rec(kNodeDraw, uint32_t(tok)) : node_rec(kNodeBad, 0);
                 }
             }
@@ -747,47 +733,37 @@ hipError_t launch_stream(const TreeLaunch& L, TreeArgs a) {
     return launch_kernel(&tree_stream_kernel<Fmt, W, CPT>, dim3(unsigned(grid)), dim3(W), 0, L.stream, a);
 }
 
-template <typename Fmt, int W, int CPT>
-hipError_t launch_tile(const TreeLaunch& L, const TreeArgs& a) {
+template <typename Fmt, int W, int CPT, bool VEC, bool GREEDY>
+hipError_t launch_node(const TreeLaunch& L, const TreeArgs& a) {
     const dim3 grid(unsigned(L.B) * unsigned(L.N)), block(W);
-    const bool greedy = L.temperature == 0.0f;
-    hipError_t e;
-    if (L.vec) {
-        if (greedy)
-            e = launch_kernel(&tree_node_kernel<Fmt, W, CPT, true, true>, grid, block, 0, L.stream, a);
-        else
-            e = launch_kernel(&tree_node_kernel<Fmt, W, CPT, true, false>, grid, block, 0, L.stream, a);
-    } else {
-        if (greedy)
-            e = launch_kernel(&tree_node_kernel<Fmt, W, CPT, false, true>, grid, block, 0, L.stream, a);
-        else
-            e = launch_kernel(&tree_node_kernel<Fmt, W, CPT, false, false>, grid, block, 0, L.stream, a);
-    }
-    return e;
+    return launch_kernel(&tree_node_kernel<Fmt, W, CPT, VEC, GREEDY>, grid, block, 0, L.stream, a);
 }
 
 template <typename Fmt>
 hipError_t launch_fmt(const TreeLaunch& L, const TreeArgs& a) {
-    RowTile s;
-    if (L.vec && L.temperature > 0.0f && pick_stream_tile(L.V, Fmt::kPerChunk, &s)) {
-        switch (s.W * 100 + s.CPT) {
+    if (L.V < Fmt::kPerChunk)  // rows shorter than one chunk, element by element
+        return L.temperature == 0.0f ? launch_node<Fmt, 256, 1, false, true>(L, a)
+                                     : launch_node<Fmt, 256, 1, false, false>(L, a);
+    RowTile t;
+    if (L.temperature > 0.0f) {
+        if (!pick_stream_tile(L.V, Fmt::kPerChunk, &t)) return hipErrorInvalidValue;
+        switch (t.W * 100 + t.CPT) {
             case 25601: return launch_stream<Fmt, 256, 1>(L, a);
             case 51201: return launch_stream<Fmt, 512, 1>(L, a);
             case 102401: return launch_stream<Fmt, 1024, 1>(L, a);
             case 102402: return launch_stream<Fmt, 1024, 2>(L, a);
             case 102403: return launch_stream<Fmt, 1024, 3>(L, a);
             case 102404: return launch_stream<Fmt, 1024, 4>(L, a);
-            default: break;
+            default: return hipErrorInvalidValue;
         }
     }
-    RowTile t;
     if (!pick_tree_tile(L.V, Fmt::kPerChunk, &t)) return hipErrorInvalidValue;
     switch (t.W * 100 + t.CPT) {
-        case 25601: return launch_tile<Fmt, 256, 1>(L, a);
-        case 25602: return launch_tile<Fmt, 256, 2>(L, a);
-        case 51202: return launch_tile<Fmt, 512, 2>(L, a);
-        case 102402: return launch_tile<Fmt, 1024, 2>(L, a);
-        case 102404: return launch_tile<Fmt, 1024, 4>(L, a);
+        case 25601: return launch_node<Fmt, 256, 1, true, true>(L, a);
+        case 25602: return launch_node<Fmt, 256, 2, true, true>(L, a);
+        case 51202: return launch_node<Fmt, 512, 2, true, true>(L, a);
+        case 102402: return launch_node<Fmt, 1024, 2, true, true>(L, a);
+        case 102404: return launch_node<Fmt, 1024, 4, true, true>(L, a);
         default: return hipErrorInvalidValue;
     }
 }
@@ -827,7 +803,6 @@ hipError_t launch_verify_tree(const TreeLaunch& L) {
     a.nitems = L.B * L.N;
     const int eb = L.dtype == 1 ? 2 : 4;
     a.row_bytes = uint32_t(int64_t(L.V) * eb);
-    a.nchunks = int(a.row_bytes / 16u);
     return L.dtype == 1 ? launch_fmt<BF16>(L, a) : launch_fmt<F32>(L, a);
 }
 
