@@ -13,13 +13,13 @@
 
 namespace osd {
 
-// x 2^SH as a whole number held in fp64: for masses of at most 1 per element
-// (chunk sums at most 8) and SH <= 44, every chunk value is below 2^47 and
-// every wave sum at most 2^53, so each is exact -- and equal to
-// mass_to_fixed<SH>(x), which takes more instructions.
+// x 2^SH as a whole number held in fp64, equal to the fixed-point value (an
+// integer conversion takes more instructions).  Exact while every wave sum stays
+// below 2^53: SH = 44 for masses of at most 1 per element (chunk sums at most
+// 8, wave sums at most 2^53), SH = 52 for probabilities (a row's total 1).
 template <int SH>
 __device__ inline double fixed_f64(float x) {
-    static_assert(SH <= 44, "exact below 2^53 only for SH <= 44");
+    static_assert(SH <= 52, "a row's total must stay below 2^53");
     return floor(double(x) * double(1ull << SH));
 }
 
@@ -38,45 +38,64 @@ template <int SH, int W, int EPC>
 __device__ inline int walk_chunk(const float (&m)[EPC], float s, uint64_t target, int nstar) {
     const int tid = threadIdx.x;
     int pick = -1, last_pos = -1;
-    if constexpr (SH <= 44) {
-        // Offsets inside one cell stay below 2^53: exact in fp64.
-        const double v = fixed_f64<SH>(s);
-        const double incl = wave_scan_add(v);
-        const double lo = incl - v, t = double(target);
-        if (!(v > 0.0 && lo <= t && t < incl)) return -1;
-        const double want = t - lo;
-        float run = 0.0f;
+    const double v = fixed_f64<SH>(s);
+    const double incl = wave_scan_add(v);
+    const double lo = incl - v, t = double(target);
+    if (!(v > 0.0 && lo <= t && t < incl)) return -1;
+    const double want = t - lo;
+    float run = 0.0f;
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            run = run + m[e];
-            if (m[e] > 0.0f) last_pos = e;
-            if (pick < 0 && fixed_f64<SH>(run) > want) pick = e;
-        }
-    } else {
-        const uint64_t v = mass_to_fixed<SH>(s);
-        const uint64_t incl = wave_inclusive_scan(v);
-        const uint64_t lo = incl - v;
-        if (!(v > 0 && lo <= target && target < incl)) return -1;
-        const uint64_t want = target - lo;
-        float run = 0.0f;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            run = run + m[e];
-            if (m[e] > 0.0f) last_pos = e;
-            if (pick < 0 && mass_to_fixed<SH>(run) > want) pick = e;
-        }
+    for (int e = 0; e < EPC; ++e) {
+        run = run + m[e];
+        if (m[e] > 0.0f) last_pos = e;
+        if (pick < 0 && fixed_f64<SH>(run) > want) pick = e;
     }
     if (pick < 0) pick = last_pos >= 0 ? last_pos : 0;
     return (nstar * W + tid) * EPC + pick;
+}
+
+// The cell that holds the point, from the totals of all cells (round n, wave w;
+// n*NW + w < cells) in s_tot: s_draw receives its round (-1 if there is no mass),
+// its wave and the point's offset inside it.  The point is floor(u * Z), or
+// c_given when >= 0 (a point already chosen in a larger CDF of which this row is
+// one part); either is clamped to Z - 1.  All threads call it; it opens and ends
+// with a barrier.
+template <int NW>
+__device__ inline void locate_cell(int cells, const unsigned long long* s_tot, float u, long long c_given,
+                                   DrawShared* s_draw) {
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    __syncthreads();
+    if (wid == 0) {
+        uint64_t z = 0;
+        for (int c0 = lane; c0 < cells; c0 += kWave) z += s_tot[c0];
+        z = wave_sum(z);
+        if (lane == 0) s_draw->cell_round = -1;
+        if (z > 0) {
+            uint64_t c = c_given >= 0 ? static_cast<uint64_t>(c_given) : static_cast<uint64_t>(double(u) * double(z));
+            if (c >= z) c = z - 1;
+            uint64_t carry = 0;
+            for (int base = 0; base < cells; base += kWave) {
+                const int idx = base + lane;
+                const uint64_t v = idx < cells ? uint64_t(s_tot[idx]) : 0;
+                const uint64_t incl = wave_inclusive_scan(v) + carry;
+                const uint64_t lo = incl - v;
+                if (v > 0 && lo <= c && c < incl) {
+                    s_draw->cell_round = idx / NW;
+                    s_draw->cell_wave = idx % NW;
+                    s_draw->target = c - lo;
+                }
+                carry = static_cast<uint64_t>(__shfl(static_cast<unsigned long long>(incl), kWave - 1, kWave));
+            }
+        }
+    }
+    __syncthreads();
 }
 
 // Inverse-CDF draw over a register-resident row pair.  mass(t, d, e) returns
 // the non-negative fp32 mass of element e of the chunks t, d (0 for padding).
 // Returns the drawn element's place (chunk * EPC + e) on exactly one thread and
 // -1 on every other thread; *z_zero is set (uniformly) when the total mass is zero.  The point drawn is
-// floor(u * Z) in fixed point, or, when c_given >= 0, c_given itself (a point
-// already chosen in a larger CDF of which this row is one part); either is
-// clamped to Z - 1.
+// locate_cell's.
 //
 // Token order is (round n, wave w, lane, element e).  Chunk masses are summed
 // left to right in fp32 and converted exactly to fixed point, so every partial
@@ -97,40 +116,11 @@ __device__ int draw_inverse_cdf(const chunk_t (&tv)[CPT], const chunk_t (&dv)[CP
         float s = 0.0f;
 #pragma unroll
         for (int e = 0; e < EPC; ++e) s = s + mass(tv[n], dv[n], e);
-        uint64_t t;
-        if constexpr (SH <= 44)
-            t = uint64_t(wave_sum(fixed_f64<SH>(s)));
-        else
-            t = wave_sum(mass_to_fixed<SH>(s));
-        if (lane == 0) s_tot[n * NW + wid] = t;
+        const double t = wave_sum(fixed_f64<SH>(s));
+        if (lane == 0) s_tot[n * NW + wid] = uint64_t(t);
         __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
-    if (wid == 0) {
-        uint64_t z = 0;
-        for (int c0 = lane; c0 < CELLS; c0 += kWave) z += s_tot[c0];
-        z = wave_sum(z);
-        if (lane == 0) s_draw->cell_round = -1;
-        if (z > 0) {
-            uint64_t c = c_given >= 0 ? static_cast<uint64_t>(c_given)
-                                      : static_cast<uint64_t>(double(u) * double(z));
-            if (c >= z) c = z - 1;
-            uint64_t carry = 0;
-            for (int base = 0; base < CELLS; base += kWave) {
-                const int idx = base + lane;
-                const uint64_t v = idx < CELLS ? uint64_t(s_tot[idx]) : 0;
-                const uint64_t incl = wave_inclusive_scan(v) + carry;
-                const uint64_t lo = incl - v;
-                if (v > 0 && lo <= c && c < incl) {
-                    s_draw->cell_round = idx / NW;
-                    s_draw->cell_wave = idx % NW;
-                    s_draw->target = c - lo;
-                }
-                carry = static_cast<uint64_t>(__shfl(static_cast<unsigned long long>(incl), kWave - 1, kWave));
-            }
-        }
-    }
-    __syncthreads();
+    locate_cell<NW>(CELLS, s_tot, u, c_given, s_draw);
     const int nstar = s_draw->cell_round;
     *z_zero = nstar < 0;
     if (nstar < 0 || wid != s_draw->cell_wave) return -1;
@@ -166,6 +156,33 @@ namespace osd {
 // logits per row).
 constexpr int kMaxStreamRounds = 16;
 
+// Inverse-CDF draw over a row whose chunk masses are already known: chunk[n] is
+// the mass of this thread's chunk of round n (the left-to-right fp32 sum of its
+// elements' masses up to rounding), element(n, m) fills m with the masses of the
+// elements of the chunk of round n (a run-time, uniform n; called by one wave).
+// Cells and result as draw_inverse_cdf.
+template <int SH, int W, int CPT, int EPC, typename ElementFn>
+__device__ int draw_from_sums(const float (&chunk)[CPT], ElementFn element, float u, unsigned long long* s_tot,
+                              DrawShared* s_draw) {
+    constexpr int NW = W / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) {
+        const double t = wave_sum(fixed_f64<SH>(chunk[n]));
+        if (lane == 0) s_tot[n * NW + wid] = uint64_t(t);
+    }
+    locate_cell<NW>(CPT * NW, s_tot, u, -1, s_draw);
+    const int nstar = s_draw->cell_round;
+    if (nstar < 0 || wid != s_draw->cell_wave) return -1;
+    float s = 0.0f;
+#pragma unroll
+    for (int n = 0; n < CPT; ++n)
+        if (n == nstar) s = chunk[n];
+    float m[EPC];
+    element(nstar, m);
+    return walk_chunk<SH, W, EPC>(m, s, s_draw->target, nstar);
+}
+
 // Inverse-CDF draw over a row that is streamed from memory instead of held in
 // registers.  masses(r, m) fills m[0..EPC) with the non-negative fp32 masses
 // of this thread's chunk in round r (0 for padding); it is called once per
@@ -181,45 +198,16 @@ __device__ int draw_inverse_cdf_streamed(int R, MassFn masses, float u, unsigned
                                          DrawShared* s_draw, bool* z_zero) {
     constexpr int NW = W / kWave;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
-    const int cells = R * NW;
     for (int r = 0; r < R; ++r) {
         float m[EPC];
         masses(r, m);
         float s = 0.0f;
 #pragma unroll
         for (int e = 0; e < EPC; ++e) s = s + m[e];
-        uint64_t t;
-        if constexpr (SH <= 44)
-            t = uint64_t(wave_sum(fixed_f64<SH>(s)));
-        else
-            t = wave_sum(mass_to_fixed<SH>(s));
-        if (lane == 0) s_tot[r * NW + wid] = t;
+        const double t = wave_sum(fixed_f64<SH>(s));
+        if (lane == 0) s_tot[r * NW + wid] = uint64_t(t);
     }
-    __syncthreads();
-    if (wid == 0) {
-        uint64_t z = 0;
-        for (int c0 = lane; c0 < cells; c0 += kWave) z += s_tot[c0];
-        z = wave_sum(z);
-        if (lane == 0) s_draw->cell_round = -1;
-        if (z > 0) {
-            uint64_t c = static_cast<uint64_t>(double(u) * double(z));
-            if (c >= z) c = z - 1;
-            uint64_t carry = 0;
-            for (int base = 0; base < cells; base += kWave) {
-                const int idx = base + lane;
-                const uint64_t v = idx < cells ? uint64_t(s_tot[idx]) : 0;
-                const uint64_t incl = wave_inclusive_scan(v) + carry;
-                const uint64_t lo = incl - v;
-                if (v > 0 && lo <= c && c < incl) {
-                    s_draw->cell_round = idx / NW;
-                    s_draw->cell_wave = idx % NW;
-                    s_draw->target = c - lo;
-                }
-                carry = static_cast<uint64_t>(__shfl(static_cast<unsigned long long>(incl), kWave - 1, kWave));
-            }
-        }
-    }
-    __syncthreads();
+    locate_cell<NW>(R * NW, s_tot, u, -1, s_draw);
     const int nstar = s_draw->cell_round;
     *z_zero = nstar < 0;
     if (nstar < 0 || wid != s_draw->cell_wave) return -1;

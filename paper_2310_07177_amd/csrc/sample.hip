@@ -4,14 +4,19 @@
 // data, at temperature T (T = 0: argmax).
 //
 // Work layout: one workgroup per sampled row n, the row (or the row pair of a
-// mixture) read once from HBM into registers with the tile of the
-// verification kernel; the softmax statistics (K, S) are folded in chunk by
-// chunk and merged over lanes and waves; the token is drawn with the exact
-// fixed-point inverse CDF of row_draw.hpp.  Masses:
+// mixture) read once from HBM into registers; the softmax statistics (K, S) are
+// folded in chunk by chunk and merged over lanes and waves; the token is drawn
+// with the exact fixed-point inverse CDF of row_draw.hpp.  Masses:
 //   one row:  2^(x c2 - K), in units of S (the verification's bonus draw);
 //   mixture:  beta 2^(t c2 - K_p)/S_p + (1 - beta) 2^(d c2 - K_q)/S_q, in
-//             probability units (each element is at most 1, every partial
-//             sum at most 1 + rounding, so 2^-60 fixed point cannot overflow).
+//             probability units (the row's total is 1).
+// Both are linear in the exponentials, so the draw takes a chunk's mass from
+// the sums that the statistics pass kept, and only the winning chunk's elements
+// are evaluated again (instruction issue bounded the kernels while every
+// element's exponentials were taken twice).  Where the rows fill the chip they
+// are streamed (sample_stream_kernel); few rows keep their chunks in registers
+// (sample_kernel: 300 pairs of V = 32000 bf16 23.9 -> 18.0 us) or are split
+// over workgroups (sample_split_kernel).
 #include <stdlib.h>
 
 #include "osd.h"
@@ -24,7 +29,7 @@ namespace osd {
 namespace {
 
 constexpr int kShiftOne = 44;  // units of S: elements <= 1, row total <= V
-constexpr int kShiftMix = 60;  // probability units: total 1
+constexpr int kShiftMix = 52;  // probability units: total 1
 
 enum : int { kModeGreedy = 0, kModeOne = 1, kModeMix = 2 };
 
@@ -40,18 +45,64 @@ struct SampleArgs {
     int32_t* out;         // [N]
 };
 
+// One chunk's sum of exponentials and the shift it is relative to.
+struct ChunkSum {
+    float s, k;
+};
+
+// fold_chunk in fp32 that also yields the chunk's own sum, taken left to right.
+template <typename Fmt>
+__device__ inline ChunkSum fold_chunk_sum(const chunk_t& x, float c2, float& K, float& S) {
+    const float kn = fmaxf(K, ceilf(chunk_max<Fmt>(x) * c2));
+    S = rescale(S, K, kn);
+    K = kn;
+    const float kx = fmaxf(K, -3.0e38f);  // see fold_chunk
+    float s = exp2_fast(__builtin_fmaf(Fmt::get(x, 0), c2, -kx));
+#pragma unroll
+    for (int e = 1; e < Fmt::kPerChunk; ++e) s = s + exp2_fast(__builtin_fmaf(Fmt::get(x, e), c2, -kx));
+    S = S + s;
+    return ChunkSum{s, kx};
+}
+
+// The masses of a row (pair) in the terms of the file's header, from the merged
+// statistics: a chunk's from its sums, an element's from its logits.
+template <bool MIX>
+struct SampleMass {
+    float c2, Kp, Kq, wp, wq;
+    __device__ SampleMass(float c2_, float beta, float Kp_, double Sp, float Kq_, double Sq)
+        : c2(c2_), Kp(Kp_), Kq(Kq_), wp(MIX ? float(double(beta) / Sp) : 1.0f),
+          wq(MIX ? float((1.0 - double(beta)) / Sq) : 0.0f) {}
+    __device__ float chunk(const ChunkSum& p, const ChunkSum& q) const {
+        if constexpr (!MIX) return rescale(p.s, p.k, Kp);
+        return __builtin_fmaf(rescale(wp, p.k, Kp), p.s, rescale(wq, q.k, Kq) * q.s);
+    }
+    template <typename Fmt>
+    __device__ void elements(const chunk_t& t, const chunk_t& d, float kp, float kq, float (&m)[Fmt::kPerChunk]) const {
+        const float sp = rescale(wp, kp, Kp), sq = MIX ? rescale(wq, kq, Kq) : 0.0f;
+#pragma unroll
+        for (int e = 0; e < Fmt::kPerChunk; ++e) {
+            const float et = exp2_fast(__builtin_fmaf(Fmt::get(t, e), c2, -kp));
+            if constexpr (!MIX) {
+                m[e] = et * sp;
+            } else {
+                const float ed = exp2_fast(__builtin_fmaf(Fmt::get(d, e), c2, -kq));
+                m[e] = __builtin_fmaf(sp, et, sq * ed);
+            }
+        }
+    }
+};
+
 template <typename Fmt, int W, int CPT, bool VEC, int MODE>
 __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(SampleArgs a) {
     constexpr int NW = W / kWave;
     constexpr int EPC = Fmt::kPerChunk;
     constexpr bool MIX = MODE == kModeMix;
-    __shared__ float s_max[2][NW];
-    __shared__ double s_sum[2][NW];
+    __shared__ float s_max[2 * NW];
+    __shared__ double s_sum[2 * NW];
     __shared__ int s_idx[NW];
     __shared__ int s_tok;
     __shared__ unsigned long long s_tot[CPT * NW];
     __shared__ DrawShared s_draw;
-    __shared__ chunk_t s_stage[MODE == kModeGreedy ? 1 : 2 * CPT * kWave];
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int n = blockIdx.x;
@@ -85,16 +136,16 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(S
             }
         wave_argmax(best, bi);
         if (lane == 0) {
-            s_max[0][wid] = best;
+            s_max[wid] = best;
             s_idx[wid] = bi;
         }
         __syncthreads();
         if (tid == 0) {
-            float bv = s_max[0][0];
+            float bv = s_max[0];
             int g = s_idx[0];
             for (int w = 1; w < NW; ++w)
-                if (s_max[0][w] > bv || (s_max[0][w] == bv && s_idx[w] < g)) {
-                    bv = s_max[0][w];
+                if (s_max[w] > bv || (s_max[w] == bv && s_idx[w] < g)) {
+                    bv = s_max[w];
                     g = s_idx[w];
                 }
             a.out[n] = (bv > kNegInf && bv < -kNegInf) ? (VEC ? cut.token(g) : g) : -1;
@@ -102,65 +153,38 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(S
         return;
     } else {
         const float c2 = a.c2;
-        float Kp = kNegInf, Kq = kNegInf;
-        {
-            float sp = 0.0f, sq = 0.0f;
-            if constexpr (VEC && MIX) {
-                row_stats2<Fmt, W, CPT>(tv, dv, cut, c2, true, Kp, sp, Kq, sq);
-            } else {
-                row_stats<Fmt, W, CPT, VEC>(tv, cut, c2, Kp, sp);
-                if constexpr (MIX) row_stats<Fmt, W, CPT, VEC>(dv, cut, c2, Kq, sq);
-            }
-            double dp = sp, dq = sq;
-            wave_merge_stats(Kp, dp);
-            if constexpr (MIX) wave_merge_stats(Kq, dq);
-            if (lane == 0) {
-                s_max[0][wid] = Kp;
-                s_max[1][wid] = Kq;
-                s_sum[0][wid] = dp;
-                s_sum[1][wid] = dq;
-            }
-        }
-        if (tid == 0) s_tok = -1;
-        __syncthreads();
-        Kp = s_max[0][0];
-        Kq = s_max[1][0];
+        const float u = a.u[n];
+        ChunkSum cp[CPT], cq[MIX ? CPT : 1];
+        float Kp = kNegInf, Kq = kNegInf, fp = 0.0f, fq = 0.0f;
 #pragma unroll
-        for (int w = 1; w < NW; ++w) {
-            Kp = fmaxf(Kp, s_max[0][w]);
-            Kq = fmaxf(Kq, s_max[1][w]);
+        for (int r = 0; r < CPT; ++r) {
+            if constexpr (VEC) tv[r] = chunk_or_pad<Fmt, W>(tv[r], r, cut);
+            cp[r] = fold_chunk_sum<Fmt>(tv[r], c2, Kp, fp);
+            if constexpr (MIX) {
+                if constexpr (VEC) dv[r] = chunk_or_pad<Fmt, W>(dv[r], r, cut);
+                cq[r] = fold_chunk_sum<Fmt>(dv[r], c2, Kq, fq);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // one chunk pair in flight: bounded VGPRs
         }
-        double Sp = 0.0, Sq = 0.0;
-        for (int w = 0; w < NW; ++w) {
-            Sp += rescale(s_sum[0][w], s_max[0][w], Kp);
-            if constexpr (MIX) Sq += rescale(s_sum[1][w], s_max[1][w], Kq);
-        }
+        double Sp = fp, Sq = fq;
+        if (tid == 0) s_tok = -1;
+        block_merge2<NW>(Kp, Sp, Kq, Sq, s_max, s_sum);
         const bool bad = !(Kp > kNegInf && Kp < -kNegInf) || !usable_sum(Sp) ||
                          (MIX && (!(Kq > kNegInf && Kq < -kNegInf) || !usable_sum(Sq)));
         if (bad) {
             if (tid == 0) a.out[n] = -1;
             return;
         }
-        // Opaque copies of the shifts and rows: the compiler must not keep
-        // the statistics pass's exponentials alive for the draw.
-        float kp = Kp, kq = Kq;
-        asm volatile("" : "+v"(kp), "+v"(kq));
-        opaque(tv);
-        if constexpr (MIX) opaque(dv);
-        const float wp = MIX ? float(double(a.beta) / Sp) : 1.0f;
-        const float wq = MIX ? float((1.0 - double(a.beta)) / Sq) : 0.0f;
-        auto mass = [=](const chunk_t& tc, const chunk_t& dc, int e) -> float {
-            const float et = exp2_fast(__builtin_fmaf(Fmt::get(tc, e), c2, -kp));
-            if constexpr (!MIX) {
-                return et;
-            } else {
-                const float ed = exp2_fast(__builtin_fmaf(Fmt::get(dc, e), c2, -kq));
-                return __builtin_fmaf(wp, et, wq * ed);
-            }
+        const SampleMass<MIX> mass(c2, a.beta, Kp, Sp, Kq, Sq);
+        float cm[CPT];
+#pragma unroll
+        for (int r = 0; r < CPT; ++r) cm[r] = mass.chunk(cp[r], cq[MIX ? r : 0]);
+        const auto element = [&](int nstar, float (&m)[EPC]) {
+#pragma unroll
+            for (int r = 0; r < CPT; ++r)
+                if (r == nstar) mass.template elements<Fmt>(tv[r], MIX ? dv[r] : tv[r], cp[r].k, cq[MIX ? r : 0].k, m);
         };
-        bool z_zero = false;
-        const int at = draw_inverse_cdf<MIX ? kShiftMix : kShiftOne, W, CPT, EPC>(
-            tv, dv, mass, a.u[n], s_tot, &s_draw, s_stage, &z_zero);
+        const int at = draw_from_sums<MIX ? kShiftMix : kShiftOne, W, CPT, EPC>(cm, element, u, s_tot, &s_draw);
         if (at >= 0) s_tok = VEC ? cut.token(at) : at;
         __syncthreads();
         if (tid == 0) a.out[n] = s_tok;  // -1 when no element carries mass
@@ -172,89 +196,81 @@ hipError_t launch_mode(const SampleLaunch& L, const SampleArgs& a) {
     return launch_kernel(&sample_kernel<Fmt, W, CPT, VEC, MODE>, dim3(unsigned(L.N)), dim3(W), 0, L.stream, a);
 }
 
-// A mixture of rows too long to hold as a pair (beyond 8 chunks per thread of
-// 1024 threads): the statistics and the draw of sample_kernel with both rows
-// streamed from memory, one 1024-thread workgroup per row pair.
-constexpr int kLongW = 1024;
-constexpr int kLongUnroll = 4;
+// sample_kernel with the rows streamed, U rounds of loads at a time: only the
+// chunk sums are held (59 VGPRs at 8 chunks per thread of a pair instead of 102,
+// so twice the waves hide the loads), and the winning wave reads its chunk
+// again.  Mixtures of 4096 row pairs of V = 32000 bf16: 131 -> 90 us (5.8 TB/s;
+// 32000 fp32 254 -> 160, 6.6 TB/s), of 2048 pairs of V = 128256: 346 -> 215 (the
+// rows were read twice before).  Four rounds at a time beat two by up to 6 %.
+constexpr int kStreamUnroll = 4;
 
-template <typename Fmt>
-__global__ __launch_bounds__(kLongW, 1) void sample_mix_long_kernel(SampleArgs a) {
-    constexpr int W = kLongW, NW = W / kWave, EPC = Fmt::kPerChunk, U = kLongUnroll;
-    __shared__ float s_max[2][NW];
-    __shared__ double s_sum[2][NW];
+template <typename Fmt, int W, int CPT, int U, bool MIX>
+__global__ __launch_bounds__(W, 1) void sample_stream_kernel(SampleArgs a) {
+    constexpr int NW = W / kWave, EPC = Fmt::kPerChunk;
+    __shared__ float s_max[2 * NW];
+    __shared__ double s_sum[2 * NW];
     __shared__ int s_tok;
-    __shared__ unsigned long long s_tot[kMaxStreamRounds * NW];
+    __shared__ unsigned long long s_tot[CPT * NW];
     __shared__ DrawShared s_draw;
 
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const int tid = threadIdx.x;
     const int n = blockIdx.x;
-    const int V = a.V;
     const char* prow = a.p + int64_t(n) * a.p_stride;
-    const char* qrow = a.q + int64_t(n) * a.q_stride;
-    const RowCut<Fmt> cut(V);
+    const char* qrow = MIX ? a.q + int64_t(n) * a.q_stride : prow;
+    const RowCut<Fmt> cut(a.V);
     const int R = (cut.nchunks + W - 1) / W;
     const float c2 = a.c2;
-    float Kp = kNegInf, Kq = kNegInf, sp = 0.0f, sq = 0.0f;
-    for (int r0 = 0; r0 < R; r0 += U) {
-        chunk_t xp[U], xq[U];
+    const float u = a.u[n];
+    ChunkSum cp[CPT], cq[MIX ? CPT : 1];
+    float Kp = kNegInf, Kq = kNegInf, fp = 0.0f, fq = 0.0f;
+    cq[0] = ChunkSum{0.0f, 0.0f};
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int off = cut.off((r0 + u) * W + tid);
-            xp[u] = load_off(prow, off);
-            xq[u] = load_off(qrow, off);
-        }
+    for (int g = 0; g < CPT; g += U) {
+        if (g < R) {
+            chunk_t xp[U], xq[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            fold_chunk<Fmt>(chunk_or_pad<Fmt, W>(xp[u], r0 + u, cut), c2, Kp, sp);
-            fold_chunk<Fmt>(chunk_or_pad<Fmt, W>(xq[u], r0 + u, cut), c2, Kq, sq);
+            for (int r = 0; r < U; ++r) {
+                const int off = cut.off((g + r) * W + tid);
+                xp[r] = load_off(prow, off);
+                if constexpr (MIX) xq[r] = load_off(qrow, off);
+            }
+#pragma unroll
+            for (int r = 0; r < U; ++r) {
+                cp[g + r] = fold_chunk_sum<Fmt>(chunk_or_pad<Fmt, W>(xp[r], g + r, cut), c2, Kp, fp);
+                if constexpr (MIX)
+                    cq[g + r] = fold_chunk_sum<Fmt>(chunk_or_pad<Fmt, W>(xq[r], g + r, cut), c2, Kq, fq);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < U; ++r) cp[g + r] = cq[MIX ? g + r : 0] = ChunkSum{0.0f, 0.0f};
         }
     }
-    {
-        double dp = sp, dq = sq;
-        wave_merge_stats(Kp, dp);
-        wave_merge_stats(Kq, dq);
-        if (lane == 0) {
-            s_max[0][wid] = Kp;
-            s_max[1][wid] = Kq;
-            s_sum[0][wid] = dp;
-            s_sum[1][wid] = dq;
-        }
-    }
+    double Sp = fp, Sq = fq;
     if (tid == 0) s_tok = -1;
-    __syncthreads();
-    Kp = s_max[0][0];
-    Kq = s_max[1][0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-        Kp = fmaxf(Kp, s_max[0][w]);
-        Kq = fmaxf(Kq, s_max[1][w]);
-    }
-    double Sp = 0.0, Sq = 0.0;
-    for (int w = 0; w < NW; ++w) {
-        Sp += rescale(s_sum[0][w], s_max[0][w], Kp);
-        Sq += rescale(s_sum[1][w], s_max[1][w], Kq);
-    }
-    const bool bad = !(Kp > kNegInf && Kp < -kNegInf) || !usable_sum(Sp) || !(Kq > kNegInf && Kq < -kNegInf) ||
-                     !usable_sum(Sq);
+    block_merge2<NW>(Kp, Sp, Kq, Sq, s_max, s_sum);
+    const bool bad = !(Kp > kNegInf && Kp < -kNegInf) || !usable_sum(Sp) ||
+                     (MIX && (!(Kq > kNegInf && Kq < -kNegInf) || !usable_sum(Sq)));
     if (bad) {
         if (tid == 0) a.out[n] = -1;
         return;
     }
-    const float wp = float(double(a.beta) / Sp), wq = float((1.0 - double(a.beta)) / Sq);
-    const float kp = Kp, kq = Kq;
-    auto masses = [&](int r, float (&m)[EPC]) {
-        const chunk_t tc = stream_chunk<Fmt, W>(prow, r, cut);
-        const chunk_t dc = stream_chunk<Fmt, W>(qrow, r, cut);
+    const SampleMass<MIX> mass(c2, a.beta, Kp, Sp, Kq, Sq);
+    float cm[CPT];
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const float et = exp2_fast(__builtin_fmaf(Fmt::get(tc, e), c2, -kp));
-            const float ed = exp2_fast(__builtin_fmaf(Fmt::get(dc, e), c2, -kq));
-            m[e] = __builtin_fmaf(wp, et, wq * ed);
-        }
+    for (int r = 0; r < CPT; ++r) cm[r] = mass.chunk(cp[r], cq[MIX ? r : 0]);
+    const auto element = [&](int nstar, float (&m)[EPC]) {
+        float kp = 0.0f, kq = 0.0f;
+#pragma unroll
+        for (int r = 0; r < CPT; ++r)
+            if (r == nstar) {
+                kp = cp[r].k;
+                kq = cq[MIX ? r : 0].k;
+            }
+        const chunk_t tc = stream_chunk<Fmt, W>(prow, nstar, cut);
+        mass.template elements<Fmt>(tc, MIX ? stream_chunk<Fmt, W>(qrow, nstar, cut) : tc, kp, kq, m);
     };
-    bool z_zero = false;
-    const int at = draw_inverse_cdf_streamed<kShiftMix, W, EPC>(R, masses, a.u[n], s_tot, &s_draw, &z_zero);
+    const int at = draw_from_sums<MIX ? kShiftMix : kShiftOne, W, CPT, EPC>(cm, element, u, s_tot, &s_draw);
     if (at >= 0) s_tok = cut.token(at);
     __syncthreads();
     if (tid == 0) a.out[n] = s_tok;
@@ -572,36 +588,49 @@ hipError_t launch_tile(const SampleLaunch& L, const SampleArgs& a) {
     return launch_mode<Fmt, W, CPT, VEC, kModeOne>(L, a);
 }
 
+// Rows that fill the chip: streamed where the chunks and sums of the row (pair)
+// would take more than the 64 VGPRs that leave room for eight waves per SIMD
+// (4 chunks per thread of a pair, 8 of one row); shorter rows keep their chunks
+// (4096 rows of V = 2000 bf16 10.6 us, streamed 12.1).
+template <typename Fmt, int W, int CPT>
+hipError_t launch_rows(const SampleLaunch& L, const SampleArgs& a) {
+    if (L.temperature == 0.0f) return launch_mode<Fmt, W, CPT, true, kModeGreedy>(L, a);
+    const dim3 grid(unsigned(L.N)), block(W);
+    if (L.beta > 0.0f && L.beta < 1.0f) {
+        if constexpr (CPT < 4)
+            return launch_mode<Fmt, W, CPT, true, kModeMix>(L, a);
+        else
+            return launch_kernel(&sample_stream_kernel<Fmt, W, CPT, kStreamUnroll, true>, grid, block, 0, L.stream, a);
+    }
+    if constexpr (CPT < 8)
+        return launch_mode<Fmt, W, CPT, true, kModeOne>(L, a);
+    else
+        return launch_kernel(&sample_stream_kernel<Fmt, W, CPT, kStreamUnroll, false>, grid, block, 0, L.stream, a);
+}
+
 template <typename Fmt>
 hipError_t launch_fmt(const SampleLaunch& L, const SampleArgs& a) {
     if (L.V < Fmt::kPerChunk) return launch_tile<Fmt, 256, 1, false>(L, a);  // shorter than one chunk
     hipError_t se;
     if (try_split<Fmt>(L, a, &se)) return se;
     RowTile t;
-    if (!pick_tile(L.V, Fmt::kPerChunk, &t)) {
-        // Longer rows: a mixture streams its row pair; one row (or an
-        // argmax) fits the resident 1024 x 16 tile without spilling.
-        const bool mix = L.temperature > 0.0f && L.beta > 0.0f && L.beta < 1.0f;
-        if (mix)
-            return launch_kernel(&sample_mix_long_kernel<Fmt>, dim3(unsigned(L.N)), dim3(kLongW), 0, L.stream, a);
-        if (L.temperature == 0.0f) return launch_mode<Fmt, 1024, 16, true, kModeGreedy>(L, a);
-        return launch_mode<Fmt, 1024, 16, true, kModeOne>(L, a);
-    }
+    if (!pick_tile(L.V, Fmt::kPerChunk, &t)) return launch_rows<Fmt, 1024, 16>(L, a);
     // Fewer rows than two per CU: the rows' latency is the cost, so each row
-    // gets the widest workgroup (half the elements per thread).
-    if (L.N < 2 * L.cus && t.W < 1024) {
+    // gets the widest workgroup (half the elements per thread), and keeps its
+    // chunks while they fit.
+    if (L.N < 2 * L.cus) {
         const int per = 1024 * Fmt::kPerChunk;
-        t = RowTile{1024, L.V <= 2 * per ? 2 : (L.V <= 4 * per ? 4 : 8)};
+        if (L.V <= 2 * per) return launch_tile<Fmt, 1024, 2, true>(L, a);
+        if (L.V <= 4 * per) return launch_tile<Fmt, 1024, 4, true>(L, a);
+        return launch_rows<Fmt, 1024, 8>(L, a);
     }
     switch (t.W * 100 + t.CPT) {
-        case 102402: return launch_tile<Fmt, 1024, 2, true>(L, a);
-        case 102404: return launch_tile<Fmt, 1024, 4, true>(L, a);
-        case 25601: return launch_tile<Fmt, 256, 1, true>(L, a);
-        case 25602: return launch_tile<Fmt, 256, 2, true>(L, a);
-        case 25604: return launch_tile<Fmt, 256, 4, true>(L, a);
-        case 51204: return launch_tile<Fmt, 512, 4, true>(L, a);
-        case 51208: return launch_tile<Fmt, 512, 8, true>(L, a);
-        case 102408: return launch_tile<Fmt, 1024, 8, true>(L, a);
+        case 25601: return launch_rows<Fmt, 256, 1>(L, a);
+        case 25602: return launch_rows<Fmt, 256, 2>(L, a);
+        case 25604: return launch_rows<Fmt, 256, 4>(L, a);
+        case 51204: return launch_rows<Fmt, 512, 4>(L, a);
+        case 51208: return launch_rows<Fmt, 512, 8>(L, a);
+        case 102408: return launch_rows<Fmt, 1024, 8>(L, a);
         default: return hipErrorInvalidValue;
     }
 }
