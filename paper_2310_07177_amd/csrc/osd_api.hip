@@ -170,8 +170,9 @@ int osd_verify(const void* target_logits, const void* draft_logits, int dtype, i
     L.counters = reinterpret_cast<uint32_t*>(w + ws.counters);
     L.seg_stats = reinterpret_cast<osd::SegStats*>(w + ws.stats);
     L.stream = static_cast<hipStream_t>(stream);
-    // Greedy: segmented kernels (balanced over every CU).  Sampling: the
-    // row-resident kernel, which draws from rows it already holds.
+    L.cus = device_cus(L.stream);
+    // Greedy: segmented kernels (balanced over every CU).  Sampling: kernels
+    // that draw from rows they already hold.
     int nseg = 0;
     const bool segmented = greedy && osd::greedy_segments(V, per_chunk(dtype), &nseg);
     const hipError_t e = segmented ? osd::launch_verify_greedy(L) : osd::launch_verify(L);

@@ -231,19 +231,38 @@ __device__ inline void load_rows_interleaved(chunk_t (&a)[CPT], chunk_t (&b)[CPT
     }
 }
 
-// Chunk n of this thread as loaded by load_row<VEC>, with its padding.
-// Rounds before the row's end take no instruction for it.
+// Chunk n of this thread as loaded by load_row<VEC>, padding if it lies past
+// the row.  Rounds before the row's end take no instruction for it.
 template <typename Fmt, int W>
 __device__ inline chunk_t chunk_or_pad(const chunk_t& c, int n, const RowCut<Fmt>& cut) {
     if (!cut.template ragged<W>(n)) return c;
-    return pad_lead<Fmt>(c, cut.lead(n * W + static_cast<int>(threadIdx.x)));
+    const bool in = n * W + static_cast<int>(threadIdx.x) < cut.nchunks;
+    const chunk_t pad = pad_chunk<Fmt>();
+    return chunk_t{in ? c.x : pad.x, in ? c.y : pad.y, in ? c.z : pad.z, in ? c.w : pad.w};
+}
+
+// Pad the shared head of the row's last chunk in the wave that holds it (among
+// rounds first .. first + CPT - 1), as soon as its load has landed.  Kept apart
+// from the per-chunk code so that the other waves skip it on one branch: in a
+// kernel of a few microseconds the instruction fetch past sixteen inline copies
+// cost 0.5 us.
+template <typename Fmt, int W, int CPT>
+__device__ inline void pad_shared_head(chunk_t (&c)[CPT], const RowCut<Fmt>& cut, int first = 0) {
+    const int n = (cut.nchunks - 1) / W - first, t = (cut.nchunks - 1) % W;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+    if (cut.dup == 0 || n < 0 || n >= CPT || t / kWave != wave) return;
+    const int lead = static_cast<int>(threadIdx.x) == t ? cut.dup : 0;
+#pragma unroll
+    for (int r = 0; r < CPT; ++r)
+        if (r == n) c[r] = pad_lead<Fmt>(c[r], lead);
 }
 
 // Apply the padding to every chunk of load_row<VEC>.
 template <typename Fmt, int W, int CPT>
-__device__ inline void pad_row_tail(chunk_t (&c)[CPT], const RowCut<Fmt>& cut) {
+__device__ inline void pad_row_tail(chunk_t (&c)[CPT], const RowCut<Fmt>& cut, int first = 0) {
+    pad_shared_head<Fmt, W, CPT>(c, cut, first);
 #pragma unroll
-    for (int n = 0; n < CPT; ++n) c[n] = chunk_or_pad<Fmt, W>(c[n], n, cut);
+    for (int n = 0; n < CPT; ++n) c[n] = chunk_or_pad<Fmt, W>(c[n], first + n, cut);
 }
 
 // Make register-resident chunks opaque to the optimiser at the start of a
@@ -435,6 +454,7 @@ __device__ inline void fold_chunk(const chunk_t& x, float c2, float& K, double& 
 // landed).
 template <typename Fmt, int W, int CPT, bool VEC, typename Acc>
 __device__ inline void row_stats(chunk_t (&c)[CPT], const RowCut<Fmt>& cut, float c2, float& K, Acc& S) {
+    if constexpr (VEC) pad_shared_head<Fmt, W, CPT>(c, cut);
 #pragma unroll
     for (int n = 0; n < CPT; ++n) {
         if constexpr (VEC) c[n] = chunk_or_pad<Fmt, W>(c[n], n, cut);
@@ -450,6 +470,8 @@ __device__ inline void row_stats(chunk_t (&c)[CPT], const RowCut<Fmt>& cut, floa
 template <typename Fmt, int W, int CPT>
 __device__ inline void row_stats2(chunk_t (&a)[CPT], chunk_t (&b)[CPT], const RowCut<Fmt>& cut, float c2, bool second,
                                   float& Ka, float& Sa, float& Kb, float& Sb) {
+    pad_shared_head<Fmt, W, CPT>(a, cut);
+    if (second) pad_shared_head<Fmt, W, CPT>(b, cut);
 #pragma unroll
     for (int n = 0; n < CPT; ++n) {
         a[n] = chunk_or_pad<Fmt, W>(a[n], n, cut);
@@ -465,7 +487,9 @@ __device__ inline void row_stats2(chunk_t (&a)[CPT], chunk_t (&b)[CPT], const Ro
 // Chunk n*W + tid of a row streamed from memory, padded.
 template <typename Fmt, int W>
 __device__ inline chunk_t stream_chunk(const void* row, int n, const RowCut<Fmt>& cut) {
-    return chunk_or_pad<Fmt, W>(load_off(row, cut.off(n * W + static_cast<int>(threadIdx.x))), n, cut);
+    const int ch = n * W + static_cast<int>(threadIdx.x);
+    const chunk_t c = load_off(row, cut.off(ch));
+    return cut.template ragged<W>(n) ? pad_lead<Fmt>(c, cut.lead(ch)) : c;
 }
 
 // Merge (K, S) across the wave; every lane returns the wave's pair.

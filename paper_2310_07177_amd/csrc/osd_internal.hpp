@@ -62,7 +62,8 @@ struct VerifyLaunch {
     uint8_t* reject_mask;
     uint32_t* records;   // [B*(K+1)] zero on entry and exit
     uint32_t* counters;  // [B]       zero on entry and exit
-    SegStats* seg_stats;  // [B*(K+1)*kMaxSeg] greedy argmax partials, zero on entry and exit
+    SegStats* seg_stats;  // [B*(K+1)*kMaxSeg] greedy argmax partials or split rows' words, zero on entry and exit
+    int cus;
     hipStream_t stream;
 };
 

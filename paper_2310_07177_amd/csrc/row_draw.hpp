@@ -150,11 +150,11 @@ __device__ int draw_inverse_cdf(const chunk_t (&tv)[CPT], const chunk_t (&dv)[CP
 
 namespace osd {
 
-// Rounds of a row streamed by a workgroup of W threads: chunk r*W + tid in
-// round r.  The streamed kernels hold at most kMaxStreamRounds rounds' worth of
-// cell totals in LDS (16 rounds of 1024 threads: 131072 bf16 or 65536 fp32
-// logits per row).
+// Rounds of the longest row in a workgroup of 1024 threads (131072 bf16 or 65536
+// fp32 logits per row).
 constexpr int kMaxStreamRounds = 16;
+// Cells (round, wave) of the longest row, whatever the workgroup's width.
+constexpr int kMaxStreamCells = kMaxStreamRounds * (1024 / kWave);
 
 // Inverse-CDF draw over a row whose chunk masses are already known: chunk[n] is
 // the mass of this thread's chunk of round n (the left-to-right fp32 sum of its
@@ -183,39 +183,53 @@ __device__ int draw_from_sums(const float (&chunk)[CPT], ElementFn element, floa
     return walk_chunk<SH, W, EPC>(m, s, s_draw->target, nstar);
 }
 
-// Inverse-CDF draw over a row that is streamed from memory instead of held in
-// registers.  masses(r, m) fills m[0..EPC) with the non-negative fp32 masses
-// of this thread's chunk in round r (0 for padding); it is called once per
-// round in pass A and once more, for the winning round, by the winning wave in
-// pass B, and must return the same values both times.  Cells are (round,
-// wave); chunk masses are summed left to right in fp32 and converted exactly
-// to 2^-SH fixed point, as in draw_inverse_cdf, so the CDF cells partition
-// [0, Z) exactly.  Returns the element's place on one thread and -1 on the others;
-// *z_zero is set (uniformly) when the total mass is zero.  s_tot holds
-// R * (W / 64) cells.  All threads call it.
-template <int SH, int W, int EPC, typename MassFn>
-__device__ int draw_inverse_cdf_streamed(int R, MassFn masses, float u, unsigned long long* s_tot,
-                                         DrawShared* s_draw, bool* z_zero) {
-    constexpr int NW = W / kWave;
+// Inverse-CDF draw over a row (pair) that is streamed from memory instead of
+// held in registers: U rounds of loads in flight per thread (one at a time, each
+// round cost a memory latency).  mass(t, d, e) as in draw_inverse_cdf; use_d: whether the second
+// row is read.  Pass A sums every chunk; pass B, by the winning wave, reads its
+// round again.  Returns the element's place on one thread and -1 on the others;
+// *z_zero is set (uniformly) when the total mass is zero.  s_tot holds R * (W / 64)
+// cells.  All threads call it.
+template <int SH, typename Fmt, int W, int U, typename MassFn>
+__device__ int draw_inverse_cdf_streamed(const void* trow, const void* drow, bool use_d, const RowCut<Fmt>& cut,
+                                         MassFn mass, float u, unsigned long long* s_tot, DrawShared* s_draw,
+                                         bool* z_zero) {
+    constexpr int NW = W / kWave, EPC = Fmt::kPerChunk;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
-    for (int r = 0; r < R; ++r) {
-        float m[EPC];
-        masses(r, m);
-        float s = 0.0f;
+    const int R = (cut.nchunks + W - 1) / W;
+    for (int r0 = 0; r0 < R; r0 += U) {
+        chunk_t xt[U], xd[U];
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) s = s + m[e];
-        const double t = wave_sum(fixed_f64<SH>(s));
-        if (lane == 0) s_tot[r * NW + wid] = uint64_t(t);
+        for (int k = 0; k < U; ++k) {
+            const int off = cut.off((r0 + k) * W + tid);
+            xt[k] = load_off(trow, off);
+            if (use_d) xd[k] = load_off(drow, off);
+        }
+        pad_row_tail<Fmt, W, U>(xt, cut, r0);
+        if (use_d) pad_row_tail<Fmt, W, U>(xd, cut, r0);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            float s = 0.0f;
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) s = s + mass(xt[k], xd[k], e);
+            const double t = wave_sum(fixed_f64<SH>(s));
+            if (lane == 0 && r0 + k < R) s_tot[(r0 + k) * NW + wid] = uint64_t(t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     locate_cell<NW>(R * NW, s_tot, u, -1, s_draw);
     const int nstar = s_draw->cell_round;
     *z_zero = nstar < 0;
     if (nstar < 0 || wid != s_draw->cell_wave) return -1;
+    const chunk_t tc = stream_chunk<Fmt, W>(trow, nstar, cut);
+    const chunk_t dc = use_d ? stream_chunk<Fmt, W>(drow, nstar, cut) : tc;
     float m[EPC];
-    masses(nstar, m);
     float s = 0.0f;
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) s = s + m[e];
+    for (int e = 0; e < EPC; ++e) {
+        m[e] = mass(tc, dc, e);
+        s = s + m[e];
+    }
     return walk_chunk<SH, W, EPC>(m, s, s_draw->target, nstar);
 }
 

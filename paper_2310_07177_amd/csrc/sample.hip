@@ -156,6 +156,10 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void sample_kernel(S
         const float u = a.u[n];
         ChunkSum cp[CPT], cq[MIX ? CPT : 1];
         float Kp = kNegInf, Kq = kNegInf, fp = 0.0f, fq = 0.0f;
+        if constexpr (VEC) {
+            pad_shared_head<Fmt, W, CPT>(tv, cut);
+            if constexpr (MIX) pad_shared_head<Fmt, W, CPT>(dv, cut);
+        }
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
             if constexpr (VEC) tv[r] = chunk_or_pad<Fmt, W>(tv[r], r, cut);
@@ -234,6 +238,8 @@ __global__ __launch_bounds__(W, 1) void sample_stream_kernel(SampleArgs a) {
                 xp[r] = load_off(prow, off);
                 if constexpr (MIX) xq[r] = load_off(qrow, off);
             }
+            pad_shared_head<Fmt, W, U>(xp, cut, g);
+            if constexpr (MIX) pad_shared_head<Fmt, W, U>(xq, cut, g);
 #pragma unroll
             for (int r = 0; r < U; ++r) {
                 cp[g + r] = fold_chunk_sum<Fmt>(chunk_or_pad<Fmt, W>(xp[r], g + r, cut), c2, Kp, fp);
@@ -393,8 +399,7 @@ __global__ __launch_bounds__(kSegSampleW) void sample_split_kernel(SplitSampleAr
     chunk_t x[CPT];
 #pragma unroll
     for (int r = 0; r < CPT; ++r) x[r] = load_off(row, cut.off(s * SEG + r * W + tid));
-#pragma unroll
-    for (int r = 0; r < CPT; ++r) x[r] = chunk_or_pad<Fmt, W>(x[r], s * CPT + r, cut);
+    pad_row_tail<Fmt, W, CPT>(x, cut, s * CPT);
     if (tid == 0) s_tok = -1;  // ordered before the walk by the statistics' barriers
     float k;
     double T;

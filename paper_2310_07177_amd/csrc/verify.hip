@@ -7,8 +7,9 @@
 // from norm(max(0, p - q)) at row a, or from p at the bonus row when all k
 // were accepted.  p and q are temperature softmaxes of the logits.
 //
-// Work layout.  One workgroup per (sequence b, proposal row i), numbered
-// position-major, then one workgroup per bonus row.  A proposal workgroup
+// Work layout (rows of up to 8 chunks per thread of 512 threads; the other
+// lengths and few rows below).  One workgroup per (sequence b, proposal row i),
+// numbered position-major, then one workgroup per bonus row.  A proposal workgroup
 // reads its target and draft rows from HBM exactly once into registers,
 // reduces the row maxima and sums of exponentials, and takes the acceptance
 // test.  A rejecting workgroup announces the rejection at once, then learns
@@ -20,9 +21,12 @@
 // its row entirely.  Every workgroup publishes a one-word record; the last of
 // the k_b + 1 workgroups of a sequence to arrive selects the first rejection,
 // writes the outputs, and clears the records and the counter.
+#include <stdlib.h>
+
 #include "osd_device.hpp"
 #include "osd_internal.hpp"
 #include "row_draw.hpp"
+#include "stream_device.hpp"
 
 namespace osd {
 namespace {
@@ -61,7 +65,9 @@ constexpr int kFixedShift = 44;
 // measured 0.4 us at B = 64, k = 8).  The streamed kernel, whose draw reads
 // the row pair again, waits longer (24 looks with a short sleep).
 constexpr int kMaxPolls = 1;
-constexpr int kMaxLongPolls = 24;
+
+// Polls of the last arriver for records that were posted before it arrived.
+constexpr int kRecordPolls = 4096;
 
 struct VerifyArgs {
     const void* target;
@@ -97,18 +103,28 @@ __device__ void publish(const VerifyArgs& a, int b, int i, int kb, uint32_t reco
     const int lane = threadIdx.x & (kWave - 1);
     uint32_t* recs = a.records + int64_t(b) * (K + 1);
     uint32_t prev = 0;
-    if (lane == 0) {
-        publish_u32(&recs[i], record);
-        prev = arrive(&a.counters[b]);
+    if (lane == 0) {  // one round trip: the arrival does not wait for the record
+        __hip_atomic_exchange(&recs[i], record, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        prev = __hip_atomic_fetch_add(&a.counters[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     prev = __shfl(prev, 0, kWave);
     if (prev != uint32_t(kb)) return;
 
+    // The last arriver.  Every record is posted; wait (bounded) for those still
+    // on their way, then clear them.
+    uint32_t r = lane == i ? record : 0u;
+    for (int p = 0; p < kRecordPolls; ++p) {
+        if (lane <= kb && lane != i) r = load_relaxed(&recs[lane]);
+        const uint32_t s = rec_state(r);
+        if (__ballot(lane <= kb && (s == kRecEmpty || s == kRecRejectPending)) == 0) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    wait_memory();  // this workgroup's own record is in place before it is cleared
+    if (lane <= kb) __hip_atomic_store(&recs[lane], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
     // First rejection (Appendix A.1: the test stops there).  A proposal
     // outside the vocabulary invalidates the sequence wherever it sits; a row
-    // without finite logits only if the test reaches it.  Records are read
-    // and cleared in one step.
-    const uint32_t r = lane <= kb ? take_u32(&recs[lane]) : 0u;
+    // without finite logits only if the test reaches it.
     const uint32_t s = rec_state(r);
     const bool bad_token = __ballot(lane < kb && s == kRecBadToken) != 0;
     const uint64_t stop = __ballot(lane < kb && s != kRecAccept);
@@ -134,7 +150,7 @@ __device__ void publish(const VerifyArgs& a, int b, int i, int kb, uint32_t reco
     }
     if (lane == 0) {
         a.accepted_len[b] = bad ? -1 : acc;
-        take_u32(&a.counters[b]);
+        __hip_atomic_store(&a.counters[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -151,6 +167,16 @@ __device__ int poll_earlier(const VerifyArgs& a, int b, int i, int polls) {
         if (p + 1 >= polls) return 0;
         __builtin_amdgcn_s_sleep(8);
     }
+}
+
+// p(y)/q(y) = 2^e S_d / S_t with e = (t_y c2 - K_t) - (d_y c2 - K_d) in fp64; 2^e is
+// split into an exact power of two and 2^frac (v_exp_f32, 1 ulp).
+__device__ inline double acceptance_ratio(float ty, float dy, float Kt, double St, float Kd, double Sd, double c2d) {
+    const double e = (double(ty) * c2d - double(Kt)) - (double(dy) * c2d - double(Kd));
+    if (!(e > -2000.0)) return 0.0;  // p(y) = 0 (or both probabilities 0)
+    if (e > 2000.0) return __builtin_huge_val();
+    const double n = floor(e);
+    return __builtin_ldexp(double(exp2_fast(float(e - n))), int(n)) * (Sd / St);
 }
 
 template <typename Fmt, int W, int CPT, bool VEC, bool GREEDY>
@@ -326,21 +352,9 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void verify_kernel(V
         if (wid == 0) {
             int flag = 1;
             if (!bonus) {
-                // Acceptance test: p(y)/q(y) = 2^e * S_d / S_t with
-                // e = (t_y c2 - K_t) - (d_y c2 - K_d) in fp64; 2^e is split
-                // into an exact power of two and 2^frac (v_exp_f32, 1 ulp).
                 asm volatile("" : "+v"(ty_raw), "+v"(dy_raw));  // converted here, not at the load
-                const float ty = Fmt::from_raw(ty_raw), dy = Fmt::from_raw(dy_raw);
-                const double e = (double(ty) * a.c2d - double(Kt)) - (double(dy) * a.c2d - double(Kd));
-                double ratio;
-                if (!(e > -2000.0)) {
-                    ratio = 0.0;  // p(y) = 0 (or both probabilities 0)
-                } else if (e > 2000.0) {
-                    ratio = __builtin_huge_val();
-                } else {
-                    const double n = floor(e);
-                    ratio = __builtin_ldexp(double(exp2_fast(float(e - n))), int(n)) * (Sd / St);
-                }
+                const double ratio =
+                    acceptance_ratio(Fmt::from_raw(ty_raw), Fmt::from_raw(dy_raw), Kt, St, Kd, Sd, a.c2d);
                 const double u = a.u_accept[int64_t(b) * K + i];
                 if (u < ratio) {
                     flag = 0;
@@ -405,24 +419,27 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void verify_kernel(V
     }
 }
 
-// Rows too long to hold (more than 8 chunks per thread of a 1024-thread
-// workgroup): the same per-row protocol as verify_kernel, with the rows
-// streamed from memory.  The statistics take one pass over the row pair (four
-// rounds of loads in flight per thread); the workgroup that draws streams the
-// row pair again (pass A of draw_inverse_cdf_streamed) and its winning wave
-// reloads one round (pass B).  Nothing is held across passes but (K, S), so
-// no register spills at any row length.
-constexpr int kLongW = 1024;
-constexpr int kLongUnroll = 4;
+// Rows too long to hold, and more of them than one per CU (verify_stream_kernel):
+// the same per-row protocol as verify_kernel, with the rows streamed.  The
+// statistics take one pass over the row pair, kUnroll rounds of loads in flight
+// per thread; the workgroup that draws streams the row pair again (pass A of
+// draw_inverse_cdf_streamed) and its winning wave reloads one round (pass B).
+// Nothing but (K, S) is held across passes, so eight waves per SIMD hide the
+// loads: 2304 rows of V = 50304 bf16 118.7 -> 95.6 us (held, 1024 threads x 8 chunks,
+// 124 VGPRs, before); 256 sequences of V = 128256, ragged, 159 -> 152 us.
+constexpr int kUnroll = 4;
+constexpr int kStreamW = 512;
+// Looks at the earlier positions before a draw that reads the rows again.
+constexpr int kMaxStreamPolls = 24;
 
-template <typename Fmt>
-__global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
-    constexpr int W = kLongW, NW = W / kWave, EPC = Fmt::kPerChunk, U = kLongUnroll;
+template <typename Fmt, int W>
+__global__ __launch_bounds__(W, 1) void verify_stream_kernel(VerifyArgs a) {
+    constexpr int NW = W / kWave, EPC = Fmt::kPerChunk, U = kUnroll;
     __shared__ float s_max[2][NW];
     __shared__ double s_sum[2][NW];
     __shared__ int s_flag;
     __shared__ int s_tok;
-    __shared__ unsigned long long s_tot[kMaxStreamRounds * NW];
+    __shared__ unsigned long long s_tot[kMaxStreamCells];
     __shared__ DrawShared s_draw;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
@@ -482,6 +499,8 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
             xt[u] = load_off(trow, off);
             if (!bonus) xd[u] = load_off(drow, off);
         }
+        pad_shared_head<Fmt, W, U>(xt, cut, r0);
+        if (!bonus) pad_shared_head<Fmt, W, U>(xd, cut, r0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             fold_chunk<Fmt>(chunk_or_pad<Fmt, W>(xt[u], r0 + u, cut), c2, Kt, st);
@@ -523,29 +542,20 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
     if (wid == 0) {
         int flag = 1;
         if (!bonus) {
-            const float ty = Fmt::from_raw(ty_raw), dy = Fmt::from_raw(dy_raw);
-            const double e = (double(ty) * a.c2d - double(Kt)) - (double(dy) * a.c2d - double(Kd));
-            double ratio;
-            if (!(e > -2000.0)) {
-                ratio = 0.0;
-            } else if (e > 2000.0) {
-                ratio = __builtin_huge_val();
-            } else {
-                const double n = floor(e);
-                ratio = __builtin_ldexp(double(exp2_fast(float(e - n))), int(n)) * (Sd / St);
-            }
+            const double ratio =
+                acceptance_ratio(Fmt::from_raw(ty_raw), Fmt::from_raw(dy_raw), Kt, St, Kd, Sd, a.c2d);
             const double u = a.u_accept[int64_t(b) * K + i];
             if (u < ratio) {
                 flag = 0;
                 publish(a, b, i, kb, make_rec(kRecAccept, 0));
             } else {
                 if (lane == 0) publish_u32(a.records + int64_t(b) * (K + 1) + i, make_rec(kRecRejectPending, 0));
-                if (i > 0 && poll_earlier(a, b, i, kMaxLongPolls) == 2) {
+                if (i > 0 && poll_earlier(a, b, i, kMaxStreamPolls) == 2) {
                     flag = 0;
                     publish(a, b, i, kb, make_rec(kRecRejectSkipped, 0));
                 }
             }
-        } else if (poll_earlier(a, b, i, kMaxLongPolls) == 2) {
+        } else if (poll_earlier(a, b, i, kMaxStreamPolls) == 2) {
             flag = 0;
             publish(a, b, i, kb, make_rec(kRecBonusSkipped, 0));
         }
@@ -561,22 +571,15 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
     for (int attempt = 0; attempt < 2; ++attempt) {
         const bool p_only = use_p;
         const float kt = Kt, kd = Kd;
-        auto masses = [&](int r, float (&m)[EPC]) {
-            const chunk_t tc = stream_chunk<Fmt, W>(trow, r, cut);
-            const chunk_t dc = p_only ? tc : stream_chunk<Fmt, W>(drow, r, cut);
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const float pt = exp2_fast(__builtin_fmaf(Fmt::get(tc, e), c2, -kt));
-                if (p_only) {
-                    m[e] = pt;
-                } else {
-                    const float qt = exp2_fast(__builtin_fmaf(Fmt::get(dc, e), c2, -kd));
-                    m[e] = fmaxf(__builtin_fmaf(-qt, rho, pt), 0.0f);
-                }
-            }
+        const auto mass = [=](const chunk_t& tc, const chunk_t& dc, int e) -> float {
+            const float pt = exp2_fast(__builtin_fmaf(Fmt::get(tc, e), c2, -kt));
+            if (p_only) return pt;
+            const float qt = exp2_fast(__builtin_fmaf(Fmt::get(dc, e), c2, -kd));
+            return fmaxf(__builtin_fmaf(-qt, rho, pt), 0.0f);
         };
         bool z_zero = false;
-        const int at = draw_inverse_cdf_streamed<kFixedShift, W, EPC>(R, masses, u, s_tot, &s_draw, &z_zero);
+        const int at = draw_inverse_cdf_streamed<kFixedShift, Fmt, W, U>(trow, drow, !p_only, cut, mass, u, s_tot, &s_draw,
+                                                                        &z_zero);
         if (at >= 0) s_tok = cut.token(at);
         if (!z_zero || use_p) break;
         use_p = true;
@@ -589,10 +592,420 @@ __global__ __launch_bounds__(kLongW, 1) void verify_long_kernel(VerifyArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// Rows split over workgroups (verify_split_kernel): rows longer than the
+// resident tiles, and few rows, where one workgroup per row would leave most of
+// the chip idle.  Each row (pair) is cut into at most kMaxSplit segments of
+// W * CPT chunks; the workgroup of a segment holds it in registers.
+//   1. It folds its (K, S) pairs and publishes them, reads its siblings' and
+//      merges all in segment order, so every segment has the same normalisers,
+//      bit for bit, and takes the same decision.
+//   2. An accepted row is reported by segment 0.  A rejected one (or a bonus
+//      row) draws: each segment publishes the fixed-point mass of its part,
+//      reads its siblings', and the one whose part holds the point walks to the
+//      token and reports the row.  A row without residual mass after rounding
+//      repeats this with the masses of p.
+// A rejecting row does not ask whether an earlier position rejected as well: its
+// segments would have to agree on what they saw, which costs as much as the
+// draw from registers.  The finalizer takes the first rejection's token.  A
+// bonus row is skipped if an earlier rejection is on record when its first
+// segment looks (the segments agree through one compare-and-swap).
+// Published words are never zero, so a reader polls the words themselves; a wait
+// is bounded (kSplitPolls polls, or the value of OSD_VERIFY_POLLS), and a
+// workgroup that runs out computes the missing records itself from the rows in
+// memory, bit for bit as their owners do.  Each segment arrives at its row's
+// counter once it has read all it needs; the last one clears the row's words.
+//
+// One workgroup per row before: B = 1, K = 4, V = 32000 bf16 13.5 -> 10.1 us (a chain
+// of memory latencies and barriers, not bandwidth, bounds these calls), B = 8,
+// K = 5 14.5 -> 11.9; B = 1, V = 128256 46.1 -> 13.8, B = 16 49.2 -> 22.1.
+// ---------------------------------------------------------------------------
+constexpr int kMaxSplit = 8;
+constexpr int kSplitPolls = 256;
+
+// A row's words in the workspace (in the place of its kMaxSeg argmax partials).
+struct SplitRow {
+    uint64_t stats[kMaxSplit][3];  // ~S_t, ~S_d, ~(K_t | K_d << 32) (bits)
+    uint64_t mass[2][kMaxSplit];   // 2^63 | mass: of the residual, of p
+    uint32_t arrivals;
+    uint32_t bonus;                // a bonus row: 1 read it, 2 skip it
+};
+static_assert(sizeof(SplitRow) <= kMaxSeg * sizeof(SegStats), "a row's words fit its partials");
+
+struct SplitVerifyArgs {
+    VerifyArgs v;
+    SegStats* rows;  // [B*(K+1)] SplitRow, kMaxSeg partials apart; zero on entry and exit
+    int nseg;
+    int polls;
+};
+
+template <int NW, int CPT>
+struct SplitShared {
+    float k[2 * NW];
+    double s[2 * NW];
+    float rk[kMaxSplit][2];    // the row's records, by segment
+    double rs[kMaxSplit][2];
+    float kt, kd;              // merged
+    double st, sd;
+    uint64_t rz[kMaxSplit];    // the row's masses, by segment
+    unsigned long long tot[CPT * NW];
+    DrawShared draw;
+    // One flag per use: a wave may still be reading one when wave 0 writes the next.
+    int skip, stats_ok, mass_ok, decision, tok;
+};
+
+// The segment's (K, S) pairs of both rows into slot `slot` (by thread 0).
+template <typename Fmt, int W, int CPT, int NW>
+__device__ inline void split_stats(chunk_t (&tv)[CPT], chunk_t (&dv)[CPT], float c2, bool second,
+                                   SplitShared<NW, CPT>& sh, int slot) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    float Kt = kNegInf, Kd = kNegInf, ft = 0.0f, fd = 0.0f;
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) {
+        fold_chunk<Fmt>(tv[n], c2, Kt, ft);
+        if (second) fold_chunk<Fmt>(dv[n], c2, Kd, fd);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    double st = ft, sd = fd;
+    wave_merge_stats_u(Kt, st);
+    wave_merge_stats_u(Kd, sd);
+    __syncthreads();  // sh.k and sh.s are reused
+    if (lane == 0) {
+        sh.k[wid] = Kt;
+        sh.k[NW + wid] = Kd;
+        sh.s[wid] = st;
+        sh.s[NW + wid] = sd;
+    }
+    __syncthreads();
+    if (wid == 0) {
+        const bool in = lane < NW;
+        float k0 = in ? sh.k[lane] : kNegInf, k1 = in ? sh.k[NW + lane] : kNegInf;
+        double s0 = in ? sh.s[lane] : 0.0, s1 = in ? sh.s[NW + lane] : 0.0;
+        row0_merge_stats_u(k0, s0);
+        row0_merge_stats_u(k1, s1);
+        if (lane == 0) {
+            sh.rk[slot][0] = k0;
+            sh.rk[slot][1] = k1;
+            sh.rs[slot][0] = s0;
+            sh.rs[slot][1] = s1;
+        }
+    }
+}
+
+// The segment's cell masses into sh.tot and their sum into sh.rz[slot] (wave 0).
+template <typename Fmt, int W, int CPT, int NW, typename MassFn>
+__device__ inline void split_mass(const chunk_t (&tv)[CPT], const chunk_t (&dv)[CPT], MassFn mass,
+                                  SplitShared<NW, CPT>& sh, int slot) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    __syncthreads();  // sh.tot is reused
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) {
+        float s = 0.0f;
+#pragma unroll
+        for (int e = 0; e < Fmt::kPerChunk; ++e) s = s + mass(tv[n], dv[n], e);
+        const double t = wave_sum(fixed_f64<kFixedShift>(s));
+        if (lane == 0) sh.tot[n * NW + wid] = uint64_t(t);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    if (wid == 0) {
+        const uint64_t z = wave_sum(lane < CPT * NW ? uint64_t(sh.tot[lane]) : uint64_t(0));
+        if (lane == 0) sh.rz[slot] = z;
+    }
+}
+
+// Wave 0: lane j < nseg, j != s, reads words[j * WORDS ..] until every one is
+// there or the polls run out; true if they are.
+template <int WORDS>
+__device__ inline bool poll_siblings(const uint64_t* words, int nseg, int s, int polls, uint64_t (&w)[WORDS]) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool mine = lane < nseg && lane != s;
+    for (int p = 0; p < polls; ++p) {
+        if (p > 0) __builtin_amdgcn_s_sleep(2);
+        bool ready = true;
+        if (mine) {
+#pragma unroll
+            for (int k = 0; k < WORDS; ++k) {
+                w[k] = poll_u64(words + lane * WORDS + k);
+                ready = ready && w[k] != 0;
+            }
+        }
+        if (__ballot(!ready) == 0) return true;
+    }
+    return false;
+}
+
+__device__ inline void store_word(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename Fmt, int W, int CPT>
+__device__ inline void split_load(chunk_t (&tv)[CPT], chunk_t (&dv)[CPT], const char* trow, const char* drow, bool second,
+                                  int s, int V) {
+    asm volatile("" : "+s"(V), "+s"(s));  // nothing derived from them is hoisted out of a loop over segments
+    const RowCut<Fmt> cut(V);
+    const int tid = opaque_tid();
+#pragma unroll
+    for (int n = 0; n < CPT; ++n) {
+        const int off = cut.off((s * CPT + n) * W + tid);
+        tv[n] = load_off(trow, off);
+        if (second) dv[n] = load_off(drow, off);
+    }
+}
+template <typename Fmt, int W, int CPT>
+__device__ inline void split_pad(chunk_t (&tv)[CPT], chunk_t (&dv)[CPT], bool second, int s, int V) {
+    asm volatile("" : "+s"(V), "+s"(s));
+    const RowCut<Fmt> cut(V);
+    pad_row_tail<Fmt, W, CPT>(tv, cut, s * CPT);
+    if (second) pad_row_tail<Fmt, W, CPT>(dv, cut, s * CPT);
+}
+
+template <typename Fmt, int W, int CPT>
+__global__ __launch_bounds__(W, Fmt::kPerChunk == 8 ? 6 : 5) void verify_split_kernel(SplitVerifyArgs sa) {
+    constexpr int NW = W / kWave, EPC = Fmt::kPerChunk;
+    static_assert(CPT * NW <= kWave, "one wave sums the cells");
+    __shared__ SplitShared<NW, CPT> sh;
+    const VerifyArgs& a = sa.v;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const int B = a.B, K = a.K, V = a.V, nseg = sa.nseg;
+    const int r = blockIdx.x / nseg, s = blockIdx.x - r * nseg;
+    const bool bonus = r >= B * K;
+    int i = bonus ? -1 : r / B;
+    const int b = bonus ? r - B * K : r - i * B;
+    const int kb = a.draft_len ? a.draft_len[b] : K;
+    if (kb < 1 || kb > K) {
+        if (bonus && s == 0) write_invalid(a, b);
+        return;
+    }
+    if (bonus)
+        i = kb;
+    else if (i >= kb)
+        return;  // padding row of a short proposal
+    const int y = bonus ? 0 : a.tokens[int64_t(b) * K + i];
+    if (!bonus && (y < 0 || y >= V)) {
+        if (s == 0 && wid == 0) publish(a, b, i, kb, make_rec(kRecBadToken, 0));
+        return;
+    }
+    SplitRow* const row = reinterpret_cast<SplitRow*>(sa.rows + (int64_t(b) * (K + 1) + i) * kMaxSeg);
+    if (bonus) {
+        // The first segment to look decides for all of them.
+        if (wid == 0) {
+            const uint32_t want = poll_earlier(a, b, i, 1) == 2 ? 2u : 1u;
+            uint32_t seen = 0u;
+            if (lane == 0) {
+                __hip_atomic_compare_exchange_strong(&row->bonus, &seen, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                sh.skip = (seen != 0u ? seen : want) == 2u;
+            }
+        }
+        __syncthreads();
+        if (sh.skip) {
+            if (wid == 0) {
+                uint32_t prev = 0;
+                if (lane == 0)
+                    prev = __hip_atomic_fetch_add(&row->arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (lane == 0 && prev == uint32_t(nseg - 1)) {  // every segment has taken the decision
+                    __hip_atomic_store(&row->bonus, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&row->arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (s == 0) publish(a, b, i, kb, make_rec(kRecBonusSkipped, 0));
+            }
+            return;
+        }
+    }
+    const bool pair = !bonus;
+    const char* trow = static_cast<const char*>(a.target) + (int64_t(b) * (K + 1) + i) * int64_t(V) * Fmt::kBytes;
+    const char* drow =
+        bonus ? trow : static_cast<const char*>(a.draft) + (int64_t(b) * K + i) * int64_t(V) * Fmt::kBytes;
+    const float c2 = a.c2;
+    // The test's and the draw's scalars, requested before the rows.
+    const uint32_t ty_raw = Fmt::load_raw(trow, y), dy_raw = Fmt::load_raw(drow, y);
+    const float u_acc = bonus ? 0.0f : a.u_accept[int64_t(b) * K + i], u_res = a.u_resample[b];
+    chunk_t tv[CPT], dv[CPT];
+    split_load<Fmt, W, CPT>(tv, dv, trow, drow, pair, s, V);
+    split_pad<Fmt, W, CPT>(tv, dv, pair, s, V);
+
+    // 1. statistics
+    split_stats<Fmt, W, CPT, NW>(tv, dv, c2, pair, sh, s);
+    if (wid == 0) {
+        if (lane == 0) {
+            store_word(&row->stats[s][0], ~uint64_t(__double_as_longlong(sh.rs[s][0])));
+            store_word(&row->stats[s][1], ~uint64_t(__double_as_longlong(sh.rs[s][1])));
+            store_word(&row->stats[s][2], ~(uint64_t(__float_as_uint(sh.rk[s][0])) |
+                                            (uint64_t(__float_as_uint(sh.rk[s][1])) << 32)));
+        }
+        uint64_t w[3] = {0, 0, 0};
+        const bool ok = poll_siblings<3>(&row->stats[0][0], nseg, s, sa.polls, w);
+        if (ok && lane < nseg && lane != s) {
+            sh.rs[lane][0] = __longlong_as_double(~w[0]);
+            sh.rs[lane][1] = __longlong_as_double(~w[1]);
+            sh.rk[lane][0] = __uint_as_float(uint32_t(~w[2]));
+            sh.rk[lane][1] = __uint_as_float(uint32_t(~w[2] >> 32));
+        }
+        if (lane == 0) sh.stats_ok = ok;
+    }
+    __syncthreads();
+    if (!sh.stats_ok) {  // out of polls: every other segment's record from memory, then this segment again
+#pragma unroll 1
+        for (int j = 0; j < nseg; ++j) {
+            if (j == s) continue;
+            split_load<Fmt, W, CPT>(tv, dv, trow, drow, pair, j, V);
+            split_pad<Fmt, W, CPT>(tv, dv, pair, j, V);
+            split_stats<Fmt, W, CPT, NW>(tv, dv, c2, pair, sh, j);
+        }
+        split_load<Fmt, W, CPT>(tv, dv, trow, drow, pair, s, V);
+        split_pad<Fmt, W, CPT>(tv, dv, pair, s, V);
+    }
+    // The decision, the same in every segment.
+    if (wid == 0) {
+        const bool in = lane < nseg;
+        float Kt = in ? sh.rk[lane][0] : kNegInf, Kd = in ? sh.rk[lane][1] : kNegInf;
+        double St = in ? sh.rs[lane][0] : 0.0, Sd = in ? sh.rs[lane][1] : 0.0;
+        row0_merge_stats_u(Kt, St);
+        row0_merge_stats_u(Kd, Sd);
+        const bool bad = !(Kt > kNegInf && Kt < -kNegInf) || !usable_sum(St) ||
+                         (pair && (!(Kd > kNegInf && Kd < -kNegInf) || !usable_sum(Sd)));
+        const bool accept = !bad && pair &&
+                            double(u_acc) < acceptance_ratio(Fmt::from_raw(ty_raw), Fmt::from_raw(dy_raw), Kt, St, Kd, Sd, a.c2d);
+        if (lane == 0) {
+            sh.kt = Kt;
+            sh.kd = Kd;
+            sh.st = St;
+            sh.sd = Sd;
+            sh.decision = bad ? 0 : (accept ? 1 : 2);
+            sh.tok = -1;
+        }
+        if (s == 0 && (bad || accept)) publish(a, b, i, kb, make_rec(bad ? kRecBadRow : kRecAccept, 0));
+    }
+    __syncthreads();
+    const bool draws = sh.decision == 2;
+    const float Kt = sh.kt, Kd = sh.kd;
+    const float rho = bonus ? 0.0f : float(sh.st / sh.sd);
+
+    // 2. the extra token: masses in units of S_t, as verify_kernel's.
+    int attempt = bonus ? 1 : 0;  // 0: max(0, p - q), 1: p
+    bool mine = false;
+    uint32_t rec = 0u;
+    while (draws) {
+        float mtc = Kt, mdc = Kd;
+        asm volatile("" : "+v"(mtc), "+v"(mdc));  // the exponentials are taken afresh (bounded VGPRs)
+        opaque(tv);
+        const bool p_only = attempt == 1;
+        if (!p_only) opaque(dv);
+        const auto mass = [=](const chunk_t& tc, const chunk_t& dc, int e) -> float {
+            const float pt = exp2_fast(__builtin_fmaf(Fmt::get(tc, e), c2, -mtc));
+            if (p_only) return pt;
+            const float qt = exp2_fast(__builtin_fmaf(Fmt::get(dc, e), c2, -mdc));
+            return fmaxf(__builtin_fmaf(-qt, rho, pt), 0.0f);
+        };
+        split_mass<Fmt, W, CPT, NW>(tv, dv, mass, sh, s);
+        if (wid == 0) {
+            if (lane == 0) store_word(&row->mass[attempt][s], (1ull << 63) | sh.rz[s]);
+            uint64_t w[1] = {0};
+            const bool ok = poll_siblings<1>(row->mass[attempt], nseg, s, sa.polls, w);
+            if (ok && lane < nseg && lane != s) sh.rz[lane] = w[0] & ~(1ull << 63);
+            if (lane == 0) sh.mass_ok = ok;
+        }
+        __syncthreads();
+        if (!sh.mass_ok) {
+#pragma unroll 1
+            for (int j = 0; j < nseg; ++j) {
+                if (j == s) continue;
+                split_load<Fmt, W, CPT>(tv, dv, trow, drow, pair, j, V);
+                split_pad<Fmt, W, CPT>(tv, dv, pair, j, V);
+                split_mass<Fmt, W, CPT, NW>(tv, dv, mass, sh, j);
+            }
+            split_load<Fmt, W, CPT>(tv, dv, trow, drow, pair, s, V);
+            split_pad<Fmt, W, CPT>(tv, dv, pair, s, V);
+            split_mass<Fmt, W, CPT, NW>(tv, dv, mass, sh, s);
+            __syncthreads();
+        }
+        // The point in the whole row's CDF, exact, the same in every segment.
+        uint64_t Z = 0, lo = 0;
+        for (int j = 0; j < nseg; ++j) {
+            const uint64_t z = sh.rz[j];
+            if (j < s) lo += z;
+            Z += z;
+        }
+        if (Z == 0) {
+            if (!p_only) {  // no residual mass after rounding: from p
+                attempt = 1;
+                continue;
+            }
+            mine = s == 0;
+            rec = make_rec(kRecBadRow, 0);
+            break;
+        }
+        uint64_t c = static_cast<uint64_t>(double(u_res) * double(Z));
+        if (c >= Z) c = Z - 1;
+        if (c < lo || c - lo >= sh.rz[s]) break;  // another segment holds it
+        mine = true;
+        locate_cell<NW>(CPT * NW, sh.tot, 0.0f, static_cast<long long>(c - lo), &sh.draw);
+        const int nstar = sh.draw.cell_round;
+        if (wid == sh.draw.cell_wave) {
+            chunk_t tc = tv[0], dc = dv[0];
+#pragma unroll
+            for (int n = 1; n < CPT; ++n)
+                if (n == nstar) {
+                    tc = tv[n];
+                    dc = dv[n];
+                }
+            float m[EPC], sum = 0.0f;
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) {
+                m[e] = mass(tc, dc, e);
+                sum = sum + m[e];
+            }
+            const int at = walk_chunk<kFixedShift, W, EPC>(m, sum, sh.draw.target, s * CPT + nstar);
+            if (at >= 0) sh.tok = RowCut<Fmt>(V).token(at);
+        }
+        __syncthreads();
+        rec = sh.tok >= 0 ? make_rec(bonus ? kRecBonus : kRecReject, uint32_t(sh.tok)) : make_rec(kRecBadRow, 0);
+        break;
+    }
+    // This segment has read all it needs; the last one clears the row's words.
+    if (wid == 0) {
+        uint32_t prev = 0;
+        if (lane == 0) {
+            wait_memory();  // its own words are in place before they may be cleared
+            prev = __hip_atomic_fetch_add(&row->arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (mine) publish(a, b, i, kb, rec);
+        if (__builtin_amdgcn_readfirstlane(int(prev)) == nseg - 1) {
+            uint64_t* words = reinterpret_cast<uint64_t*>(row);
+            if (lane < int(sizeof(SplitRow) / 8)) store_word(words + lane, 0ull);
+        }
+    }
+}
+
 template <typename Fmt, int W, int CPT>
 hipError_t launch_tile(const VerifyLaunch& L, const VerifyArgs& a) {
     const dim3 grid(unsigned(L.B) * unsigned(L.K + 1)), block(W);
     return launch_kernel(&verify_kernel<Fmt, W, CPT, true, false>, grid, block, 0, L.stream, a);
+}
+
+// kSplitPolls, or the value of OSD_VERIFY_POLLS (read once; 0 makes every
+// workgroup compute its siblings' records itself).
+int verify_polls() {
+    static const int v = [] {
+        const char* e = getenv("OSD_VERIFY_POLLS");
+        if (e == nullptr || *e == 0) return kSplitPolls;
+        const int k = atoi(e);
+        return k < 0 ? kSplitPolls : (k > 65536 ? 65536 : k);
+    }();
+    return v;
+}
+
+template <typename Fmt, int W, int CPT>
+hipError_t launch_split(const VerifyLaunch& L, const VerifyArgs& a, int nchunks) {
+    SplitVerifyArgs sa;
+    sa.v = a;
+    sa.rows = L.seg_stats;
+    sa.nseg = (nchunks + W * CPT - 1) / (W * CPT);
+    sa.polls = verify_polls();
+    const int64_t grid = int64_t(L.B) * (L.K + 1) * sa.nseg;
+    if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    return launch_kernel(&verify_split_kernel<Fmt, W, CPT>, dim3(unsigned(grid)), dim3(W), 0, L.stream, sa);
 }
 
 template <typename Fmt>
@@ -604,19 +1017,32 @@ hipError_t launch_fmt(const VerifyLaunch& L, const VerifyArgs& a) {
                    : launch_kernel(&verify_kernel<Fmt, 256, 1, false, false>, grid, dim3(256), 0, L.stream, a);
     }
     if (!(L.temperature > 0.0f)) return hipErrorInvalidValue;  // the segmented greedy kernels take these
-    RowTile t;
-    if (!pick_tile(L.V, Fmt::kPerChunk, &t)) {
-        if (L.V > max_vocab_for(Fmt::kPerChunk)) return hipErrorInvalidValue;
-        // Rows longer than the largest resident tile: streamed.
-        return launch_kernel(&verify_long_kernel<Fmt>, grid, dim3(kLongW), 0, L.stream, a);
+    if (L.V > max_vocab_for(Fmt::kPerChunk)) return hipErrorInvalidValue;
+    const int nchunks = (L.V + Fmt::kPerChunk - 1) / Fmt::kPerChunk;
+    const int64_t rows = int64_t(L.B) * (L.K + 1);
+    const bool resident = nchunks <= 512 * 8;
+    // Few rows are split: up to one per CU beyond the resident tiles (against
+    // the streaming kernel: 224 rows of V = 50257 bf16 23.4 and 31.1 us, 576 rows of
+    // V = 50304 39.7 and 38.5, 100 rows of V = 128256 25.1 and 48.7), one per two
+    // CUs where 4 to 8 chunks per thread would be held (128 rows of V = 32000 14.5
+    // and 15.4, 216 rows 19.3 and 16.0), one per eight CUs for 2 to 4 (32 rows of
+    // V = 9000 9.7 and 10.5, 96 rows of V = 16000 12.3 and 11.0).
+    const int most = !resident ? L.cus : nchunks > 2048 ? L.cus / 2 : nchunks > 1024 ? L.cus / 8 : 0;
+    if (rows <= most) {
+        if (nchunks <= kMaxSplit * 256) return launch_split<Fmt, 256, 1>(L, a, nchunks);
+        if (nchunks <= kMaxSplit * 512) return launch_split<Fmt, 256, 2>(L, a, nchunks);
+        if (nchunks <= kMaxSplit * 1024) return launch_split<Fmt, 256, 4>(L, a, nchunks);
+        return launch_split<Fmt, 512, 4>(L, a, nchunks);
     }
+    if (!resident) return launch_kernel(&verify_stream_kernel<Fmt, kStreamW>, grid, dim3(kStreamW), 0, L.stream, a);
+    RowTile t;
+    if (!pick_tile(L.V, Fmt::kPerChunk, &t)) return hipErrorInvalidValue;
     switch (t.W * 100 + t.CPT) {
         case 25601: return launch_tile<Fmt, 256, 1>(L, a);
         case 25602: return launch_tile<Fmt, 256, 2>(L, a);
         case 25604: return launch_tile<Fmt, 256, 4>(L, a);
         case 51204: return launch_tile<Fmt, 512, 4>(L, a);
         case 51208: return launch_tile<Fmt, 512, 8>(L, a);
-        case 102408: return launch_tile<Fmt, 1024, 8>(L, a);
         default: return hipErrorInvalidValue;
     }
 }

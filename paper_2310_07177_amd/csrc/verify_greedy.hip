@@ -73,8 +73,7 @@ __global__ __launch_bounds__(kW) void verify_greedy_stats(SegArgs a) {
     chunk_t xt[CPT];
 #pragma unroll
     for (int n = 0; n < CPT; ++n) xt[n] = load_off(trow, cut.off((s * CPT + n) * kW + tid));
-#pragma unroll
-    for (int n = 0; n < CPT; ++n) xt[n] = chunk_or_pad<Fmt, kW>(xt[n], s * CPT + n, cut);
+    pad_row_tail<Fmt, kW, CPT>(xt, cut, s * CPT);
     const int c0 = s * kW * CPT + tid;  // this thread's first chunk in the row
     // Within a thread indices grow with (n, e): a strict ">" keeps the first
     // maximum.
