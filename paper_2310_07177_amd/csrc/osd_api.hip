@@ -17,18 +17,17 @@ size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int per_chunk(int dtype) { return dtype == OSD_BF16 ? 8 : (dtype == OSD_F32 ? 4 : 0); }
 
-// Counters and records of the row-resident kernel, then the argmax partials
-// of the segmented greedy kernels.  Every call leaves all of it zero.
+// The fused kernel's records, then what the verification kernels keep per row
+// (the fused kernel: its decisions).  Every call leaves all of it zero.
 struct VerifyWs {
-    size_t records, counters, stats, total;
+    size_t records, rows, total;
 };
 VerifyWs verify_layout(int B, int K) {
     VerifyWs w;
     const size_t rows = size_t(B) * size_t(K + 1);
-    w.counters = 0;
     w.records = round_up(size_t(B) * 4, kAlign);
-    w.stats = w.records + round_up(rows * 4, kAlign);
-    w.total = w.stats + round_up(rows * osd::kMaxSeg * sizeof(osd::SegStats), kAlign);
+    w.rows = w.records + round_up(rows * 4, kAlign);
+    w.total = w.rows + round_up(rows * sizeof(osd::VerifyRow), kAlign);
     return w;
 }
 
@@ -53,7 +52,7 @@ DistillWs distill_layout(int B, int K) {
 
 // The fused entry points: the verify workspace, then the distill workspace
 // (both used as they are by the two-call path; the fused kernel keeps its
-// per-position decisions where the greedy partials go), then per-workgroup
+// per-position decisions where the verification's rows go), then per-workgroup
 // loss partials of the fused kernel (at most one per item; per-row losses in
 // the error-index mode), then a [B, K] mask for the error-index mode's
 // two-call path when the caller passes no reject_mask.
@@ -166,9 +165,7 @@ int osd_verify(const void* target_logits, const void* draft_logits, int dtype, i
     L.out_tokens = out_tokens;
     L.reject_mask = reject_mask;
     char* w = static_cast<char*>(workspace);
-    L.records = reinterpret_cast<uint32_t*>(w + ws.records);
-    L.counters = reinterpret_cast<uint32_t*>(w + ws.counters);
-    L.seg_stats = reinterpret_cast<osd::SegStats*>(w + ws.stats);
+    L.rows = reinterpret_cast<osd::VerifyRow*>(w + ws.rows);
     L.stream = static_cast<hipStream_t>(stream);
     L.cus = device_cus(L.stream);
     // Greedy: segmented kernels (balanced over every CU).  Sampling: kernels
@@ -311,7 +308,7 @@ int verify_distill_impl(const void* target_logits, const void* draft_logits, int
     L.grad_out = grad_out;
     const VerifyWs vw = verify_layout(B, K);
     L.records = reinterpret_cast<uint32_t*>(w + ws.verify + vw.records);
-    L.dec = reinterpret_cast<uint32_t*>(w + ws.verify + vw.stats);
+    L.dec = reinterpret_cast<uint32_t*>(w + ws.verify + vw.rows);
     L.erridx = erridx;
     L.done = reinterpret_cast<uint32_t*>(w + ws.distill + distill_layout(B, K).done);
     L.part_ws = reinterpret_cast<double*>(w + ws.part);
@@ -552,11 +549,12 @@ extern "C" int osd_verify_noalloc(const void* target_logits, const void* draft_l
     }
     void* ptr = scratch_on(dev);
     if (!ptr) return OSD_ERR_DEVICE;
-    // The counters and records must start at zero.  osd_verify's kernels
-    // leave them zero, but the array keeps whatever the previous call on this
-    // GPU left, so they are cleared here on the call's own stream.  (The
-    // greedy partials are written before they are read.)
-    if (launch_clear_words(static_cast<uint32_t*>(ptr), int(ws.stats / 4), s) != hipSuccess) return OSD_ERR_DEVICE;
+    // The rows' words must start at zero.  osd_verify's kernels leave them
+    // zero, but the array keeps whatever the previous call on this GPU left, so
+    // they are cleared here on the call's own stream.
+    if (launch_clear_words(reinterpret_cast<uint32_t*>(static_cast<char*>(ptr) + ws.rows),
+                           int((ws.total - ws.rows) / 4), s) != hipSuccess)
+        return OSD_ERR_DEVICE;
     return osd_verify(target_logits, draft_logits, dtype, B, K, V, draft_tokens, draft_len, u_accept, u_resample,
                       temperature, accepted_len, out_tokens, reject_mask, ptr, ws.total, stream);
 }

@@ -38,14 +38,21 @@ struct RowTile {
 // 64 VGPRs, and the spills that forces cost more than the occupancy gains.)
 constexpr int min_waves_per_simd(int W, int CPT) { return (void)W, (void)CPT, 4; }
 
-// Argmax partial of one vocabulary segment of a target row (segmented greedy
-// verification): (max, lowest index) in (kt, kd's bits).
-struct SegStats {
-    double st, sd;
-    float kt, kd;
-};
-// Segments per row in the segmented greedy kernels (at most).
+// Segments per row in the segmented greedy kernel (at most).
 constexpr int kMaxSeg = 16;
+
+// What the verification kernels keep in the workspace for one row of one
+// sequence, zero between calls.  Every row has cache lines of its own: the
+// device-wide atomics on one line are served one after another (about 10 ns
+// each), whatever the word, so words of different sequences side by side wait
+// for each other.
+struct VerifyRow {
+    uint64_t words[41];  // split rows: statistics and masses by segment; greedy: argmaxes by segment
+    uint32_t record;     // the row's outcome
+    uint32_t arrivals;   // (row 0) arrivals of the sequence
+    uint32_t pad[12];
+};
+static_assert(sizeof(VerifyRow) == 384, "three cache lines");
 
 struct VerifyLaunch {
     const void* target;
@@ -60,9 +67,7 @@ struct VerifyLaunch {
     int32_t* accepted_len;
     int32_t* out_tokens;
     uint8_t* reject_mask;
-    uint32_t* records;   // [B*(K+1)] zero on entry and exit
-    uint32_t* counters;  // [B]       zero on entry and exit
-    SegStats* seg_stats;  // [B*(K+1)*kMaxSeg] greedy argmax partials or split rows' words, zero on entry and exit
+    VerifyRow* rows;  // [B*(K+1)] zero on entry and exit
     int cus;
     hipStream_t stream;
 };

@@ -82,8 +82,7 @@ struct VerifyArgs {
     int32_t* accepted_len;
     int32_t* out_tokens;
     uint8_t* reject_mask;
-    uint32_t* records;
-    uint32_t* counters;
+    VerifyRow* rows;
 };
 
 __device__ void write_invalid(const VerifyArgs& a, int b) {
@@ -101,11 +100,11 @@ __device__ void write_invalid(const VerifyArgs& a, int b) {
 __device__ void publish(const VerifyArgs& a, int b, int i, int kb, uint32_t record) {
     const int K = a.K;
     const int lane = threadIdx.x & (kWave - 1);
-    uint32_t* recs = a.records + int64_t(b) * (K + 1);
+    VerifyRow* rows = a.rows + int64_t(b) * (K + 1);
     uint32_t prev = 0;
     if (lane == 0) {  // one round trip: the arrival does not wait for the record
-        __hip_atomic_exchange(&recs[i], record, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        prev = __hip_atomic_fetch_add(&a.counters[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_exchange(&rows[i].record, record, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        prev = __hip_atomic_fetch_add(&rows[0].arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     prev = __shfl(prev, 0, kWave);
     if (prev != uint32_t(kb)) return;
@@ -114,13 +113,13 @@ __device__ void publish(const VerifyArgs& a, int b, int i, int kb, uint32_t reco
     // on their way, then clear them.
     uint32_t r = lane == i ? record : 0u;
     for (int p = 0; p < kRecordPolls; ++p) {
-        if (lane <= kb && lane != i) r = load_relaxed(&recs[lane]);
+        if (lane <= kb && lane != i) r = load_relaxed(&rows[lane].record);
         const uint32_t s = rec_state(r);
         if (__ballot(lane <= kb && (s == kRecEmpty || s == kRecRejectPending)) == 0) break;
         __builtin_amdgcn_s_sleep(1);
     }
     wait_memory();  // this workgroup's own record is in place before it is cleared
-    if (lane <= kb) __hip_atomic_store(&recs[lane], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane <= kb) __hip_atomic_store(&rows[lane].record, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // First rejection (Appendix A.1: the test stops there).  A proposal
     // outside the vocabulary invalidates the sequence wherever it sits; a row
@@ -150,7 +149,7 @@ __device__ void publish(const VerifyArgs& a, int b, int i, int kb, uint32_t reco
     }
     if (lane == 0) {
         a.accepted_len[b] = bad ? -1 : acc;
-        __hip_atomic_store(&a.counters[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&rows[0].arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -159,9 +158,9 @@ __device__ void publish(const VerifyArgs& a, int b, int i, int kb, uint32_t reco
 // accepted, 0 if still undecided after `polls` looks.
 __device__ int poll_earlier(const VerifyArgs& a, int b, int i, int polls) {
     const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t* recs = a.records + int64_t(b) * (a.K + 1);
+    const VerifyRow* rows = a.rows + int64_t(b) * (a.K + 1);
     for (int p = 0;; ++p) {
-        const uint32_t s = lane < i ? rec_state(load_relaxed(&recs[lane])) : uint32_t(kRecAccept);
+        const uint32_t s = lane < i ? rec_state(load_relaxed(&rows[lane].record)) : uint32_t(kRecAccept);
         if (__ballot(rejects(s)) != 0) return 2;
         if (__ballot(s != kRecAccept) == 0) return 1;
         if (p + 1 >= polls) return 0;
@@ -363,7 +362,7 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void verify_kernel(V
                     // Announce the rejection, then find out whether it is the
                     // first one of the sequence.
                     if (lane == 0)
-                        publish_u32(a.records + int64_t(b) * (K + 1) + i, make_rec(kRecRejectPending, 0));
+                        publish_u32(&a.rows[int64_t(b) * (K + 1) + i].record, make_rec(kRecRejectPending, 0));
                     if (i > 0 && poll_earlier(a, b, i, kMaxPolls) == 2) {
                         flag = 0;
                         publish(a, b, i, kb, make_rec(kRecRejectSkipped, 0));
@@ -549,7 +548,7 @@ __global__ __launch_bounds__(W, 1) void verify_stream_kernel(VerifyArgs a) {
                 flag = 0;
                 publish(a, b, i, kb, make_rec(kRecAccept, 0));
             } else {
-                if (lane == 0) publish_u32(a.records + int64_t(b) * (K + 1) + i, make_rec(kRecRejectPending, 0));
+                if (lane == 0) publish_u32(&a.rows[int64_t(b) * (K + 1) + i].record, make_rec(kRecRejectPending, 0));
                 if (i > 0 && poll_earlier(a, b, i, kMaxStreamPolls) == 2) {
                     flag = 0;
                     publish(a, b, i, kb, make_rec(kRecRejectSkipped, 0));
@@ -623,18 +622,17 @@ __global__ __launch_bounds__(W, 1) void verify_stream_kernel(VerifyArgs a) {
 constexpr int kMaxSplit = 8;
 constexpr int kSplitPolls = 256;
 
-// A row's words in the workspace (in the place of its kMaxSeg argmax partials).
+// A row's words in the workspace (VerifyRow::words).
 struct SplitRow {
     uint64_t stats[kMaxSplit][3];  // ~S_t, ~S_d, ~(K_t | K_d << 32) (bits)
     uint64_t mass[2][kMaxSplit];   // 2^63 | mass: of the residual, of p
     uint32_t arrivals;
     uint32_t bonus;                // a bonus row: 1 read it, 2 skip it
 };
-static_assert(sizeof(SplitRow) <= kMaxSeg * sizeof(SegStats), "a row's words fit its partials");
+static_assert(sizeof(SplitRow) == sizeof(VerifyRow::words), "the row's words");
 
 struct SplitVerifyArgs {
     VerifyArgs v;
-    SegStats* rows;  // [B*(K+1)] SplitRow, kMaxSeg partials apart; zero on entry and exit
     int nseg;
     int polls;
 };
@@ -786,7 +784,7 @@ __global__ __launch_bounds__(W, Fmt::kPerChunk == 8 ? 6 : 5) void verify_split_k
         if (s == 0 && wid == 0) publish(a, b, i, kb, make_rec(kRecBadToken, 0));
         return;
     }
-    SplitRow* const row = reinterpret_cast<SplitRow*>(sa.rows + (int64_t(b) * (K + 1) + i) * kMaxSeg);
+    SplitRow* const row = reinterpret_cast<SplitRow*>(a.rows[int64_t(b) * (K + 1) + i].words);
     if (bonus) {
         // The first segment to look decides for all of them.
         if (wid == 0) {
@@ -1000,7 +998,6 @@ template <typename Fmt, int W, int CPT>
 hipError_t launch_split(const VerifyLaunch& L, const VerifyArgs& a, int nchunks) {
     SplitVerifyArgs sa;
     sa.v = a;
-    sa.rows = L.seg_stats;
     sa.nseg = (nchunks + W * CPT - 1) / (W * CPT);
     sa.polls = verify_polls();
     const int64_t grid = int64_t(L.B) * (L.K + 1) * sa.nseg;
@@ -1083,8 +1080,7 @@ hipError_t launch_verify(const VerifyLaunch& L) {
     a.accepted_len = L.accepted_len;
     a.out_tokens = L.out_tokens;
     a.reject_mask = L.reject_mask;
-    a.records = L.records;
-    a.counters = L.counters;
+    a.rows = L.rows;
     return L.dtype == 1 ? launch_fmt<BF16>(L, a) : launch_fmt<F32>(L, a);
 }
 

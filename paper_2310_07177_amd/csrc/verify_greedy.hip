@@ -7,14 +7,16 @@
 // a, or of the bonus row k_b when every proposal matched.  Only target rows
 // are read.
 //
-// Work layout: two flat grids of small workgroups, so the hardware
-// dispatcher balances the work over every CU whatever B and k are.
-//  1. verify_greedy_stats -- one workgroup per (target row, vocabulary
-//     segment of kW*4 chunks): the segment's (max, lowest index) partial.
-//     This kernel moves every byte the method reads.
-//  2. verify_greedy_decide -- one workgroup per sequence: stages the
-//     partials of rows 0..k_b in LDS, merges them in segment order, finds the
-//     first mismatch and writes the outputs, then zeroes the partials.
+// Work layout: one flat grid of small workgroups, one per (target row, vocabulary
+// segment of kW*4 chunks), so the hardware dispatcher balances the work over every
+// CU whatever B and k are.  Each posts its segment's (max, lowest index) as one
+// word and arrives at its sequence's counter without waiting for the word; the
+// last of a sequence to arrive merges the words of rows 0..k_b in segment order,
+// finds the first mismatch, writes the outputs and clears words and counter.
+// (The decision in a kernel of its own took B = 1, K = 4, V = 32000 bf16 5.2 us and
+// B = 8, K = 5 6.0, this one 4.7 and 5.3; larger batches are bound by the read: B = 64,
+// K = 8, V = 32128 10.8.  With the counters of all sequences side by side the same
+// batch took 22.1 us: see VerifyRow.)
 #include "osd.h"
 #include "osd_device.hpp"
 #include "osd_internal.hpp"
@@ -35,7 +37,7 @@ struct SegArgs {
     const int32_t* draft_len;  // [B] or null
     int nseg;                  // segments per row
     int64_t first;             // first work unit of this launch
-    SegStats* stats;           // [B*(K+1), kMaxSeg] argmax partials, zero between calls
+    VerifyRow* rows;           // [B*(K+1)], zero between calls
     int32_t* accepted_len;
     int32_t* out_tokens;
     uint8_t* reject_mask;
@@ -47,15 +49,40 @@ __device__ inline int seq_k(const SegArgs& a, int b) { return a.draft_len ? scal
 // would cost a round trip to the argument buffer (about a microsecond).
 __device__ inline void request_args(const SegArgs& a) {
     asm volatile("" ::"s"(a.target), "s"(a.B), "s"(a.K), "s"(a.V), "s"(a.tokens), "s"(a.draft_len), "s"(a.nseg),
-                 "s"(a.first), "s"(a.stats));
+                 "s"(a.first), "s"(a.rows));
     asm volatile("" ::"s"(a.accepted_len), "s"(a.out_tokens), "s"(a.reject_mask));
 }
 
+// Outputs of sequence b, written by wave 0 (lane j handles position j; K < 64).
+__device__ inline void write_outputs(const SegArgs& a, int b, int kb, int acc, bool bad, int extra) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int K = a.K;
+    if (lane <= K) {
+        int32_t o = -1;
+        if (!bad) o = lane < acc ? a.tokens[int64_t(b) * K + lane] : (lane == acc ? extra : -1);
+        a.out_tokens[int64_t(b) * (K + 1) + lane] = o;
+        if (a.reject_mask && lane < K)
+            a.reject_mask[int64_t(b) * K + lane] = (!bad && lane == acc && acc < kb) ? 1 : 0;
+    }
+    if (lane == 0) a.accepted_len[b] = bad ? -1 : acc;
+}
+
+// A segment's argmax as one word: larger for a larger value, then for a lower
+// index; never zero (a segment without finite logits: -inf).
+__device__ inline uint64_t argmax_word(float v, int idx) {
+    return (uint64_t(float_key(v)) << 32) | (0xFFFFFFFFu - uint32_t(idx));
+}
+
+// Polls of the last arriver for words that were posted before it arrived.
+constexpr int kWordPolls = 4096;
+
 template <typename Fmt, int CPT>
-__global__ __launch_bounds__(kW) void verify_greedy_stats(SegArgs a) {
+__global__ __launch_bounds__(kW) void verify_greedy_kernel(SegArgs a) {
     constexpr int EPC = Fmt::kPerChunk;
     __shared__ float s_k[kNW];
     __shared__ int s_i[kNW];
+    __shared__ int s_last;
+    __shared__ unsigned long long s_row[OSD_MAX_K + 1][kMaxSeg];
 
     request_args(a);
     const int tid = threadIdx.x;
@@ -65,7 +92,11 @@ __global__ __launch_bounds__(kW) void verify_greedy_stats(SegArgs a) {
     const int b = int(pair / (a.K + 1));
     const int i = int(pair - int64_t(b) * (a.K + 1));
     const int kb = seq_k(a, b);
-    if (kb < 1 || kb > a.K || i > kb) return;  // invalid k_b (reported later) or a padding row
+    if (kb < 1 || kb > a.K) {
+        if (i == 0 && s == 0 && tid < kWave) write_outputs(a, b, kb, 0, true, -1);
+        return;
+    }
+    if (i > kb) return;  // a padding row
 
     const char* trow = static_cast<const char*>(a.target) + pair * int64_t(a.V) * Fmt::kBytes;
     // Segment s holds rounds s*CPT .. s*CPT + CPT - 1 of the row.
@@ -104,105 +135,64 @@ __global__ __launch_bounds__(kW) void verify_greedy_stats(SegArgs a) {
                 bv = s_k[w];
                 bx = s_i[w];
             }
-        SegStats r;
-        r.st = 0.0;
-        r.sd = 0.0;
-        r.kt = bv;
-        r.kd = __int_as_float(bx == 0x7FFFFFFF ? bx : cut.token(bx));
-        a.stats[pair * kMaxSeg + s] = r;
-    }
-}
-
-
-// Outputs of sequence b, written by wave 0 (lane j handles position j; K < 64).
-__device__ inline void write_outputs(const SegArgs& a, int b, int kb, int acc, bool bad, int extra) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int K = a.K;
-    if (lane <= K) {
-        int32_t o = -1;
-        if (!bad) o = lane < acc ? a.tokens[int64_t(b) * K + lane] : (lane == acc ? extra : -1);
-        a.out_tokens[int64_t(b) * (K + 1) + lane] = o;
-        if (a.reject_mask && lane < K)
-            a.reject_mask[int64_t(b) * K + lane] = (!bad && lane == acc && acc < kb) ? 1 : 0;
-    }
-    if (lane == 0) a.accepted_len[b] = bad ? -1 : acc;
-}
-
-// Zero the argmax partials of sequence b (lane i: row i), once nothing reads
-// them any more.
-__device__ inline void clear_stats(const SegArgs& a, int b, int kb) {
-    const int i = threadIdx.x & (kWave - 1);
-    if (kb < 1 || kb > a.K || i > kb) return;
-    const int64_t pi = int64_t(b) * (a.K + 1) + i;
-    SegStats z;
-    z.st = 0.0;
-    z.sd = 0.0;
-    z.kt = 0.0f;
-    z.kd = 0.0f;
-    for (int s = 0; s < a.nseg; ++s) a.stats[pi * kMaxSeg + s] = z;
-}
-
-// Greedy decision: merge the argmax partials of rows 0..k_b (lowest index on
-// ties), accept while y_i equals the argmax, emit the argmax where the test
-// stops.
-template <typename Fmt>
-__global__ __launch_bounds__(kW) void verify_greedy_decide(SegArgs a) {
-    __shared__ SegStats s_st[(OSD_MAX_K + 1) * kMaxSeg];
-    request_args(a);
-    const int tid = threadIdx.x;
-    const int b = int(a.first + blockIdx.x);
-    const int K = a.K;
-    const int kb = seq_k(a, b);
-    {
-        const SegStats* st = a.stats + int64_t(b) * (K + 1) * kMaxSeg;
-        for (int j = tid; j < (K + 1) * kMaxSeg; j += kW)
-            if ((j % kMaxSeg) < a.nseg) s_st[j] = st[j];
+        const uint64_t word = argmax_word(bv, bx == 0x7FFFFFFF ? bx : cut.token(bx));
+        __hip_atomic_store(&a.rows[pair].words[s], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t prev = __hip_atomic_fetch_add(&a.rows[int64_t(b) * (a.K + 1)].arrivals, 1u, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+        s_last = prev == uint32_t((kb + 1) * a.nseg - 1);
     }
     __syncthreads();
-    if (tid >= kWave) return;
-    const int lane = tid;
-    const bool kb_ok = kb >= 1 && kb <= K;
-    const int i = lane;
-    float best = kNegInf;
-    int g = 0x7FFFFFFF;
-    if (kb_ok && i <= kb) {
-        const SegStats* st = s_st + i * kMaxSeg;
-        for (int s = 0; s < a.nseg; ++s) {
-            const float v = st[s].kt;
-            const int x = __float_as_int(st[s].kd);
-            if (v > best) {  // segments hold increasing indices
-                best = v;
-                g = x;
-            }
-        }
+    if (!s_last) return;
+
+    // The sequence's last arriver: every word is posted; wait (bounded) for those
+    // still on their way, then clear them.
+    VerifyRow* rows = a.rows + int64_t(b) * (a.K + 1);
+    for (int j = tid; j < (kb + 1) * a.nseg; j += kW) {
+        const int r = j / a.nseg, q = j - r * a.nseg;
+        uint64_t v = 0;
+        for (int p = 0; p < kWordPolls && v == 0; ++p) v = poll_u64(&rows[r].words[q]);
+        s_row[r][q] = v;
     }
-    clear_stats(a, b, kb);  // this workgroup is the only reader
-    const bool bad_row = !(best > kNegInf) || best == -kNegInf;
-    int y = 0;
-    if (kb_ok && i < kb) y = a.tokens[int64_t(b) * K + i];
-    const uint64_t tok_bad = __ballot(kb_ok && i < kb && (y < 0 || y >= a.V));
-    const uint64_t stop = __ballot(kb_ok && i < kb && (bad_row || y != g));
-    const int acc = stop ? __builtin_ctzll(stop) : (kb_ok ? kb : 0);
-    const uint64_t row_bad = __ballot(kb_ok && i <= kb && bad_row);
-    const bool bad = !kb_ok || tok_bad != 0 || ((row_bad >> acc) & 1ull) != 0;
-    const int extra = __shfl(g, acc, kWave);
-    write_outputs(a, b, kb, acc, bad, extra);
+    wait_memory();  // this workgroup's own word is in place before it is cleared
+    __syncthreads();
+    for (int j = tid; j < (kb + 1) * a.nseg; j += kW) {
+        const int r = j / a.nseg, q = j - r * a.nseg;
+        __hip_atomic_store(&rows[r].words[q], uint64_t(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (tid == 0) __hip_atomic_store(&rows[0].arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid >= kWave) return;
+    // Lane r: row r's argmax (lowest index on ties); accept while y_r equals it,
+    // emit the argmax where the test stops.
+    uint64_t w = 0;
+    if (lane <= kb)
+        for (int q = 0; q < a.nseg; ++q) {
+            const uint64_t v = s_row[lane][q];
+            if (v > w) w = v;
+        }
+    const float top = key_float(uint32_t(w >> 32));
+    const int g = int(0xFFFFFFFFu - uint32_t(w));
+    const bool bad_row = !(top > kNegInf && top < -kNegInf);
+    const int y = lane < kb ? a.tokens[int64_t(b) * a.K + lane] : 0;
+    const uint64_t tok_bad = __ballot(lane < kb && (y < 0 || y >= a.V));
+    const uint64_t stop = __ballot(lane < kb && (bad_row || y != g));
+    const int acc = stop ? __builtin_ctzll(stop) : kb;
+    const uint64_t row_bad = __ballot(lane <= kb && bad_row);
+    const bool bad = tok_bad != 0 || ((row_bad >> acc) & 1ull) != 0;
+    write_outputs(a, b, kb, acc, bad, __shfl(g, acc, kWave));
 }
 
 template <typename Fmt>
 hipError_t launch_fmt(const VerifyLaunch& L, SegArgs a) {
     if (!greedy_segments(L.V, Fmt::kPerChunk, &a.nseg)) return hipErrorInvalidValue;
+    // Twice the chunks per thread beyond 8 segments (the sequence's arrivals
+    // meet at one word).
+    const auto kernel = a.nseg > 8 ? &verify_greedy_kernel<Fmt, 8> : &verify_greedy_kernel<Fmt, 4>;
+    if (a.nseg > 8) a.nseg = (a.nseg + 1) / 2;
     const int64_t units = int64_t(a.B) * (a.K + 1) * a.nseg;
     for (int64_t f = 0; f < units; f += kMaxGrid) {
         a.first = f;
         const unsigned g = unsigned(units - f < kMaxGrid ? units - f : kMaxGrid);
-        const hipError_t e = launch_kernel(&verify_greedy_stats<Fmt, 4>, dim3(g), dim3(kW), 0, L.stream, a);
-        if (e != hipSuccess) return e;
-    }
-    for (int64_t f = 0; f < a.B; f += kMaxGrid) {
-        a.first = f;
-        const unsigned g = unsigned(a.B - f < kMaxGrid ? a.B - f : kMaxGrid);
-        const hipError_t e = launch_kernel(&verify_greedy_decide<Fmt>, dim3(g), dim3(kW), 0, L.stream, a);
+        const hipError_t e = launch_kernel(kernel, dim3(g), dim3(kW), 0, L.stream, a);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -230,7 +220,7 @@ hipError_t launch_verify_greedy(const VerifyLaunch& L) {
     a.tokens = L.tokens;
     a.draft_len = L.draft_len;
     a.first = 0;
-    a.stats = L.seg_stats;
+    a.rows = L.rows;
     a.accepted_len = L.accepted_len;
     a.out_tokens = L.out_tokens;
     a.reject_mask = L.reject_mask;
