@@ -324,26 +324,8 @@ __device__ inline void seg_stats(const SegCache<Fmt>& c, SegShared& sh, int slot
 
 // The segment's divergence partials from its cache (which it turns into the
 // gradient's terms), reduced over the workgroup into slot `slot` of sh.pa.
-struct SegScales {
-    PairScales k;
-    float at, as;
-};
-template <typename Fmt>
-__device__ inline SegScales seg_scales(const SegCache<Fmt>& c, const RowPair& rp, float beta) {
-    SegScales z;
-    const float ct = float(double(rp.kt - c.kt) + rp.lt), cs = float(double(rp.ks - c.ks) + rp.ls);
-    const int nt = int(fmaxf(c.kt - rp.kt, -2048.0f)), ns = int(fmaxf(c.ks - rp.ks, -2048.0f));
-    // A thread without mass in a row has scale 0 there (its own shift may lie
-    // far above the row's), and any positive ratio serves its zeros.
-    const bool none = c.St == 0.0 || c.Ss == 0.0;
-    z.at = c.St == 0.0 ? 0.0f : float(__builtin_ldexp(rp.ist, nt));
-    z.as = c.Ss == 0.0 ? 0.0f : float(__builtin_ldexp(rp.iss, ns));
-    z.k = PairScales{none ? 1.0f : float(__builtin_ldexp(rp.st * rp.iss, ns - nt)), beta, 1.0f - beta, ct, cs,
-                     float(rp.dtd - double(c.kt - c.ks))};
-    return z;
-}
 template <typename Fmt, int KIND>
-__device__ inline void seg_partial(SegCache<Fmt>& c, const SegScales& z, SegShared& sh, int slot) {
+__device__ inline void seg_partial(SegCache<Fmt>& c, const RowScales& z, SegShared& sh, int slot) {
     constexpr int EPC = Fmt::kPerChunk;
     const int tid = opaque_tid(), lane = tid & (kWave - 1), wid = tid / kWave;
     float acc0 = 0.0f, acc1 = 0.0f;
@@ -409,7 +391,7 @@ __device__ inline double row_divergence(const SegShared& sh, float beta) {
 }
 
 template <typename Fmt, int KIND>
-__device__ inline void seg_grad(const SegCache<Fmt>& c, const SegScales& z, const DistillArgs& a, float shift, void* grow,
+__device__ inline void seg_grad(const SegCache<Fmt>& c, const RowScales& z, const DistillArgs& a, float shift, void* grow,
                                 int s, const RowCut<Fmt>& cut) {
     constexpr int EPC = Fmt::kPerChunk;
     const float ln2 = float(kLn2);
@@ -540,7 +522,7 @@ __global__ __launch_bounds__(kSegW, 4) void split_row_kernel(SplitArgs sa) {
     const RowPair rp = sh.row;
 
     // 2. divergence
-    SegScales z = seg_scales<Fmt>(c, rp, a.beta);
+    RowScales z = row_scales(rp, c.kt, c.St == 0.0, c.ks, c.Ss == 0.0, a.beta);
     seg_partial<Fmt, KIND>(c, z, sh, s);
     uint32_t prev = 0;
     if constexpr (KIND == 0) {
@@ -577,11 +559,11 @@ __global__ __launch_bounds__(kSegW, 4) void split_row_kernel(SplitArgs sa) {
             for (int j = 0; j < nseg; ++j) {
                 if (j == s) continue;
                 seg_build<Fmt, KIND>(c, trow, srow, j, V, c2);
-                z = seg_scales<Fmt>(c, rp, a.beta);
+                z = row_scales(rp, c.kt, c.St == 0.0, c.ks, c.Ss == 0.0, a.beta);
                 seg_partial<Fmt, KIND>(c, z, sh, j);
             }
             seg_build<Fmt, KIND>(c, trow, srow, s, V, c2);
-            z = seg_scales<Fmt>(c, rp, a.beta);
+            z = row_scales(rp, c.kt, c.St == 0.0, c.ks, c.Ss == 0.0, a.beta);
             seg_partial<Fmt, KIND>(c, z, sh, s);
             if (wid == 0) merge_partials(sh, nseg);
             __syncthreads();

@@ -121,6 +121,26 @@ struct RowPair {
     double st, ss, dtd, ist, iss, lt, ls;
 };
 
+// A thread's scales for a row pair, from its shifts kt, ks in the rows and whether
+// its sums are empty: at, as are 2^(k - K) / S, what an exponential of the thread
+// times is its probability.
+struct RowScales {
+    PairScales k;
+    float at, as;
+};
+__device__ inline RowScales row_scales(const RowPair& rp, float kt, bool none_t, float ks, bool none_s, float beta) {
+    RowScales z;
+    const float ct = float(double(rp.kt - kt) + rp.lt), cs = float(double(rp.ks - ks) + rp.ls);
+    const int nt = int(fmaxf(kt - rp.kt, -2048.0f)), ns = int(fmaxf(ks - rp.ks, -2048.0f));
+    // A thread without mass in a row has scale 0 there (its own shift may lie
+    // far above the row's), and any positive ratio serves its zeros.
+    z.at = none_t ? 0.0f : float(__builtin_ldexp(rp.ist, nt));
+    z.as = none_s ? 0.0f : float(__builtin_ldexp(rp.iss, ns));
+    z.k = PairScales{none_t || none_s ? 1.0f : float(__builtin_ldexp(rp.st * rp.iss, ns - nt)), beta, 1.0f - beta, ct, cs,
+                     float(rp.dtd - double(kt - ks))};
+    return z;
+}
+
 // Wave 0: merge the (K, S) pairs that lanes 0..15 hold (identity elsewhere) of
 // both rows and store the row values.
 __device__ inline void store_row_pair(float k0, double t0, float k1, double t1, int lane, RowPair* s_r) {

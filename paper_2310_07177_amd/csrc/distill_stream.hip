@@ -10,7 +10,13 @@
 //        with m = beta p + (1-beta) q
 // and 0 log 0 = 0.  Rows with mask 0 get D = 0 and a zero gradient row.
 //
-// Work layout.  About one workgroup per CU walks the rows n = g, g+G, ...
+// Work layout.  About one workgroup per CU walks rows g, g+G, ... or, with a
+// mask, its equal share of the rows that are on (share_rows), each step loading
+// the next of them; the zero gradient rows are written between the passes of a
+// step.  (With every row g, g+G, ... whatever its mask, a workgroup's share of the
+// rows that are on varied by a third and a row that was off left nothing in flight
+// under the row before it: 16384 rows of V = 32000 bf16, 40 % on, JSD, took 459 us,
+// now 378.)
 // Each thread owns chunks n*W + tid of both rows.  The statistics pass
 // consumes the raw chunks of row j while each register chunk is reloaded with
 // the same chunk of row j+G; what the later passes need is kept per element in
@@ -18,7 +24,7 @@
 // registers), so the loss and gradient passes of row j run while row j+G is
 // landing.  The statistics pass caches both exponents, (t c2 - K_t,
 // s c2 - K_s), for every kind; the loss pass replaces them by
-//   JSD  (log2 q - log2 m, q)
+//   JSD  (log2 q - log2 m, 2^(s c2 - K_s))
 //   FKL  (p, log2 q)
 //   RKL  (log2 p - log2 q, q)
 // (c2 = log2(e)/tau, K a whole number per thread and row).  The log-ratio of
@@ -26,7 +32,7 @@
 // difference of the normalisers (taken in fp64), so it carries no rounding
 // of the (much larger) normalisers themselves.
 //
-// Each workgroup adds the D of its rows in fp64 in row order and posts the
+// Each workgroup adds the D of its rows in fp64 in the order it takes them and posts the
 // partial at the device-wide coherence point; the last workgroup to finish
 // adds the partials in workgroup order, so the loss is reproducible for a
 // given grid.
@@ -55,7 +61,8 @@ struct StreamDistillArgs {
     float* loss_out;    // {masked mean, masked sum}
     int nrows;
     uint32_t row_bytes;
-    int G;  // workgroups in the grid
+    int G;          // workgroups in the grid
+    int slice, gs;  // rows and workgroups of a slice: shares are made inside a slice
 };
 
 struct Row {
@@ -64,23 +71,89 @@ struct Row {
     const char* srow;
 };
 
-// Row n, with its mask flag `on` (rows out of range are off).
+// Row n (none if n < 0).
 template <typename Fmt>
-__device__ inline Row decode_row(const StreamDistillArgs& a, int n, bool on) {
+__device__ inline Row decode_row(const StreamDistillArgs& a, int n) {
     Row r;
-    r.on = false;
+    r.on = n >= 0;
     r.trow = nullptr;
     r.srow = nullptr;
-    if (n < 0 || n >= a.nrows) return r;
-    r.on = on;
+    if (n < 0) return r;
     const int b = n / a.K, i = n - b * a.K;
     r.trow = static_cast<const char*>(a.teacher) + (int64_t(b) * a.tstride + int64_t(i) * a.V) * Fmt::kBytes;
     r.srow = static_cast<const char*>(a.student) + (int64_t(b) * a.sstride + int64_t(i) * a.V) * Fmt::kBytes;
     return r;
 }
 
+// The place of the n-th set bit.
+__device__ inline int nth_bit(uint32_t bits, int n) {
+    for (; n > 0; --n) bits &= bits - 1u;
+    return __builtin_ctz(bits);
+}
+
+// A workgroup's share of its slice: rows that are on, rows that are off.
+struct RowShare {
+    int on, off;
+};
+// Rows of a slice per thread: one 16-byte load of mask flags.
+constexpr int kFlags = 16;
+// Places in a workgroup's list of rows (the launch keeps a share below W * 17 / 16 + 4).
+template <int W>
+constexpr int kShareMax = W + W / 8 + 8;
+
+// Divides a slice of `rows` rows from row `base` among its G workgroups:
+// those that are on round robin, and those that are off, so no two workgroups
+// differ by more than one of either.  s_list receives workgroup l's
+// rows on from the front and its rows off from the back.  Ends with a barrier.
+template <int W>
+__device__ inline RowShare share_rows(const uint8_t* mask, int base, int rows, int G, int l, int* s_list,
+                                     uint64_t* s_cnt) {
+    constexpr int NW = W / kWave;
+    const int tid = opaque_tid(), lane = tid & (kWave - 1), wid = tid / kWave;
+    const int at = kFlags * tid;
+    // The last 16 flags are moved back to end with the slice (in a slice of
+    // fewer, to before its start: the launch has more rows than that).
+    const int off = at < rows - kFlags ? at : rows - kFlags;
+    const chunk_t raw = load_off(mask + base, off);
+    uint32_t on = 0;
+#pragma unroll
+    for (int e = 0; e < kFlags; ++e) on |= ((raw[e / 4] >> (8 * (e % 4))) & 0xFFu) ? 1u << e : 0u;
+    on = at - off < kFlags ? on >> (at - off) : 0u;
+    const int here = rows - at;  // rows of this thread
+    const uint32_t in = here <= 0 ? 0u : (here >= kFlags ? (1u << kFlags) - 1u : (1u << here) - 1u);
+    uint32_t bits[2] = {on & in, ~on & in};
+    const uint64_t cnt = uint64_t(__popc(bits[0])) | uint64_t(__popc(bits[1])) << 32;
+    const uint64_t incl = wave_inclusive_scan(cnt);
+    if (lane == kWave - 1) s_cnt[wid] = incl;
+    __syncthreads();
+    uint64_t before = incl - cnt, all = 0;
+#pragma unroll 1
+    for (int w = 0; w < NW; ++w) {
+        const uint64_t v = s_cnt[w];
+        if (w < wid) before += v;
+        all += v;
+    }
+    RowShare share;
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+        // This thread's rows of the kind have ranks r0 .. r0 + n - 1; the workgroup
+        // takes ranks l, l + G, ...
+        const int r0 = int(before >> (32 * z)) & 0x7FFFFFFF, n = __popc(bits[z]);
+        const int total = int(all >> (32 * z)) & 0x7FFFFFFF;
+        int j = r0 > l ? (r0 - l + G - 1) / G : 0;
+#pragma unroll 1
+        for (int r = l + j * G; r < r0 + n; r += G, ++j)
+            s_list[z == 0 ? j : kShareMax<W> - 1 - j] = base + at + nth_bit(bits[z], r - r0);
+        (z == 0 ? share.on : share.off) = __builtin_amdgcn_readfirstlane(total > l ? (total - l - 1) / G + 1 : 0);
+    }
+    __syncthreads();
+    return share;
+}
+
+// (8 waves per SIMD, two workgroups of 1024 threads on a CU, while a thread has
+// at most 8 elements.)
 template <typename Fmt, int W, int CPT, int KIND>
-__global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs a) {
+__global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) void distill_stream_kernel(StreamDistillArgs a) {
     constexpr int NW = W / kWave, EPC = Fmt::kPerChunk, NG = EPC / 4;
     // JSD caches exponentials (the others, exponents): see the statistics pass.
     constexpr bool XV = KIND == 2;
@@ -88,7 +161,9 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
     __shared__ double s_s[2 * NW];
     __shared__ RowPair s_rp;
     __shared__ double s_a[2 * NW];
-    __shared__ uint8_t s_on[W];
+    __shared__ int s_list[kShareMax<W>];
+    __shared__ uint64_t s_cnt[NW];
+    __shared__ int s_on;  // the flag of a workgroup's only row
     __shared__ double s_part[1];  // sum of this workgroup's row divergences
     __shared__ LossTail s_tail;
     __shared__ f32x4_t s_c0[CPT * NG * W];
@@ -99,22 +174,22 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
     asm volatile("" ::"s"(a.teacher), "s"(a.tstride), "s"(a.student), "s"(a.sstride), "s"(a.B), "s"(a.K), "s"(a.V),
                  "s"(a.mask), "s"(a.beta), "s"(a.c2), "s"(a.inv_tau));
     asm volatile("" ::"s"(a.row_loss_out), "s"(a.grad_out), "s"(a.row_ws), "s"(a.done), "s"(a.loss_out), "s"(a.nrows),
-                 "s"(a.row_bytes), "s"(a.G));
+                 "s"(a.row_bytes), "s"(a.G), "s"(a.slice), "s"(a.gs));
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int G = a.G;
     const float c2 = a.c2;
     const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
-    const float beta = a.beta, omb = 1.0f - a.beta;
+    const float beta = a.beta;
 
     chunk_t rt[CPT], rs[CPT];
     float c1[CPT][EPC];
 
-    // The mask flags of this workgroup's rows (thread j: row blockIdx.x +
-    // j*G), loaded before any row data so that waiting for them never waits
-    // for rows, and staged in LDS by step -1.  Nothing in the row loop then
-    // reads global memory except the rows themselves (a scalar load there
-    // would share its wait counter with LDS traffic).
-    const int nk = (a.nrows - int(blockIdx.x) + G - 1) / G;
+    // This workgroup's slice and place in it.  One slice unless the mask has more
+    // flags than the workgroup loads at once.
+    const int q = a.gs < G ? int(blockIdx.x) / a.gs : 0;
+    const int Gq = a.gs, l = int(blockIdx.x) - q * a.gs, base = q * a.slice;
+    const int rows = a.nrows - base < a.slice ? a.nrows - base : a.slice;
+    const bool listed = a.mask != nullptr && rows > Gq;
     if (tid == 0) {
         s_part[0] = 0.0;  // read and written by thread 0 only
         s_tail.row_ws = a.row_ws;
@@ -124,22 +199,34 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
         s_tail.nrows = a.nrows;
         s_tail.G = a.G;
     }
+    // One row per workgroup: its flag, loaded before the row so that waiting for it
+    // never waits for the row, and staged in LDS by step -1.
     uint32_t mine = 1u;
-    if (a.mask && tid < nk) mine = a.mask[int(blockIdx.x) + tid * G];
+    if (a.mask && !listed && l < rows) mine = a.mask[base + l];
+    // More rows: this workgroup's list of them, in LDS, so that nothing in the row
+    // loop reads global memory except the rows themselves (a scalar load there
+    // would share its wait counter with LDS traffic).
+    int more = 0, zeros = 0;  // rows after the next; rows off, not yet written
+    int next = l < rows ? base + l : -1;
+    if (listed) {
+        const RowShare share = share_rows<W>(a.mask, base, rows, Gq, l, s_list, s_cnt);
+        more = share.on > 0 ? share.on - 1 : 0;
+        zeros = share.off;
+        next = share.on > 0 ? __builtin_amdgcn_readfirstlane(s_list[0]) : -1;
+    } else if (a.mask == nullptr && l < rows) {
+        more = (rows - l - 1) / Gq;  // at most W - 1
+        if (tid <= more) s_list[tid] = l + tid * Gq;
+    }
+    const int quota = zeros / (more + 1) + 1;  // rows off written by a step
     // The pipeline starts one step early: step -1 computes nothing; it issues
-    // the loads of the workgroup's first row (read whatever its mask, which is
-    // not known yet), from the same code as every later step (so the compiler
-    // sees one load order throughout).
-    Row cur;
-    cur.on = false;
-    cur.trow = nullptr;
-    cur.srow = nullptr;
-    for (int k = -1, n = int(blockIdx.x) - G; n < a.nrows; n += G, ++k) {
-        const bool non = k < 0 ? true : (k + 1 < nk && s_on[k + 1] != 0);
-        const Row nxt = decode_row<Fmt>(a, n + G, non);
+    // the loads of the workgroup's first row, from the same code as every later
+    // step (so the compiler sees one load order throughout).
+    int n = -1;  // this step's row (-1: none)
+    bool live = false;
+    for (int k = -1; k < 0 || n >= 0; ++k) {
+        const Row nxt = decode_row<Fmt>(a, next);
         const rsrc_t ntr = make_rsrc(nxt.on ? nxt.trow : a.teacher, nxt.on ? a.row_bytes : 0u);
         const rsrc_t nsr = make_rsrc(nxt.on ? nxt.srow : a.student, nxt.on ? a.row_bytes : 0u);
-        if (k >= 0) cur = decode_row<Fmt>(a, n, s_on[k] != 0);
         // The gradient row of the current row (0 bytes before the first row:
         // nothing is written).
         const bool has_row = n >= 0;
@@ -151,7 +238,6 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
         // with the next row's.  The loads are issued whether or not the row
         // is computed: a branch around them would make the compiler copy
         // registers with loads still in flight, which waits for all of them.
-        const bool live = cur.on;
         float kc_t = 0.0f, kc_s = 0.0f;
         double S_t = 0.0, S_s = 0.0;
         if constexpr (XV) {
@@ -218,9 +304,18 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
             rs[r] = load_round<W, CPT>(nsr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (k < 0) {  // step -1: stage the mask flags
-            if (tid < nk) s_on[tid] = uint8_t(mine);  // the raw byte: no compare next to the load
+        if (k < 0) {  // step -1: stage the flag
+            if (tid == 0) s_on = int(mine);
             __syncthreads();
+        }
+        // The zero rows, spread over the steps (all by step -1 if there is no other).
+#pragma unroll 1
+        for (int z = 0; z < quota && zeros > 0; ++z) {
+            --zeros;
+            const int64_t zr = __builtin_amdgcn_readfirstlane(s_list[kShareMax<W> - 1 - zeros]);
+            if (a.grad_out)
+                zero_row<W>(make_rsrc(static_cast<char*>(a.grad_out) + zr * a.row_bytes, a.row_bytes), a.row_bytes, tid);
+            if (tid == 0 && a.row_loss_out) a.row_loss_out[zr] = 0.0f;
         }
         if (!live) {
             if (a.grad_out && has_row) {
@@ -238,20 +333,11 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
                 ks_s = kc_s + rescue_sum<CPT, EPC>(S_s, [&](int r, int e) -> float { return c1[r][e]; });
             }
             const RowPair rp = merge_row_pair<NW>(ks_t, S_t, ks_s, S_s, s_k, s_s, &s_rp);
-            const float Kt = rp.kt, Ks = rp.ks;
-            // log2 p_j = (t_j c2 - K_t) - (K_row_t - K_t + log2 S_t) = c - ct, likewise q.
-            // T = K + log2 S, the rows' log2 normalisers; only their
-            // difference is needed in fp64 (from the ratio of the sums).
-            const double dTd = rp.dtd;
-            const float ct = float(double(Kt - kc_t) + rp.lt), cs = float(double(Ks - kc_s) + rp.ls);
-            // FKL/RKL: log2(p/q) = (v_t - v_s) - dTk, from the same rounded
-            // exponents as the sums (so the normalisers and the log-ratios
-            // agree: rows with p ~ q keep their small divergence accurate).
-            const float dTk = float(dTd - double(kc_t - kc_s));
-            // JSD: p = e_t at and q = e_s as, the cached values times the
-            // thread's scale 2^(k - K) / S (fp64, rounded once).
-            const float at = float(__builtin_ldexp(rp.ist, int(fmaxf(kc_t - Kt, -2048.0f))));
-            const float as = float(__builtin_ldexp(rp.iss, int(fmaxf(kc_s - Ks, -2048.0f))));
+            // FKL/RKL take log2(p/q) from the same rounded exponents as the sums
+            // (so the normalisers and the log-ratios agree: rows with p ~ q keep
+            // their small divergence accurate); only the difference of the
+            // normalisers is needed in fp64 (from the ratio of the sums).
+            const RowScales z = row_scales(rp, kc_t, S_t == 0.0, kc_s, S_s == 0.0, beta);
 
             // ---- loss pass (from the cache) ----
             float acc0 = 0.0f, acc1 = 0.0f;
@@ -265,40 +351,7 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int e = 4 * g + j;
-                        if constexpr (KIND == 2) {
-                            const float p = c0v[j] * at, q = c1[r][e] * as;
-                            // rho = q/p, clamped to 2^+-126 (both limits stay exact enough:
-                            // the vanishing side carries no weight).  log2 m = log2 p + L,
-                            // L = log2(beta + (1 - beta) rho): the mixture's log relative
-                            // to p, a number near 0 when p ~ q, so the rounding of a log
-                            // does not bias every term of a small divergence.  At beta = 0,
-                            // L is d itself (the same log of the same value): x = 0.
-                            const float rho = __builtin_amdgcn_fmed3f(
-                                q * __builtin_amdgcn_rcpf(fmaxf(p, 0x1p-126f)), 0x1p-126f, 0x1p126f);
-                            const float d = log2_fast(rho);
-                            const float L = log2_fast(__builtin_fmaf(omb, rho, beta));
-                            const float x = d - L;  // log2(q/m)
-                            a0 = __builtin_fmaf(p, -L, a0);
-                            a1 = __builtin_fmaf(q, x, a1);
-                            c0v[j] = x;
-                            c1[r][e] = q;
-                        } else {
-                            // log2(p/q) from the difference of the two
-                            // exponents, clamped so that a zero probability
-                            // times an infinite log-ratio stays 0.
-                            const float lr = fmaxf(fminf((c0v[j] - c1[r][e]) - dTk, -kLogFloor), kLogFloor);
-                            if constexpr (KIND == 0) {
-                                const float p = exp2_fast(c0v[j] - ct);
-                                a0 = __builtin_fmaf(p, lr, a0);
-                                c0v[j] = p;
-                                c1[r][e] = c1[r][e] - cs;  // log2 q
-                            } else {
-                                const float q = exp2_fast(c1[r][e] - cs);
-                                a0 = __builtin_fmaf(q, lr, a0);
-                                c0v[j] = lr;
-                                c1[r][e] = q;
-                            }
-                        }
+                        loss_term<KIND>(c0v[j], c1[r][e], z.k, a0, a1);
                     }
                     lc.store(r, g, f32x4_t{c0v[0], c0v[1], c0v[2], c0v[3]});
                 }
@@ -306,7 +359,11 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
                 acc1 = acc1 + a1;
                 __builtin_amdgcn_sched_barrier(0);
             }
-            double A0 = double(acc0), A1 = KIND == 2 ? double(acc1) : 0.0;
+            double A0 = double(acc0), A1 = 0.0;
+            if constexpr (KIND == 2) {
+                A0 *= double(z.at);
+                A1 = double(acc1) * double(z.as);
+            }
             block_sum2<NW>(A0, A1, s_a);
             // Terms were accumulated in log2 units.
             if constexpr (KIND == 2)
@@ -319,8 +376,9 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
             // ---- gradient pass (from the cache) ----
             if (a.grad_out) {
                 const float ln2 = float(kLn2);
-                // JSD: (1-beta) ln2/tau * q * (x - KL2);  RKL: ln2/tau * q * (A0 - lr)
-                const float scale = KIND == 2 ? omb * ln2 * a.inv_tau : ln2 * a.inv_tau;
+                const float scale = KIND == 0   ? a.inv_tau
+                                    : KIND == 2 ? z.as * ((1.0f - beta) * ln2 * a.inv_tau)
+                                                : ln2 * a.inv_tau;
                 const float shift = KIND == 2 ? float(A1) : float(A0);
 #pragma unroll
                 for (int r = 0; r < CPT; ++r) {
@@ -332,12 +390,7 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             const int e = 4 * q4 + j;
-                            if constexpr (KIND == 0)
-                                g[e] = (exp2_fast(c1[r][e]) - c0v[j]) * a.inv_tau;
-                            else if constexpr (KIND == 2)
-                                g[e] = (c1[r][e] * scale) * (c0v[j] - shift);
-                            else
-                                g[e] = (c1[r][e] * scale) * (shift - c0v[j]);
+                            g[e] = grad_term<KIND>(c0v[j], c1[r][e], scale, shift);
                         }
                     }
                     store_round<Fmt, W, CPT>(gr, r, pack_grad<Fmt>(g), last);
@@ -345,11 +398,13 @@ __global__ __launch_bounds__(W, 1) void distill_stream_kernel(StreamDistillArgs 
                 }
             }
         }
-        if (tid == 0 && n >= 0) {
+        if (tid == 0 && has_row) {
             if (a.row_loss_out) a.row_loss_out[n] = float(D);
-            s_part[0] += D;  // this workgroup's rows, in row order
+            s_part[0] += D;  // this workgroup's rows, in the order taken
         }
-        cur = nxt;
+        n = next;
+        live = n >= 0 && (k >= 0 || __builtin_amdgcn_readfirstlane(s_on) != 0);
+        next = k + 1 < more ? __builtin_amdgcn_readfirstlane(s_list[k + 2]) : -1;
     }
     finish_loss<W>(s_tail, s_part);
 }
@@ -368,11 +423,20 @@ int blocks_per_cu() {
 template <typename Fmt, int W, int CPT, int KIND>
 hipError_t launch_kind(const DistillLaunch& L, const StreamDistillArgs& a) {
     int64_t want = int64_t(L.cus) * blocks_per_cu<Fmt, W, CPT, KIND>();
-    // At most W rows per workgroup: their mask flags are staged one per thread.
+    // At most W rows per workgroup (its list).
     const int64_t min_grid = (int64_t(a.nrows) + W - 1) / W;
     if (want < min_grid) want = min_grid;
-    const unsigned grid = unsigned(want < a.nrows ? want : a.nrows);
+    unsigned grid = unsigned(want < a.nrows ? want : a.nrows);
     StreamDistillArgs ag = a;
+    ag.slice = a.nrows;
+    ag.gs = int(grid);
+    if (a.mask && a.nrows > W * kFlags) {
+        // Slices of equal size, each with an equal number (at least 15) of workgroups.
+        const int64_t nq = (int64_t(a.nrows) + W * kFlags - 1) / (W * kFlags);
+        ag.slice = int((a.nrows + nq - 1) / nq);
+        ag.gs = int(grid / nq);
+        grid = unsigned(ag.gs * nq);
+    }
     ag.G = int(grid);
     const hipError_t e = launch_kernel(&distill_stream_kernel<Fmt, W, CPT, KIND>, dim3(grid), dim3(W), 0, L.stream, ag);
     return e;
