@@ -530,7 +530,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
     const int G = a.G;
     const float c2 = a.c2;
     const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
-    const float beta = a.beta, omb = 1.0f - a.beta;
+    const float beta = a.beta;
 
     chunk_t rt[CPT], rs[CPT];
     float c1[CPT][EPC];
@@ -760,21 +760,14 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
                 ks_s = kc_s + rescue_sum<CPT, EPC>(S_s, [&](int r, int e) -> float { return c1[r][e]; });
             }
             const RowPair rp = merge_row_pair<NW>(ks_t, S_t, ks_s, S_s, s_k[k & 1], s_s[k & 1], &s_rp[k & 1]);
-            const float Kt = rp.kt, Ks = rp.ks;
             const double St = rp.st, Ss = rp.ss;
-            // log2 p_j = (t_j c2 - K_t) - (K_row_t - K_t + log2 S_t) = c - ct, likewise q.
-            // T = K + log2 S, the rows' log2 normalisers; only their
-            // difference is needed in fp64 (from the ratio of the sums).
+            // FKL/RKL take log2(p/q) from the same rounded exponents as the sums
+            // (so the normalisers and the log-ratios agree: rows with p ~ q keep
+            // their small divergence accurate); only the difference of the
+            // normalisers is needed in fp64 (from the ratio of the sums).
             const double dTd = rp.dtd;
-            const float ct = float(double(Kt - kc_t) + rp.lt), cs = float(double(Ks - kc_s) + rp.ls);
-            // FKL/RKL: log2(p/q) = (v_t - v_s) - dTk, from the same rounded
-            // exponents as the sums (so the normalisers and the log-ratios
-            // agree: rows with p ~ q keep their small divergence accurate).
-            const float dTk = float(dTd - double(kc_t - kc_s));
-            // JSD: p = e_t at and q = e_s as, the cached values times the
-            // thread's scale 2^(k - K) / S (fp64, rounded once).
-            const float at = float(__builtin_ldexp(rp.ist, int(fmaxf(kc_t - Kt, -2048.0f))));
-            const float as = float(__builtin_ldexp(rp.iss, int(fmaxf(kc_s - Ks, -2048.0f))));
+            const RowScales z = row_scales(rp, kc_t, S_t == 0.0, kc_s, S_s == 0.0, beta);
+            const float at = z.at, as = z.as, ct = z.k.ct, cs = z.k.cs;
 
             // ---- verification ----
             bool spec = false;  // drew without knowing the earlier positions' outcomes
@@ -903,40 +896,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             const int e = 4 * g + j;
-                            if constexpr (KIND == 2) {
-                                const float p = c0v[j] * at, q = c1[r][e] * as;
-                                // rho = q/p, clamped to 2^+-126 (both limits stay exact enough:
-                                // the vanishing side carries no weight).  log2 m = log2 p + L,
-                                // L = log2(beta + (1 - beta) rho): the mixture's log relative
-                                // to p, a number near 0 when p ~ q, so the rounding of a log
-                                // does not bias every term of a small divergence.  At beta = 0,
-                                // L is d itself (the same log of the same value): x = 0.
-                                const float rho = __builtin_amdgcn_fmed3f(
-                                    q * __builtin_amdgcn_rcpf(fmaxf(p, 0x1p-126f)), 0x1p-126f, 0x1p126f);
-                                const float d = log2_fast(rho);
-                                const float L = log2_fast(__builtin_fmaf(omb, rho, beta));
-                                const float x = d - L;  // log2(q/m)
-                                a0 = __builtin_fmaf(p, -L, a0);
-                                a1 = __builtin_fmaf(q, x, a1);
-                                c0v[j] = x;
-                                c1[r][e] = q;
-                            } else {
-                                // log2(p/q) from the difference of the two
-                                // exponents, clamped so that a zero probability
-                                // times an infinite log-ratio stays 0.
-                                const float lr = fmaxf(fminf((c0v[j] - c1[r][e]) - dTk, -kLogFloor), kLogFloor);
-                                if constexpr (KIND == 0) {
-                                    const float p = exp2_fast(c0v[j] - ct);
-                                    a0 = __builtin_fmaf(p, lr, a0);
-                                    c0v[j] = p;
-                                    c1[r][e] = c1[r][e] - cs;  // log2 q
-                                } else {
-                                    const float q = exp2_fast(c1[r][e] - cs);
-                                    a0 = __builtin_fmaf(q, lr, a0);
-                                    c0v[j] = lr;
-                                    c1[r][e] = q;
-                                }
-                            }
+                            loss_term<KIND>(c0v[j], c1[r][e], z.k, a0, a1);
                         }
                         lc.store(r, g, f32x4_t{c0v[0], c0v[1], c0v[2], c0v[3]});
                     }
@@ -944,7 +904,11 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
                     acc1 = acc1 + a1;
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                double A0 = double(acc0), A1 = KIND == 2 ? double(acc1) : 0.0;
+                double A0 = double(acc0), A1 = 0.0;
+                if constexpr (KIND == 2) {
+                    A0 *= double(at);
+                    A1 = double(acc1) * double(as);
+                }
                 block_sum2<NW>(A0, A1, s_a);
                 // Terms were accumulated in log2 units.  (ln 2 is read from
                 // LDS here rather than held in registers across the item loop.)
@@ -957,8 +921,9 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
                     D = -ln2d * A0;
                 if (a.grad_out && distilled) {
                     const float ln2 = float(kLn2);
-                    // JSD: (1-beta) ln2/tau * q * (x - KL2);  RKL: ln2/tau * q * (A0 - lr)
-                    const float scale = KIND == 2 ? omb * ln2 * a.inv_tau : ln2 * a.inv_tau;
+                    const float scale = KIND == 0   ? a.inv_tau
+                                        : KIND == 2 ? as * ((1.0f - beta) * ln2 * a.inv_tau)
+                                                    : ln2 * a.inv_tau;
                     const float shift = KIND == 2 ? float(A1) : float(A0);
 #pragma unroll
                     for (int r = 0; r < CPT; ++r) {
@@ -970,12 +935,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
 #pragma unroll
                             for (int j = 0; j < 4; ++j) {
                                 const int e = 4 * q4 + j;
-                                if constexpr (KIND == 0)
-                                    g[e] = (exp2_fast(c1[r][e]) - c0v[j]) * a.inv_tau;
-                                else if constexpr (KIND == 2)
-                                    g[e] = (c1[r][e] * scale) * (c0v[j] - shift);
-                                else
-                                    g[e] = (c1[r][e] * scale) * (shift - c0v[j]);
+                                g[e] = grad_term<KIND>(c0v[j], c1[r][e], scale, shift);
                             }
                         }
                         store_round<Fmt, W, CPT>(gr, r, pack_grad<Fmt>(g), last);
