@@ -46,6 +46,8 @@ class OsdError(RuntimeError):
 def lib():
     """Load libosd.so (built in-tree by paper_2310_07177_amd.build)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -97,13 +99,24 @@ def lib():
     return _lib
 
 
+# The host path of a short call is as long as its kernel (verification of one
+# sequence on the GPU: 10 us), so what every entry point does per call is kept to
+# plain integers: no argument objects, no torch.cuda.Stream built to ask for its
+# handle, one lookup of module and library (verification of one sequence, K = 4,
+# V = 32000, call after call: 15.2 -> 10.6 us, the kernel's own 10.1). 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(t):
@@ -122,8 +135,7 @@ def _check_cuda(*ts):
 
 
 def _stream_handle(device):
-    torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return _torch()._C._cuda_getCurrentRawStream(device.index)
 
 
 # Zero-initialised workspaces, one per (device, stream, kind, size): the kernels
@@ -132,11 +144,10 @@ _workspaces = {}
 
 
 def workspace(kind, nbytes, device):
-    torch = _torch()
-    stream = torch.cuda.current_stream(device).cuda_stream
-    key = (str(device), stream, kind)
+    key = (device.index, _stream_handle(device), kind)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
+        torch = _torch()
         ws = torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)
         _workspaces[key] = ws
     return ws
