@@ -11,12 +11,12 @@
 // and 0 log 0 = 0.  Rows with mask 0 get D = 0 and a zero gradient row.
 //
 // Work layout.  About one workgroup per CU walks rows g, g+G, ... or, with a
-// mask, its equal share of the rows that are on (share_rows), each step loading
-// the next of them; the zero gradient rows are written between the passes of a
-// step.  (With every row g, g+G, ... whatever its mask, a workgroup's share of the
-// rows that are on varied by a third and a row that was off left nothing in flight
-// under the row before it: 16384 rows of V = 32000 bf16, 40 % on, JSD, took 459 us,
-// now 378.)
+// mask and more than two rows each, its equal share of the rows that are on
+// (share_rows), each step loading the next of them; the zero gradient rows are
+// written between the passes of a step.  (With every row g, g+G, ... whatever its
+// mask, a workgroup's share of the rows that are on varied by a third and a row
+// that was off left nothing in flight under the row before it: 16384 rows of
+// V = 32000 bf16, 40 % on, JSD, took 459 us, now 374.)
 // Each thread owns chunks n*W + tid of both rows.  The statistics pass
 // consumes the raw chunks of row j while each register chunk is reloaded with
 // the same chunk of row j+G; what the later passes need is kept per element in
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     __shared__ double s_a[2 * NW];
     __shared__ int s_list[kShareMax<W>];
     __shared__ uint64_t s_cnt[NW];
-    __shared__ int s_on;  // the flag of a workgroup's only row
+    __shared__ int s_on[2];  // the flags of a workgroup's only rows
     __shared__ double s_part[1];  // sum of this workgroup's row divergences
     __shared__ LossTail s_tail;
     __shared__ f32x4_t s_c0[CPT * NG * W];
@@ -189,7 +189,10 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     const int q = a.gs < G ? int(blockIdx.x) / a.gs : 0;
     const int Gq = a.gs, l = int(blockIdx.x) - q * a.gs, base = q * a.slice;
     const int rows = a.nrows - base < a.slice ? a.nrows - base : a.slice;
-    const bool listed = a.mask != nullptr && rows > Gq;
+    // (Up to two rows per workgroup are not worth the list: finding it keeps the first
+    // row's loads waiting for the flags.  512 rows of V = 32128 bf16, all on: 30.7 us
+    // with it and 28.1 without, RKL 27.9 and 24.8.)
+    const bool listed = a.mask != nullptr && rows > 2 * Gq;
     if (tid == 0) {
         s_part[0] = 0.0;  // read and written by thread 0 only
         s_tail.row_ws = a.row_ws;
@@ -199,10 +202,10 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
         s_tail.nrows = a.nrows;
         s_tail.G = a.G;
     }
-    // One row per workgroup: its flag, loaded before the row so that waiting for it
-    // never waits for the row, and staged in LDS by step -1.
+    // One or two rows per workgroup: their flags, loaded before the row so that waiting
+    // for them never waits for the row, and staged in LDS by step -1.
     uint32_t mine = 1u;
-    if (a.mask && !listed && l < rows) mine = a.mask[base + l];
+    if (a.mask && !listed && tid < 2 && l + tid * Gq < rows) mine = a.mask[base + l + tid * Gq];
     // More rows: this workgroup's list of them, in LDS, so that nothing in the row
     // loop reads global memory except the rows themselves (a scalar load there
     // would share its wait counter with LDS traffic).
@@ -213,9 +216,9 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
         more = share.on > 0 ? share.on - 1 : 0;
         zeros = share.off;
         next = share.on > 0 ? __builtin_amdgcn_readfirstlane(s_list[0]) : -1;
-    } else if (a.mask == nullptr && l < rows) {
+    } else if (l < rows) {
         more = (rows - l - 1) / Gq;  // at most W - 1
-        if (tid <= more) s_list[tid] = l + tid * Gq;
+        if (tid <= more) s_list[tid] = base + l + tid * Gq;
     }
     const int quota = zeros / (more + 1) + 1;  // rows off written by a step
     // The pipeline starts one step early: step -1 computes nothing; it issues
@@ -224,7 +227,9 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     int n = -1;  // this step's row (-1: none)
     bool live = false;
     for (int k = -1; k < 0 || n >= 0; ++k) {
-        const Row nxt = decode_row<Fmt>(a, next);
+        // (The first row is read whatever its flag, which is not known yet.)
+        const bool skip = k == 0 && __builtin_amdgcn_readfirstlane(s_on[1]) == 0;
+        const Row nxt = decode_row<Fmt>(a, skip ? -1 : next);
         const rsrc_t ntr = make_rsrc(nxt.on ? nxt.trow : a.teacher, nxt.on ? a.row_bytes : 0u);
         const rsrc_t nsr = make_rsrc(nxt.on ? nxt.srow : a.student, nxt.on ? a.row_bytes : 0u);
         // The gradient row of the current row (0 bytes before the first row:
@@ -304,8 +309,8 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
             rs[r] = load_round<W, CPT>(nsr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (k < 0) {  // step -1: stage the flag
-            if (tid == 0) s_on = int(mine);
+        if (k < 0) {  // step -1: stage the flags
+            if (tid < 2) s_on[tid] = int(mine);
             __syncthreads();
         }
         // The zero rows, spread over the steps (all by step -1 if there is no other).
@@ -403,7 +408,7 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
             s_part[0] += D;  // this workgroup's rows, in the order taken
         }
         n = next;
-        live = n >= 0 && (k >= 0 || __builtin_amdgcn_readfirstlane(s_on) != 0);
+        live = n >= 0 && (k >= 1 || __builtin_amdgcn_readfirstlane(s_on[k + 1]) != 0);
         next = k + 1 < more ? __builtin_amdgcn_readfirstlane(s_list[k + 2]) : -1;
     }
     finish_loss<W>(s_tail, s_part);
