@@ -227,7 +227,13 @@ int osd_distill_loss_grad(const void* teacher_logits, int64_t teacher_batch_stri
     L.stream = static_cast<hipStream_t>(stream);
     L.cus = device_cus(L.stream);
     osd::RowTile t;
-    const bool streaming = osd::pick_stream_tile(V, per_chunk(dtype), &t);
+    // A few rows of the longest streaming tile, where one workgroup per row would leave
+    // most of the chip idle, are split as the rows beyond it are (V = 32000 bf16, FKL:
+    // 4 rows 13.0 -> 11.2 us, 40 rows 13.7 -> 11.6, 128 rows 15.3 -> 14.8, but 192 rows
+    // 16.9 -> 17.4; shorter rows gain nothing: 40 rows of V = 16000 10.3 and 11.2, of
+    // V = 16000 fp32 10.9 and 11.8).
+    const bool few = int64_t(B) * K <= L.cus / 2 && V > 3 * 1024 * 8;
+    const bool streaming = osd::pick_stream_tile(V, per_chunk(dtype), &t) && !few;
     const hipError_t e = streaming ? osd::launch_distill_stream(L) : osd::launch_distill(L);
     return e == hipSuccess ? OSD_OK : OSD_ERR_DEVICE;
 }
