@@ -191,7 +191,8 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     const int rows = a.nrows - base < a.slice ? a.nrows - base : a.slice;
     // (Up to two rows per workgroup are not worth the list: finding it keeps the first
     // row's loads waiting for the flags.  512 rows of V = 32128 bf16, all on: 30.7 us
-    // with it and 28.1 without, RKL 27.9 and 24.8.)
+    // with it and 27.8 without, RKL 27.9 and 25.1; an eighth of them on, behind a
+    // verification: 44.7 and 48.9 in all.)
     const bool listed = a.mask != nullptr && rows > 2 * Gq;
     if (tid == 0) {
         s_part[0] = 0.0;  // read and written by thread 0 only
