@@ -68,9 +68,11 @@ __device__ inline void write_outputs(const SegArgs& a, int b, int kb, int acc, b
 }
 
 // A segment's argmax as one word: larger for a larger value, then for a lower
-// index; never zero (a segment without finite logits: -inf).
+// index; never zero (a segment without finite logits: -inf).  The keys order
+// -0.0 below +0.0, which are equal logits, so either zero gets the key of +0.0.
 __device__ inline uint64_t argmax_word(float v, int idx) {
-    return (uint64_t(float_key(v)) << 32) | (0xFFFFFFFFu - uint32_t(idx));
+    const uint32_t key = v == 0.0f ? 0x80000000u : float_key(v);
+    return (uint64_t(key) << 32) | (0xFFFFFFFFu - uint32_t(idx));
 }
 
 // Polls of the last arriver for words that were posted before it arrived.
