@@ -10,12 +10,12 @@
 // Work layout: one flat grid of small workgroups, one per (target row, vocabulary
 // segment of kW*4 chunks), so the hardware dispatcher balances the work over every
 // CU whatever B and k are.  Each posts its segment's (max, lowest index) as one
-// word and arrives at its sequence's counter without waiting for the word; the
+// word and, once the word is in place, arrives at its sequence's counter; the
 // last of a sequence to arrive merges the words of rows 0..k_b in segment order,
 // finds the first mismatch, writes the outputs and clears words and counter.
-// (The decision in a kernel of its own took B = 1, K = 4, V = 32000 bf16 5.2 us and
-// B = 8, K = 5 6.0, this one 4.7 and 5.3; larger batches are bound by the read: B = 64,
-// K = 8, V = 32128 10.8.  With the counters of all sequences side by side the same
+// (The wait for the word costs 0.2 to 0.3 us: B = 1, K = 4, V = 32000 bf16 5.1 -> 5.4, B = 64,
+// K = 8, V = 32128 9.6 -> 9.9.  The decision in a kernel of its own took the first of the
+// two 0.5 us longer than the variant without the wait.  With the counters of all sequences side by side the same
 // batch took 22.1 us: see VerifyRow.)
 #include "osd.h"
 #include "osd_device.hpp"
@@ -74,9 +74,6 @@ __device__ inline uint64_t argmax_word(float v, int idx) {
     const uint32_t key = v == 0.0f ? 0x80000000u : float_key(v);
     return (uint64_t(key) << 32) | (0xFFFFFFFFu - uint32_t(idx));
 }
-
-// Polls of the last arriver for words that were posted before it arrived.
-constexpr int kWordPolls = 4096;
 
 template <typename Fmt, int CPT>
 __global__ __launch_bounds__(kW) void verify_greedy_kernel(SegArgs a) {
@@ -138,30 +135,21 @@ __global__ __launch_bounds__(kW) void verify_greedy_kernel(SegArgs a) {
                 bx = s_i[w];
             }
         const uint64_t word = argmax_word(bv, bx == 0x7FFFFFFF ? bx : cut.token(bx));
-        __hip_atomic_store(&a.rows[pair].words[s], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t prev = __hip_atomic_fetch_add(&a.rows[int64_t(b) * (a.K + 1)].arrivals, 1u, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
+        publish_u64(&a.rows[pair].words[s], word);
+        const uint32_t prev = arrive(&a.rows[int64_t(b) * (a.K + 1)].arrivals);  // after the word
         s_last = prev == uint32_t((kb + 1) * a.nseg - 1);
     }
     __syncthreads();
     if (!s_last) return;
 
-    // The sequence's last arriver: every word is posted; wait (bounded) for those
-    // still on their way, then clear them.
+    // The sequence's last arriver: every word is in place; read and clear them.
     VerifyRow* rows = a.rows + int64_t(b) * (a.K + 1);
     for (int j = tid; j < (kb + 1) * a.nseg; j += kW) {
         const int r = j / a.nseg, q = j - r * a.nseg;
-        uint64_t v = 0;
-        for (int p = 0; p < kWordPolls && v == 0; ++p) v = poll_u64(&rows[r].words[q]);
-        s_row[r][q] = v;
-    }
-    wait_memory();  // this workgroup's own word is in place before it is cleared
-    __syncthreads();
-    for (int j = tid; j < (kb + 1) * a.nseg; j += kW) {
-        const int r = j / a.nseg, q = j - r * a.nseg;
-        __hip_atomic_store(&rows[r].words[q], uint64_t(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_row[r][q] = take_u64(&rows[r].words[q]);
     }
     if (tid == 0) __hip_atomic_store(&rows[0].arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
     if (tid >= kWave) return;
     // Lane r: row r's argmax (lowest index on ties); accept while y_r equals it,
     // emit the argmax where the test stops.
