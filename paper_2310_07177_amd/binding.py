@@ -138,17 +138,53 @@ def _stream_handle(device):
     return _torch()._C._cuda_getCurrentRawStream(device.index)
 
 
-# Zero-initialised workspaces, one per (device, stream, kind, size): the kernels
-# leave them zeroed, so they are reused across calls on the same stream.
+# Zero-initialised workspaces, one per (device, stream, kind): the kernels leave
+# them zeroed, so they are reused across calls on the same stream.  A captured graph
+# holds its workspace's address, so one that a larger call supersedes is kept (sizes
+# are powers of two: all of a stream's superseded ones together are smaller than the
+# one in use).  A graph replayed on another stream than the one it was captured on
+# must not overlap calls on that one, nor other graphs captured on it.
 _workspaces = {}
+_superseded = []
+# A workspace first needed during a capture is the graph's own: its zero fill is
+# recorded, not executed, so calls outside that capture cannot use it.
+# key -> (capture, workspace)
+_captured = {}
+
+
+def _capture_id(stream):
+    """The capture that `stream` (a handle) takes part in, 0 if none (as the null stream)."""
+    if not stream:
+        return 0
+    status, capture = ctypes.c_int(0), ctypes.c_ulonglong(0)
+    err = lib().hipStreamGetCaptureInfo(ctypes.c_void_p(stream), ctypes.byref(status), ctypes.byref(capture))
+    return capture.value if err == 0 and status.value == 1 else 0
 
 
 def workspace(kind, nbytes, device):
     key = (device.index, _stream_handle(device), kind)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
-        torch = _torch()
-        ws = torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        ws = _new_workspace(key, nbytes, device)
+    return ws
+
+
+def _new_workspace(key, nbytes, device):
+    torch = _torch()
+    capture = _capture_id(key[1])
+    if capture:
+        held = _captured.get(key)
+        if held is not None and held[0] == capture and held[1].numel() >= nbytes:
+            return held[1]
+    size = 1 << (max(int(nbytes), 256) - 1).bit_length()
+    ws = torch.zeros(size, dtype=torch.uint8, device=device)
+    if capture:
+        _captured[key] = (capture, ws)
+        return ws
+    with _lock:
+        _captured.pop(key, None)
+        if key in _workspaces:
+            _superseded.append(_workspaces[key])
         _workspaces[key] = ws
     return ws
 

@@ -264,3 +264,43 @@ def test_graph_replays_match_eager_sharded():
         torch.cuda.synchronize()
         for e, o in zip(eager, (stats, mass, acc, toks, rm)):
             assert torch.equal(e, o), f"replay {rep}"
+
+
+def _verify_set(B, K, V, dev, seed):
+    x = synth.verify_inputs(B, K, V, "bf16", T=0.8, seed=seed, target_std=2.5, draft_noise=1.0)
+    return [_dev(x[k], dev) for k in ("target", "draft")] + [_dev(x["tokens"].astype(np.int32), dev)] + \
+        [_dev(x[k], dev) for k in ("u_accept", "u_resample")]
+
+
+@pytest.mark.parametrize("warm", [True, False])
+def test_graph_through_the_binding_keeps_its_workspace(warm):
+    """A call captured through the binding, with and without an eager call on the
+    stream before it, then a larger call on the same stream (another workspace) and
+    other tensors in whatever memory is free: every replay is the eager result."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    dev = torch.device("cuda:0")
+    small, other, large = (_verify_set(B, 4, 8192, dev, seed) for B, seed in ((4, 1), (4, 2), (96, 3)))
+    want = [o.clone() for o in binding.osd_verify(*small, 0.8)]
+    want_other, want_large = binding.osd_verify(*other, 0.8), binding.osd_verify(*large, 0.8)
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream(dev)
+    if warm:
+        with torch.cuda.stream(stream):
+            binding.osd_verify(*small, 0.8)
+        torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        out = binding.osd_verify(*small, 0.8)
+    for rep in range(3):
+        with torch.cuda.stream(stream):  # the first of them before the first replay
+            for a, b in ((want_other, binding.osd_verify(*other, 0.8)), (want_large, binding.osd_verify(*large, 0.8))):
+                torch.cuda.synchronize()
+                assert all(torch.equal(u, v) for u, v in zip(a, b)), rep
+            junk = [torch.full((n,), 0xA5, dtype=torch.uint8, device=dev) for n in (8192, 16384, 32768, 65536) for _ in range(8)]
+            torch.cuda.synchronize()
+            g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(u, v) for u, v in zip(want, out)), rep
+        assert all(bool((j == 0xA5).all()) for j in junk)
