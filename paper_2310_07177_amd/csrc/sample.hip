@@ -227,7 +227,7 @@ __global__ __launch_bounds__(W, 1) void sample_stream_kernel(SampleArgs a) {
     const float u = a.u[n];
     ChunkSum cp[CPT], cq[MIX ? CPT : 1];
     float Kp = kNegInf, Kq = kNegInf, fp = 0.0f, fq = 0.0f;
-    cq[0] = ChunkSum{0.0f, 0.0f};
+    cq[0] = ChunkSum{0.0f, kNegInf};
 #pragma unroll
     for (int g = 0; g < CPT; g += U) {
         if (g < R) {
@@ -248,8 +248,10 @@ __global__ __launch_bounds__(W, 1) void sample_stream_kernel(SampleArgs a) {
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
+            // Rounds past the row, as a chunk of padding: a shift above the row's (0, where
+            // every logit lies far below) would scale the absent mass up to infinity.
 #pragma unroll
-            for (int r = 0; r < U; ++r) cp[g + r] = cq[MIX ? g + r : 0] = ChunkSum{0.0f, 0.0f};
+            for (int r = 0; r < U; ++r) cp[g + r] = cq[MIX ? g + r : 0] = ChunkSum{0.0f, kNegInf};
         }
     }
     double Sp = fp, Sq = fq;

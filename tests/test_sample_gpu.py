@@ -278,3 +278,15 @@ def test_sample_split_fallback_is_bit_identical(osd, tmp_path):
         ws = torch.zeros(osd.lib().osd_sample_workspace_bytes(N), dtype=torch.uint8, device=qd.device)
         want = raw_sample(osd, None, qd, 0.8, 0.0, ud, ws)
         assert np.array_equal(got[f"{N}_{V}"], want), f"N={N} V={V} {dtype}"
+
+
+@pytest.mark.parametrize("V,dtype", [(65537, "bf16"), (70001, "bf16"), (98304, "bf16"), (40001, "f32")])
+@pytest.mark.parametrize("N", [1, 5])
+def test_sample_mixture_far_below_zero(osd, V, dtype, N):
+    """Mixtures whose shifts lie far below zero (every logit times log2(e)/T under
+    -128), of lengths whose last rounds of the 16-round tile are absent: an
+    absent chunk has no mass, whatever the shift."""
+    x = synth.sample_inputs(N, V, dtype, seed=V % 61, p_std=1.0)
+    p, q = (synth.store(synth.as_f32(x[k]) - np.float32(40.0), dtype) for k in ("p", "q"))
+    for u in (x["u"], np.full(N, 0.999, np.float32)):
+        check(osd, p, q, 0.1, 0.4, u, f"V={V} {dtype} far below zero")
