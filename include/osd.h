@@ -161,7 +161,10 @@ size_t osd_distill_workspace_bytes(int B, int K);
  *                 reduced in a fixed order in fp64, so bitwise deterministic
  * row_loss_out    out [B, K] fp32, nullable: D per row, 0 where mask is 0
  * grad_out        out [B, K, V] in `dtype`, contiguous, nullable: the
- *                 gradient of sum(mask*D); rows with mask 0 are written as 0
+ *                 gradient of sum(mask*D); rows with mask 0 are written as 0.
+ *                 It may take the student rows' own place for V up to 32768
+ *                 (bf16) or 16384 (fp32); otherwise outputs and inputs must
+ *                 not overlap
  * workspace       osd_distill_workspace_bytes(B, K) zero-initialised bytes
  */
 int osd_distill_loss_grad(const void* teacher_logits, int64_t teacher_batch_stride,

@@ -86,6 +86,18 @@ int device_cus(hipStream_t stream) {
     return n;
 }
 
+// Whether the gradient shares memory with the rows that it is taken from.
+bool grad_overlaps(const osd::DistillLaunch& L) {
+    if (!L.grad_out) return false;
+    const int64_t eb = L.dtype == OSD_BF16 ? 2 : 4, rows = int64_t(L.K) * L.V;
+    const auto begin = [](const void* p) { return reinterpret_cast<uintptr_t>(p); };
+    const auto meets = [&](const void* p, int64_t stride) {
+        const uintptr_t end = begin(p) + uintptr_t(((L.B - 1) * stride + rows) * eb);
+        return begin(L.grad_out) < end && begin(p) < begin(L.grad_out) + uintptr_t(L.B * rows * eb);
+    };
+    return meets(L.teacher, L.teacher_stride) || meets(L.student, L.student_stride);
+}
+
 // Zero n 32-bit words (a kernel rather than a memset: it may be captured
 // into a graph).
 __global__ void clear_words(uint32_t* p, int n) {
@@ -227,13 +239,17 @@ int osd_distill_loss_grad(const void* teacher_logits, int64_t teacher_batch_stri
     L.stream = static_cast<hipStream_t>(stream);
     L.cus = device_cus(L.stream);
     osd::RowTile t;
-    // A few rows of the longest streaming tile, where one workgroup per row would leave
-    // most of the chip idle, are split as the rows beyond it are (V = 32000 bf16, FKL:
-    // 4 rows 13.0 -> 11.2 us, 40 rows 13.7 -> 11.6, 128 rows 15.3 -> 14.8, but 192 rows
-    // 16.9 -> 17.4; shorter rows gain nothing: 40 rows of V = 16000 10.3 and 11.2, of
-    // V = 16000 fp32 10.9 and 11.8).
-    const bool few = int64_t(B) * K <= L.cus / 2 && V > 3 * 1024 * 8;
-    const bool streaming = osd::pick_stream_tile(V, per_chunk(dtype), &t) && !few;
+    const bool tiled = osd::pick_stream_tile(V, per_chunk(dtype), &t);
+    // A few bf16 rows of the longest streaming tile (1024 threads x 4 chunks), where one
+    // workgroup per row would leave most of the chip idle, are split as the rows beyond
+    // it are (V = 32000 bf16, FKL: 4 rows 13.0 -> 11.2 us, 40 rows 13.7 -> 11.6, 128 rows
+    // 15.3 -> 14.8, but 192 rows 16.9 -> 17.4; the other tiles and fp32 gain nothing: 40
+    // rows of V = 16000 bf16 10.3 and 11.2, of V = 16000 fp32 10.9 and 11.8).  A gradient
+    // written over the rows themselves stays with the streaming kernel, which has read a
+    // row whole before it writes: a segment of a split row may be read again late.
+    const bool few = tiled && dtype == OSD_BF16 && t.W * t.CPT == 1024 * 4 && int64_t(B) * K <= L.cus / 2 &&
+                     !grad_overlaps(L);
+    const bool streaming = tiled && !few;
     const hipError_t e = streaming ? osd::launch_distill_stream(L) : osd::launch_distill(L);
     return e == hipSuccess ? OSD_OK : OSD_ERR_DEVICE;
 }
