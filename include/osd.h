@@ -166,6 +166,11 @@ size_t osd_distill_workspace_bytes(int B, int K);
  *                 (bf16) or 16384 (fp32); otherwise outputs and inputs must
  *                 not overlap
  * workspace       osd_distill_workspace_bytes(B, K) zero-initialised bytes
+ *
+ * Equal calls give equal bits.  Which kernel takes a row, and so the order of
+ * its sums, depends on V, dtype and, for bf16 rows of 24577 to 32768 logits, on
+ * whether the call has more than one row per two CUs: there a row's loss and
+ * gradient may differ in their last bits between calls of few and of many rows.
  */
 int osd_distill_loss_grad(const void* teacher_logits, int64_t teacher_batch_stride,
                           const void* student_logits, int64_t student_batch_stride,
@@ -201,7 +206,8 @@ size_t osd_verify_distill_workspace_bytes(int B, int K);
  * masses are formed from the distillation's cached exponents, so a draw that
  * sits within ~1e-7 of a CDF edge may differ from osd_verify's); losses and
  * gradients match osd_distill_loss_grad's within fp32 rounding (the fp64 loss
- * sum is taken in a different fixed order).
+ * sum is taken in a different fixed order; a row's own values are the same bit
+ * for bit, except in osd_distill_loss_grad's calls of few rows described there).
  */
 int osd_verify_distill(const void* target_logits, const void* draft_logits, int dtype,
                        int B, int K, int V,

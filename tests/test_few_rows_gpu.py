@@ -1,7 +1,8 @@
 """Distillation of few rows of the longest streaming tile, which are split over
 workgroups (up to one row per two CUs, V above 24576 bf16): both sides of either
 limit, ragged and whole rows, with and without a mask, against the fp64 oracle;
-gradients written over the student rows."""
+gradients written over the student rows; and where the one-call step and the
+separate call give the same bits."""
 import os
 import subprocess
 import sys
@@ -66,3 +67,23 @@ def test_gradient_over_the_student_rows(osd):
     r = subprocess.run([sys.executable, "-u", "-c", CHILD], cwd=root, env=dict(os.environ, OSD_SPLIT_POLLS="0"),
                        capture_output=True, text=True, timeout=110)
     assert r.returncode == 0 and "IN_PLACE_OK" in r.stdout, r.stdout[-1000:] + r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("B,K,V,dtype", [(2, 3, 16000, "bf16"), (2, 3, 16000, "f32"), (2, 2, 40000, "bf16"),
+                                         (64, 3, 32000, "bf16"), (2, 3, 32000, "bf16")])
+@pytest.mark.parametrize("kind", ["fkl", "rkl", "jsd"])
+def test_one_call_and_separate_call(osd, B, K, V, dtype, kind):
+    import torch
+    x = synth.verify_inputs(B, K, V, dtype, T=0.9, seed=7, target_std=2.0, draft_noise=1.0)
+    t, s = to_device(x["target"]), to_device(x["draft"])
+    one = osd.osd_verify_distill(t, s, to_device(x["tokens"]), to_device(x["u_accept"]), to_device(x["u_resample"]),
+                                 0.9, kind, 0.4)
+    two = osd.osd_distill_loss_grad(t, s, kind, 0.4, 0.9, B=B, K=K, teacher_batch_stride=(K + 1) * V,
+                                    student_batch_stride=K * V)
+    torch.cuda.synchronize()
+    few = dtype == "bf16" and 24576 < V <= 32768 and B * K <= torch.cuda.get_device_properties(0).multi_processor_count // 2
+    if few:  # another order of sums
+        assert torch.allclose(one[4], two[1], rtol=1e-5, atol=1e-7)
+        assert torch.allclose(one[5].float(), two[2].float(), rtol=2.0 ** -7, atol=1e-6)
+    else:
+        assert torch.equal(one[4], two[1]) and torch.equal(one[5], two[2])
