@@ -254,7 +254,7 @@ __device__ inline void seg_build(SegCache<Fmt>& c, const char* trow, const char*
             xs[0] = load_short<Fmt>(srow, V);
         }
     }
-    const LastChunk whole{0, 0, false};  // the padding is in place
+    const LastChunk<false> whole{0, 0, false};  // the padding is in place
     c.kt = shift_of_max(chunks_max<Fmt, kSegCPT<Fmt>>(xt, whole), c2);
     c.ks = shift_of_max(chunks_max<Fmt, kSegCPT<Fmt>>(xs, whole), c2);
 #pragma unroll

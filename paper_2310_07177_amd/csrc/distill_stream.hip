@@ -178,7 +178,7 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int G = a.G;
     const float c2 = a.c2;
-    const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
+    const LastChunk<true> last = last_chunk<Fmt, W, CPT>(a.V);
     const float beta = a.beta;
 
     chunk_t rt[CPT], rs[CPT];
@@ -261,10 +261,7 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
         for (int r = 0; r < CPT; ++r) {
             if (live) {
                 chunk_t xt = rt[r], xs = rs[r];
-                if (r == CPT - 1 && last.ragged) {
-                    xt = pad_lead<Fmt>(xt, last.lead);
-                    xs = pad_lead<Fmt>(xs, last.lead);
-                }
+                if (r == CPT - 1) pad_last<Fmt>(xt, xs, last);
                 if (!XV && r == 0) {
                     kc_t = first_chunk_shift<Fmt>(xt, c2);
                     kc_s = first_chunk_shift<Fmt>(xs, c2);

@@ -37,27 +37,42 @@ __device__ inline rsrc_t make_rsrc(const void* base, uint32_t bytes) {
 // byte offset in the row (past the row's end if it is all padding).  ragged
 // says whether any lane of the wave holds padding: the other waves skip its
 // handling on one scalar branch (lane by lane it cost the fused kernel 2 %).
+// PART: rows may end inside a chunk; else a chunk is padding whole or not at all.
+template <bool PART>
 struct LastChunk {
     int lead, off;
     bool ragged;
 };
-template <typename Fmt, int W, int CPT>
-__device__ inline LastChunk last_chunk(int V) {
+template <typename Fmt, int W, int CPT, bool PART = true>
+__device__ inline LastChunk<PART> last_chunk(int V) {
     const RowCut<Fmt> cut(V);
     const int ch = (CPT - 1) * W + static_cast<int>(threadIdx.x);
     const int lead = cut.lead(ch);
-    return LastChunk{lead, ch == cut.nchunks - 1 ? int(cut.last_off) : ch * 16, __ballot(lead != 0) != 0};
+    return LastChunk<PART>{lead, PART && ch == cut.nchunks - 1 ? int(cut.last_off) : ch * 16, __ballot(lead != 0) != 0};
+}
+
+// The chunks of that round of two rows, padded.
+template <typename Fmt, bool PART>
+__device__ inline void pad_last(chunk_t& a, chunk_t& b, const LastChunk<PART>& last) {
+    if constexpr (PART) {
+        if (!last.ragged) return;
+        a = pad_lead<Fmt>(a, last.lead);
+        b = pad_lead<Fmt>(b, last.lead);
+    } else if (last.lead != 0) {
+        a = pad_chunk<Fmt>();
+        b = pad_chunk<Fmt>();
+    }
 }
 
 // Chunk of round n of this thread; chunks past the row read as zeros.
-template <int W, int CPT>
-__device__ inline chunk_t load_round(rsrc_t r, int n, const LastChunk& last) {
-    const int off = n == CPT - 1 ? last.off : (n * W + static_cast<int>(threadIdx.x)) * 16;
+template <int W, int CPT, bool PART>
+__device__ inline chunk_t load_round(rsrc_t r, int n, const LastChunk<PART>& last) {
+    const int off = PART && n == CPT - 1 ? last.off : (n * W + static_cast<int>(threadIdx.x)) * 16;
     return __builtin_bit_cast(chunk_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kStreamAux));
 }
 
 template <typename Fmt, int W, int CPT>
-__device__ inline void store_round(rsrc_t r, int n, const chunk_t& c, const LastChunk& last) {
+__device__ inline void store_round(rsrc_t r, int n, const chunk_t& c, const LastChunk<true>& last) {
     const int off = n == CPT - 1 ? last.off : (n * W + static_cast<int>(threadIdx.x)) * 16;
     if (n < CPT - 1 || !last.ragged || last.lead == 0) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) int, c), r, off,
@@ -122,12 +137,12 @@ __device__ inline float first_chunk_shift(const chunk_t& c, float c2) {
 }
 
 // The largest element of a thread's CPT chunks of one row, element by element.
-template <typename Fmt, int CPT>
+template <typename Fmt, int CPT, bool PART>
 __device__ inline float chunks_max_exact(const chunk_t (&x)[CPT], int lead) {
     float m = kNegInf;
 #pragma unroll
     for (int r = 0; r < CPT; ++r) {
-        const chunk_t c = (r == CPT - 1 && lead != 0) ? pad_lead<Fmt>(x[r], lead) : x[r];
+        const chunk_t c = (r != CPT - 1 || lead == 0) ? x[r] : PART ? pad_lead<Fmt>(x[r], lead) : pad_chunk<Fmt>();
         m = fmaxf(m, chunk_max<Fmt>(c));
     }
     return m;
@@ -143,8 +158,8 @@ __device__ inline float chunks_max_exact(const chunk_t (&x)[CPT], int lead) {
 // (f16 -inf) gets an unusable result and is decided element by element, as is
 // the thread whose last chunk is part padding.  Either way the value is the
 // exact maximum.
-template <typename Fmt, int CPT>
-__device__ inline float chunks_max(const chunk_t (&x)[CPT], const LastChunk& last) {
+template <typename Fmt, int CPT, bool PART>
+__device__ inline float chunks_max(const chunk_t (&x)[CPT], const LastChunk<PART>& last) {
     if constexpr (Fmt::kPerChunk == 8) {
         typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
         constexpr uint32_t kNegInfPair = 0xFC00FC00u;  // f16 -inf in both halves
@@ -157,13 +172,13 @@ __device__ inline float chunks_max(const chunk_t (&x)[CPT], const LastChunk& las
         // The last chunk joins unless it holds padding (one select).
         const chunk_t& l = x[CPT - 1];
         const h2_t ml = mx(mx(mx(m, H(l.x)), mx(H(l.y), H(l.z))), H(l.w));
-        if (!last.ragged || last.lead == 0) m = ml;
+        if (PART ? !last.ragged || last.lead == 0 : last.lead == 0) m = ml;
         const uint32_t b = __builtin_bit_cast(uint32_t, m);
         const float lo = __uint_as_float(b << 16), hi = __uint_as_float(b & 0xFFFF0000u);
-        const bool part = last.ragged && last.lead != 0 && last.lead != Fmt::kPerChunk;
+        const bool part = PART && last.ragged && last.lead != 0 && last.lead != Fmt::kPerChunk;
         if (__builtin_fabsf(lo) < 0x1p121f && __builtin_fabsf(hi) < 0x1p121f && !part) return fmaxf(lo, hi);
     }
-    return chunks_max_exact<Fmt, CPT>(x, last.lead);
+    return chunks_max_exact<Fmt, CPT, PART>(x, last.lead);
 }
 
 // The thread index through an opaque copy: lane and wave numbers derived from

@@ -529,7 +529,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
     const int tid = threadIdx.x;
     const int G = a.G;
     const float c2 = a.c2;
-    const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
+    const LastChunk<true> last = last_chunk<Fmt, W, CPT>(a.V);
     const float beta = a.beta;
 
     chunk_t rt[CPT], rs[CPT];
@@ -674,10 +674,7 @@ __global__ __launch_bounds__(W, 1) void verify_distill_kernel(FusedArgs a) {
         for (int r = 0; r < CPT; ++r) {
             if (live) {
                 chunk_t xt = rt[r], xs = rs[r];
-                if (r == CPT - 1 && last.ragged) {
-                    xt = pad_lead<Fmt>(xt, last.lead);
-                    xs = pad_lead<Fmt>(xs, last.lead);
-                }
+                if (r == CPT - 1) pad_last<Fmt>(xt, xs, last);
                 if (vlive && !cur.bonus && r * W + tid == ychunk) {
                     const int ye = cur.y - (r == CPT - 1 ? last.off / Fmt::kBytes : ychunk * EPC);
                     s_y[k & 1][0] = Fmt::get(xt, ye);

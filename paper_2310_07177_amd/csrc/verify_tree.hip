@@ -440,7 +440,7 @@ __device__ void finish_tree_polled(const TreeArgs& a, int b) {
     finish_tree(a, b);
 }
 
-template <typename Fmt, int W, int CPT>
+template <typename Fmt, int W, int CPT, bool PART>
 __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
     constexpr int NW = W / kWave, EPC = Fmt::kPerChunk, NG = EPC / 4;
     __shared__ f32x4_t s_c0[CPT * NG * W];
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
     const int tid = threadIdx.x;
     const int g = blockIdx.x, G = a.G, B = a.B, N = a.N;
     const float c2 = a.c2;
-    const LastChunk last = last_chunk<Fmt, W, CPT>(a.V);
+    const LastChunk<PART> last = last_chunk<Fmt, W, CPT, PART>(a.V);
     const int nk = g < a.nitems ? (a.nitems - 1 - g) / G + 1 : 0;  // <= kMaxTreeItems (launch)
     const char* const tbase = static_cast<const char*>(a.target);
     const char* const dbase = static_cast<const char*>(a.draft);
@@ -552,10 +552,7 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
         for (int r = 0; r < CPT; ++r) {
             if (live) {
                 chunk_t xt = rt[r], xs = rs[r];
-                if (r == CPT - 1 && last.ragged) {
-                    xt = pad_lead<Fmt>(xt, last.lead);
-                    xs = pad_lead<Fmt>(xs, last.lead);
-                }
+                if (r == CPT - 1) pad_last<Fmt>(xt, xs, last);
                 float st = 0.0f, ss = 0.0f;
 #pragma unroll
                 for (int q4 = 0; q4 < NG; ++q4) {
@@ -614,7 +611,7 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
                         // The holder of y posts R(y) and Q(y).
                         const int ch = y / EPC, rr = ch / W, th = ch - rr * W;
                         if (opaque_tid() == th) {
-                            const int ey = y - (rr == CPT - 1 ? last.off / Fmt::kBytes : ch * EPC);
+                            const int ey = y - (PART && rr == CPT - 1 ? last.off / Fmt::kBytes : ch * EPC);
                             float ev = 0.0f;
 #pragma unroll
                             for (int r = 0; r < CPT; ++r)
@@ -695,7 +692,7 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
                         m = at;
                         tok = draw_cached<W, CPT, EPC, false>(mass, mass_at, ures, s_cell, &s_dz, &s_tok);
                     }
-                    if (tok >= 0) tok = RowCut<Fmt>(a.V).token(tok);
+                    if (PART && tok >= 0) tok = RowCut<Fmt>(a.V).token(tok);
                     rec = (tok >= 0 && tok < a.V) ? node_rec(kNodeDraw, uint32_t(tok)) : node_rec(kNodeBad, 0);
                 }
             }
@@ -713,24 +710,32 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
         finish_tree_polled(a, pend_b);
 }
 
-template <typename Fmt, int W, int CPT>
+template <typename Fmt, int W, int CPT, bool PART>
 int tree_stream_blocks_per_cu() {
     static const int v = [] {
         int nb = 0;
-        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, tree_stream_kernel<Fmt, W, CPT>, W, 0);
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, tree_stream_kernel<Fmt, W, CPT, PART>, W, 0);
         return (e != hipSuccess || nb < 1) ? 1 : nb;
     }();
     return v;
 }
 
-template <typename Fmt, int W, int CPT>
-hipError_t launch_stream(const TreeLaunch& L, TreeArgs a) {
-    int64_t grid = int64_t(L.cus) * tree_stream_blocks_per_cu<Fmt, W, CPT>();
+template <typename Fmt, int W, int CPT, bool PART>
+hipError_t launch_rows(const TreeLaunch& L, TreeArgs a) {
+    int64_t grid = int64_t(L.cus) * tree_stream_blocks_per_cu<Fmt, W, CPT, PART>();
     const int64_t min_grid = (int64_t(a.nitems) + kMaxTreeItems - 1) / kMaxTreeItems;
     if (grid < min_grid) grid = min_grid;
     if (grid > a.nitems) grid = a.nitems;
     a.G = int(grid);
-    return launch_kernel(&tree_stream_kernel<Fmt, W, CPT>, dim3(unsigned(grid)), dim3(W), 0, L.stream, a);
+    return launch_kernel(&tree_stream_kernel<Fmt, W, CPT, PART>, dim3(unsigned(grid)), dim3(W), 0, L.stream, a);
+}
+
+// Rows of whole chunks have a kernel of their own, without the handling of a row that
+// ends inside one: 16 trees of 64 nodes, V = 32000 bf16, 52.1 us against 52.7 (the
+// fused and the distillation kernel lose nothing by holding it).
+template <typename Fmt, int W, int CPT>
+hipError_t launch_stream(const TreeLaunch& L, const TreeArgs& a) {
+    return L.V % Fmt::kPerChunk ? launch_rows<Fmt, W, CPT, true>(L, a) : launch_rows<Fmt, W, CPT, false>(L, a);
 }
 
 template <typename Fmt, int W, int CPT, bool VEC, bool GREEDY>
