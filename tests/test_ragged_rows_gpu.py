@@ -47,6 +47,39 @@ def test_verify_and_greedy(osd, dtype, V):
         compare_verify(r, *[o.cpu().numpy() for o in out], f"V={V} {dtype} T={T}")
 
 
+@pytest.mark.parametrize("dtype,V", [("bf16", v) for v in (8193, 16383, 16391, 32003, 32769, 50257, 65537)] +
+                         [("f32", v) for v in (4097, 8191, 16383, 16385, 20001)])
+def test_verify_many_rows(osd, dtype, V):
+    """More rows than are split over workgroups (360: above one per CU), so the
+    resident 512 x 4 and 512 x 8 tiles and the streaming kernel take them.  Most
+    of the target's mass lies on the last tokens, so that draws end in the last
+    chunk and the one it shares elements with; proposals of the last token ids are
+    tested as well."""
+    import torch
+    B, K = 40, 8
+    x = synth.verify_inputs(B, K, V, dtype, T=0.9, seed=V % 53, target_std=2.0, draft_noise=1.0, ragged=True)
+    t = synth.as_f32(x["target"]).copy()
+    t[1::2, :, V - 12:] += 11.0  # (every other sequence)
+    x["target"] = synth.store(t, dtype)
+    x["tokens"][2::4, 0] = V - 1
+    x["tokens"][3::4, 0] = V - 1 - np.arange(B // 4) % 12
+    assert x["target"].shape[0] * x["target"].shape[1] > torch.cuda.get_device_properties(0).multi_processor_count
+    for u in (None, 0.0, 1.0 - 2.0 ** -24):  # as drawn; bonus draws; nearly every proposal rejected
+        if u is not None:
+            x["u_accept"] = np.full_like(x["u_accept"], u)
+        out = osd.osd_verify(to_device(x["target"]), to_device(x["draft"]), to_device(x["tokens"]),
+                             to_device(x["u_accept"]), to_device(x["u_resample"]), x["T"],
+                             draft_len=to_device(x["draft_len"]))
+        torch.cuda.synchronize()
+        r = ref.verify(x["target"], x["draft"], x["tokens"], x["u_accept"], x["u_resample"], x["T"],
+                       draft_len=x["draft_len"])
+        n, _ = compare_verify(r, *[o.cpu().numpy() for o in out], f"V={V} {dtype} u={u}")
+        assert n >= B * 3 // 4
+        if u is not None:  # the draws did end in the last chunks
+            extra = r["out_tokens"][np.arange(B), r["accepted_len"]][1::2]
+            assert (extra >= V - 12).mean() > 0.5
+
+
 @pytest.mark.parametrize("dtype,V", STREAM + [("bf16", 32769), ("f32", 16385)])
 def test_fused_and_rejected(osd, dtype, V):
     import torch
