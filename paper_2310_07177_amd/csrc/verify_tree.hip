@@ -392,13 +392,11 @@ __global__ __launch_bounds__(W, min_waves_per_simd(W, CPT)) void tree_node_kerne
 // rewritten.  Where no child is accepted, the token is drawn from the last
 // residual over the cache (exact fixed point, as the fused kernel draws), or
 // from p should that residual have no mass after rounding.  Each item posts
-// its record and arrives at its sequence's counter without waiting for
-// either; the arrival's count is read at the start of the next item (it
-// returns after that item's rows, which the statistics wait for anyway), and
-// the item whose arrival is its sequence's last writes the outputs
-// (finish_tree_polled, which waits for records still on their way).  No item
-// waits for another.
-constexpr int kTreeRecordPolls = 4096;
+// its record without waiting for it.  At the start of the next item the record
+// is in place (it completes after that item's rows, which the statistics wait for
+// anyway) and the arrival at the sequence's counter is issued; its count is read
+// an item later in the same way, and the item whose arrival is its sequence's last
+// writes the outputs.  No item waits for another.
 constexpr int kMaxTreeItems = 128;  // items staged per workgroup (the grid grows beyond)
 
 __device__ inline float f4_get(const f32x4_t& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
@@ -407,37 +405,6 @@ __device__ inline uint64_t uniform_u64(uint64_t v) {
     const uint32_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v))));
     const uint32_t hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v >> 32))));
     return (uint64_t(hi) << 32) | lo;
-}
-
-// finish_tree for records posted without a wait before the arrival: each
-// lane first waits (bounded) until its node's record is there.  A record
-// still missing after the polls makes the tree invalid.
-__device__ void finish_tree_polled(const TreeArgs& a, int b) {
-    const int lane = opaque_tid() & (kWave - 1);
-    bool missing = false;
-    if (lane < a.N) {
-        const uint32_t* rp = &a.records[int64_t(b) * a.N + lane];
-        int p = 0;
-        while (load_relaxed(rp) == 0u && p < kTreeRecordPolls) {
-            __builtin_amdgcn_s_sleep(2);
-            ++p;
-        }
-        missing = p >= kTreeRecordPolls;
-    }
-    if (__ballot(missing) != 0) {
-        // (not reached in practice: every record is posted before its arrival)
-        if (lane < a.N) {
-            take_u32(&a.records[int64_t(b) * a.N + lane]);
-            a.out_tokens[int64_t(b) * a.N + lane] = -1;
-            if (a.path_nodes) a.path_nodes[int64_t(b) * a.N + lane] = -1;
-        }
-        if (lane == 0) {
-            a.accepted_len[b] = -1;
-            take_u32(&a.counters[b]);
-        }
-        return;
-    }
-    finish_tree(a, b);
 }
 
 template <typename Fmt, int W, int CPT, bool PART>
@@ -507,10 +474,21 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
     }
     __syncthreads();
 
-    // Wave 0's pending arrival (the previous item's): its sequence and the
-    // number of earlier arrivals, read at the start of the next item.
-    int pend_b = -1;
+    // Wave 0's record without an arrival (the previous item's): its sequence.
+    // Its pending arrival (the item's before that): its sequence and the number of
+    // earlier arrivals.
+    int rec_b = -1, pend_b = -1;
     uint32_t pend = 0u;
+    // The next step of both, by wave 0 (what it waits for was issued an item ago).
+    const auto arrive_next = [&]() {
+        if (pend_b >= 0 && uint32_t(__shfl(int(pend), 0, kWave)) == uint32_t(N - 1)) finish_tree(a, pend_b);
+        pend_b = rec_b;
+        rec_b = -1;
+        if (pend_b < 0) return;
+        wait_memory();  // the record is in place
+        if (opaque_tid() == 0)
+            pend = __hip_atomic_fetch_add(&a.counters[pend_b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     for (int k = 0; k < nk; ++k) {
         const int j = g + k * G, n = j / B, b = j - n * B, par = k & 1;
         const uint64_t kids = uniform_u64(s_kids[k]);
@@ -523,15 +501,12 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
         const int64_t nrow = int64_t(bn) * N + nn;
         const rsrc_t ntr = make_rsrc(nload ? tbase + nrow * a.row_bytes : tbase, nload ? a.row_bytes : 0u);
         const rsrc_t nsr = make_rsrc(ndraft ? dbase + nrow * a.row_bytes : tbase, ndraft ? a.row_bytes : 0u);
-        // Wave 0: the previous item's arrival (it returns after this item's
-        // rows, which the statistics wait for anyway; it may complete that
-        // sequence), then this item's candidate tokens and uniforms (lane c:
-        // node c), requested now and used after the statistics.
+        // Wave 0: the arrivals, then this item's candidate tokens and uniforms
+        // (lane c: node c), requested now and used after the statistics.
         int ktok = -1;
         float ku = 0.0f;
         if (opaque_tid() < kWave) {
-            if (pend_b >= 0 && uint32_t(__shfl(int(pend), 0, kWave)) == uint32_t(N - 1)) finish_tree_polled(a, pend_b);
-            pend_b = -1;
+            arrive_next();
             const int lane = opaque_tid();
             if (live && !leaf && lane < N) {
                 ktok = a.node_tokens[int64_t(b) * N + lane];
@@ -697,17 +672,17 @@ __global__ __launch_bounds__(W, 1) void tree_stream_kernel(TreeArgs a) {
                 }
             }
         }
-        // The record and the arrival, without waiting for either.
+        // The record, without waiting for it.
         if (opaque_tid() < kWave) {
-            if (opaque_tid() == 0) {
+            if (opaque_tid() == 0)
                 __hip_atomic_exchange(&a.records[int64_t(b) * N + n], rec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                pend = __hip_atomic_fetch_add(&a.counters[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            pend_b = b;
+            rec_b = b;
         }
     }
-    if (opaque_tid() < kWave && pend_b >= 0 && uint32_t(__shfl(int(pend), 0, kWave)) == uint32_t(N - 1))
-        finish_tree_polled(a, pend_b);
+    if (opaque_tid() < kWave) {  // the last two items' arrivals
+        arrive_next();
+        arrive_next();
+    }
 }
 
 template <typename Fmt, int W, int CPT, bool PART>

@@ -28,7 +28,7 @@ def assembly(src, out):
         return f.read().splitlines()
 
 
-@pytest.mark.parametrize("src", ["verify.hip", "verify_greedy.hip"])
+@pytest.mark.parametrize("src", ["verify.hip", "verify_greedy.hip", "verify_tree.hip"])
 def test_word_before_arrival(src, tmp_path):
     if not os.path.exists(build.HIPCC):
         pytest.skip("needs hipcc")
