@@ -10,8 +10,8 @@
 //        with m = beta p + (1-beta) q
 // and 0 log 0 = 0.  Rows with mask 0 get D = 0 and a zero gradient row.
 //
-// Work layout.  About one workgroup per CU walks rows g, g+G, ... or, with a
-// mask and more than two rows each, its equal share of the rows that are on
+// Work layout.  About one workgroup per CU walks rows g, g+G, ... or (LISTED),
+// with a mask and more than two rows each, its equal share of the rows that are on
 // (share_rows), each step loading the next of them; the zero gradient rows are
 // written between the passes of a step.  (With every row g, g+G, ... whatever its
 // mask, a workgroup's share of the rows that are on varied by a third and a row
@@ -36,6 +36,8 @@
 // partial at the device-wide coherence point; the last workgroup to finish
 // adds the partials in workgroup order, so the loss is reproducible for a
 // given grid.
+#include <algorithm>
+
 #include "osd_device.hpp"
 #include "osd_internal.hpp"
 #include "stream_device.hpp"
@@ -150,10 +152,8 @@ __device__ inline RowShare share_rows(const uint8_t* mask, int base, int rows, i
     return share;
 }
 
-// (8 waves per SIMD, two workgroups of 1024 threads on a CU, while a thread has
-// at most 8 elements.)
-template <typename Fmt, int W, int CPT, int KIND>
-__global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) void distill_stream_kernel(StreamDistillArgs a) {
+template <typename Fmt, int W, int CPT, int KIND, bool LISTED, int WAVES>
+__global__ __launch_bounds__(W, WAVES) void distill_stream_kernel(StreamDistillArgs a) {
     constexpr int NW = W / kWave, EPC = Fmt::kPerChunk, NG = EPC / 4;
     // JSD caches exponentials (the others, exponents): see the statistics pass.
     constexpr bool XV = KIND == 2;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     __shared__ double s_s[2 * NW];
     __shared__ RowPair s_rp;
     __shared__ double s_a[2 * NW];
-    __shared__ int s_list[kShareMax<W>];
+    __shared__ int s_list[LISTED ? kShareMax<W> : 1];
     __shared__ uint64_t s_cnt[NW];
     __shared__ int s_on[2];  // the flags of a workgroup's only rows
     __shared__ double s_part[1];  // sum of this workgroup's row divergences
@@ -184,16 +184,6 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     chunk_t rt[CPT], rs[CPT];
     float c1[CPT][EPC];
 
-    // This workgroup's slice and place in it.  One slice unless the mask has more
-    // flags than the workgroup loads at once.
-    const int q = a.gs < G ? int(blockIdx.x) / a.gs : 0;
-    const int Gq = a.gs, l = int(blockIdx.x) - q * a.gs, base = q * a.slice;
-    const int rows = a.nrows - base < a.slice ? a.nrows - base : a.slice;
-    // (Up to two rows per workgroup are not worth the list: finding it keeps the first
-    // row's loads waiting for the flags.  512 rows of V = 32128 bf16, all on: 30.7 us
-    // with it and 27.8 without, RKL 27.9 and 25.1; an eighth of them on, behind a
-    // verification: 44.7 and 48.9 in all.)
-    const bool listed = a.mask != nullptr && rows > 2 * Gq;
     if (tid == 0) {
         s_part[0] = 0.0;  // read and written by thread 0 only
         s_tail.row_ws = a.row_ws;
@@ -203,23 +193,37 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
         s_tail.nrows = a.nrows;
         s_tail.G = a.G;
     }
-    // One or two rows per workgroup: their flags, loaded before the row so that waiting
-    // for them never waits for the row, and staged in LDS by step -1.
     uint32_t mine = 1u;
-    if (a.mask && !listed && tid < 2 && l + tid * Gq < rows) mine = a.mask[base + l + tid * Gq];
-    // More rows: this workgroup's list of them, in LDS, so that nothing in the row
-    // loop reads global memory except the rows themselves (a scalar load there
-    // would share its wait counter with LDS traffic).
-    int more = 0, zeros = 0;  // rows after the next; rows off, not yet written
-    int next = l < rows ? base + l : -1;
-    if (listed) {
-        const RowShare share = share_rows<W>(a.mask, base, rows, Gq, l, s_list, s_cnt);
-        more = share.on > 0 ? share.on - 1 : 0;
-        zeros = share.off;
-        next = share.on > 0 ? __builtin_amdgcn_readfirstlane(s_list[0]) : -1;
-    } else if (l < rows) {
-        more = (rows - l - 1) / Gq;  // at most W - 1
-        if (tid <= more) s_list[tid] = base + l + tid * Gq;
+    int more = 0, zeros = 0;  // LISTED: rows after the next; rows off, not yet written
+    int next = int(blockIdx.x);
+    if constexpr (LISTED) {
+        // This workgroup's slice and place in it.  One slice unless the mask has more
+        // flags than the workgroup loads at once.
+        const int q = a.gs < G ? int(blockIdx.x) / a.gs : 0;
+        const int Gq = a.gs, l = int(blockIdx.x) - q * a.gs, base = q * a.slice;
+        const int rows = a.nrows - base < a.slice ? a.nrows - base : a.slice;
+        next = l < rows ? base + l : -1;
+        // A slice of few rows is dealt out as it is: the flags of its workgroups' one or two
+        // rows are staged as below.
+        const bool listed = rows > 2 * Gq;
+        if (!listed && tid < 2 && l + tid * Gq < rows) mine = a.mask[base + l + tid * Gq];
+        // More rows: this workgroup's list of them, in LDS, so that nothing in the row
+        // loop reads global memory except the rows themselves (a scalar load there
+        // would share its wait counter with LDS traffic).
+        if (listed) {
+            const RowShare share = share_rows<W>(a.mask, base, rows, Gq, l, s_list, s_cnt);
+            more = share.on > 0 ? share.on - 1 : 0;
+            zeros = share.off;
+            next = share.on > 0 ? __builtin_amdgcn_readfirstlane(s_list[0]) : -1;
+        } else if (l < rows) {
+            more = (rows - l - 1) / Gq;  // at most 1
+            if (tid <= more) s_list[tid] = base + l + tid * Gq;
+        }
+    } else {
+        // Rows g, g + G, ...  With a mask (then one or two of them) their flags,
+        // loaded before the row so that waiting for them never waits for the row,
+        // and staged in LDS by step -1.
+        if (a.mask && tid < 2 && tid * G < a.nrows - next) mine = a.mask[next + tid * G];
     }
     const int quota = zeros / (more + 1) + 1;  // rows off written by a step
     // The pipeline starts one step early: step -1 computes nothing; it issues
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
     bool live = false;
     for (int k = -1; k < 0 || n >= 0; ++k) {
         // (The first row is read whatever its flag, which is not known yet.)
-        const bool skip = k == 0 && __builtin_amdgcn_readfirstlane(s_on[1]) == 0;
+        const bool skip = (LISTED || a.mask) && k == 0 && __builtin_amdgcn_readfirstlane(s_on[1]) == 0;
         const Row nxt = decode_row<Fmt>(a, skip ? -1 : next);
         const rsrc_t ntr = make_rsrc(nxt.on ? nxt.trow : a.teacher, nxt.on ? a.row_bytes : 0u);
         const rsrc_t nsr = make_rsrc(nxt.on ? nxt.srow : a.student, nxt.on ? a.row_bytes : 0u);
@@ -307,18 +311,21 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
             rs[r] = load_round<W, CPT>(nsr, r, last);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (k < 0) {  // step -1: stage the flags
+        if (k < 0 && (LISTED || a.mask)) {  // step -1: stage the flags
             if (tid < 2) s_on[tid] = int(mine);
             __syncthreads();
         }
-        // The zero rows, spread over the steps (all by step -1 if there is no other).
+        if constexpr (LISTED) {
+            // The zero rows, spread over the steps (all by step -1 if there is no other).
 #pragma unroll 1
-        for (int z = 0; z < quota && zeros > 0; ++z) {
-            --zeros;
-            const int64_t zr = __builtin_amdgcn_readfirstlane(s_list[kShareMax<W> - 1 - zeros]);
-            if (a.grad_out)
-                zero_row<W>(make_rsrc(static_cast<char*>(a.grad_out) + zr * a.row_bytes, a.row_bytes), a.row_bytes, tid);
-            if (tid == 0 && a.row_loss_out) a.row_loss_out[zr] = 0.0f;
+            for (int z = 0; z < quota && zeros > 0; ++z) {
+                --zeros;
+                const int64_t zr = __builtin_amdgcn_readfirstlane(s_list[kShareMax<W> - 1 - zeros]);
+                if (a.grad_out)
+                    zero_row<W>(make_rsrc(static_cast<char*>(a.grad_out) + zr * a.row_bytes, a.row_bytes), a.row_bytes,
+                                tid);
+                if (tid == 0 && a.row_loss_out) a.row_loss_out[zr] = 0.0f;
+            }
         }
         if (!live) {
             if (a.grad_out && has_row) {
@@ -406,43 +413,67 @@ __global__ __launch_bounds__(W, W >= 512 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1) v
             s_part[0] += D;  // this workgroup's rows, in the order taken
         }
         n = next;
-        live = n >= 0 && (k >= 1 || __builtin_amdgcn_readfirstlane(s_on[k + 1]) != 0);
-        next = k + 1 < more ? __builtin_amdgcn_readfirstlane(s_list[k + 2]) : -1;
+        if constexpr (LISTED) {
+            live = n >= 0 && (k >= 1 || __builtin_amdgcn_readfirstlane(s_on[k + 1]) != 0);
+            next = k + 1 < more ? __builtin_amdgcn_readfirstlane(s_list[k + 2]) : -1;
+        } else {
+            live = n >= 0 && (!a.mask || __builtin_amdgcn_readfirstlane(s_on[k + 1]) != 0);
+            next = n >= 0 && a.nrows - n > G ? n + G : -1;
+        }
     }
     finish_loss<W>(s_tail, s_part);
 }
 
-template <typename Fmt, int W, int CPT, int KIND>
+template <typename Fmt, int W, int CPT, int KIND, bool LISTED, int WAVES>
 int blocks_per_cu() {
     static const int v = [] {
         int nb = 0;
-        const hipError_t e =
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, distill_stream_kernel<Fmt, W, CPT, KIND>, W, 0);
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &nb, distill_stream_kernel<Fmt, W, CPT, KIND, LISTED, WAVES>, W, 0);
         return (e != hipSuccess || nb < 1) ? 1 : nb;
     }();
     return v;
 }
 
-template <typename Fmt, int W, int CPT, int KIND>
-hipError_t launch_kind(const DistillLaunch& L, const StreamDistillArgs& a) {
-    int64_t want = int64_t(L.cus) * blocks_per_cu<Fmt, W, CPT, KIND>();
-    // At most W rows per workgroup (its list).
-    const int64_t min_grid = (int64_t(a.nrows) + W - 1) / W;
-    if (want < min_grid) want = min_grid;
-    unsigned grid = unsigned(want < a.nrows ? want : a.nrows);
+template <typename Fmt, int W, int CPT, int KIND, bool LISTED, int WAVES>
+hipError_t launch_rows(const DistillLaunch& L, const StreamDistillArgs& a, int64_t grid) {
     StreamDistillArgs ag = a;
     ag.slice = a.nrows;
     ag.gs = int(grid);
-    if (a.mask && a.nrows > W * kFlags) {
+    if (LISTED && a.nrows > W * kFlags) {
         // Slices of equal size, each with an equal number (at least 15) of workgroups.
         const int64_t nq = (int64_t(a.nrows) + W * kFlags - 1) / (W * kFlags);
         ag.slice = int((a.nrows + nq - 1) / nq);
         ag.gs = int(grid / nq);
-        grid = unsigned(ag.gs * nq);
+        grid = ag.gs * nq;
     }
     ag.G = int(grid);
-    const hipError_t e = launch_kernel(&distill_stream_kernel<Fmt, W, CPT, KIND>, dim3(grid), dim3(W), 0, L.stream, ag);
-    return e;
+    return launch_kernel(&distill_stream_kernel<Fmt, W, CPT, KIND, LISTED, WAVES>, dim3(unsigned(grid)), dim3(W), 0, L.stream,
+                         ag);
+}
+
+template <typename Fmt, int W, int CPT, int KIND>
+hipError_t launch_kind(const DistillLaunch& L, const StreamDistillArgs& a) {
+    // Two workgroups of 1024 threads on a CU (8 waves per SIMD) while a thread has at
+    // most 8 elements, where there are rows for both: 5000 rows of V = 5000 bf16, FKL,
+    // 78.5 -> 68.3 us, but 16 rows 8.2 -> 8.8.  (At 512 threads 5000 rows of V = 3000,
+    // JSD, took 46.7 us without the bound on registers and 48.3 with it.)
+    constexpr int kMany = W == 1024 && CPT * Fmt::kPerChunk <= 8 ? 8 : 1;
+    const bool many = a.nrows > L.cus;
+    // At most 7 workgroups on a CU: their arrivals at one counter are served one after
+    // another (5000 rows of V = 1000 fp32, JSD: 36.8 us with 8, 33.5 with 7).
+    int64_t grid = int64_t(L.cus) * (many ? std::min(blocks_per_cu<Fmt, W, CPT, KIND, true, kMany>(), 7) : 1);
+    // At most W rows per workgroup (its list).
+    const int64_t min_grid = (int64_t(a.nrows) + W - 1) / W;
+    if (grid < min_grid) grid = min_grid;
+    if (grid > a.nrows) grid = a.nrows;
+    // Up to two rows per workgroup are not worth the list: finding it keeps the first
+    // row's loads waiting for the flags.  (512 rows of V = 32128 bf16, all on: 30.7 us
+    // with it and 27.8 without, RKL 27.9 and 25.1; an eighth of them on, behind a
+    // verification: 44.7 and 48.9 in all.)  Rows without a mask do not carry its code.
+    if (a.mask && a.nrows > 2 * grid) return launch_rows<Fmt, W, CPT, KIND, true, kMany>(L, a, grid);
+    return many ? launch_rows<Fmt, W, CPT, KIND, false, kMany>(L, a, grid)
+                : launch_rows<Fmt, W, CPT, KIND, false, 1>(L, a, grid);
 }
 
 template <typename Fmt, int W, int CPT>

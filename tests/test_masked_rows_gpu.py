@@ -11,7 +11,11 @@ pytestmark = pytest.mark.gpu
 
 # (rows, V, dtype): 256 threads (slices of 4096 flags) and 1024 threads (slices of 16384).
 CASES = [(257, 20000, "bf16"), (700, 17000, "f32"), (2049, 40, "bf16"), (4096, 2041, "bf16"), (4099, 8, "bf16"),
-         (9001, 37, "f32"), (16385, 4100, "bf16")]
+         (9001, 37, "f32"), (16385, 4100, "bf16"),
+         # One row per CU and one more (the kernel for two workgroups on a CU); two rows per
+         # workgroup and one more (the list), at one, two and seven workgroups on a CU.
+         (256, 5000, "bf16"), (257, 5000, "bf16"), (512, 9000, "bf16"), (513, 9000, "bf16"), (1024, 8000, "f32"),
+         (1025, 8000, "f32"), (3584, 600, "bf16"), (3585, 600, "f32")]
 
 
 @pytest.mark.parametrize("rows,V,dtype", CASES)
