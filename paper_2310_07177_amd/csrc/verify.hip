@@ -1011,15 +1011,19 @@ hipError_t launch_fmt(const VerifyLaunch& L, const VerifyArgs& a) {
     const int nchunks = (L.V + Fmt::kPerChunk - 1) / Fmt::kPerChunk;
     const int64_t rows = int64_t(L.B) * (L.K + 1);
     const bool resident = nchunks <= 512 * 8;
-    // Few rows are split: up to one per CU beyond the resident tiles (against
-    // the streaming kernel: 224 rows of V = 50257 bf16 23.4 and 31.1 us, 576 rows of
-    // V = 50304 39.7 and 38.5, 100 rows of V = 128256 25.1 and 48.7), one per two
-    // CUs where 4 to 8 chunks per thread would be held (128 rows of V = 32000 14.5
-    // and 15.4, 216 rows 19.3 and 16.0), one per eight CUs for 2 to 4 (32 rows of
-    // V = 9000 9.7 and 10.5, 96 rows of V = 16000 12.3 and 11.0).
-    const int most = !resident ? L.cus : nchunks > 2048 ? L.cus / 2 : nchunks > 1024 ? L.cus / 8 : 0;
+    // Few rows are split: up to one per CU beyond the resident tiles (split and whole: 224
+    // rows of V = 50257 bf16 22.7 and 30.1 us, 576 rows of V = 50304 38.8 and 37.4, 100 rows
+    // of V = 128256 23.1 and 48.3).  In bf16, one per two CUs where 4 to 8 chunks per thread
+    // would be held (128 rows of V = 32000 14.5 and 14.9, 216 rows 18.5 and 15.5), one per
+    // eight CUs for 2 to 4 (30 rows of V = 9000 9.9 and 10.4, 125 rows 11.6 and 10.6).  A
+    // chunk of fp32 is half the work, so less is gained: one per four CUs for 4 to 8 (60
+    // rows of V = 16000 11.2 and 12.0, 125 rows 13.4 and 12.1), none for fewer (5 rows of
+    // V = 5000 9.0 and 8.2).
+    constexpr bool wide = Fmt::kPerChunk == 8;
+    const int most = !resident ? L.cus : nchunks > 2048 ? L.cus / (wide ? 2 : 4) : wide && nchunks > 1024 ? L.cus / 8 : 0;
     if (rows <= most) {
-        if (nchunks <= kMaxSplit * 256) return launch_split<Fmt, 256, 1>(L, a, nchunks);
+        if constexpr (wide)
+            if (nchunks <= kMaxSplit * 256) return launch_split<Fmt, 256, 1>(L, a, nchunks);
         if (nchunks <= kMaxSplit * 512) return launch_split<Fmt, 256, 2>(L, a, nchunks);
         if (nchunks <= kMaxSplit * 1024) return launch_split<Fmt, 256, 4>(L, a, nchunks);
         return launch_split<Fmt, 512, 4>(L, a, nchunks);

@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
 # (B, K, V, dtype): 256 x 1, 256 x 2, 256 x 4 and 512 x 4 chunks per segment, 3 to 8 segments.
 CASES = [(2, 4, 4104, "bf16"), (3, 3, 9001, "bf16"), (1, 4, 32000, "bf16"), (8, 5, 32003, "bf16"),
          (40, 3, 40000, "bf16"), (5, 8, 65535, "bf16"), (3, 2, 65537, "bf16"), (2, 2, 131072, "bf16"),
-         (2, 4, 2052, "f32"), (4, 4, 8191, "f32"), (30, 2, 20001, "f32"), (2, 3, 65536, "f32")]
+         (2, 4, 2052, "f32"), (4, 4, 8191, "f32"), (30, 2, 20001, "f32"), (2, 3, 65536, "f32"),
+         # Both sides of the limits on few rows (256 CUs): 64 and 65 fp32 rows, 32 and 33 bf16 ones.
+         (3, 4, 8193, "f32"), (16, 3, 16001, "f32"), (13, 4, 16384, "f32"), (8, 3, 16384, "bf16"), (11, 2, 16383, "bf16")]
 
 
 def inputs(B, K, V, dtype):
