@@ -540,12 +540,14 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 // Cross-workgroup hand-off through device memory, without cache flushes.
 //
 // Every word that crosses workgroups is written and read with agent-scope
-// atomic read-modify-write operations, which the hardware performs at the
-// device-wide coherence point (not in an XCD's private L2).  A publisher
-// waits for its payload RMW to complete (s_waitcnt) before it bumps the
-// arrival counter; the last arriver reads (and clears) the payloads with RMWs
-// issued after its counter RMW returned.  Release/acquire fences would instead
-// write back and invalidate the whole L2 of the XCD on every arrival.
+// atomic operations, which the hardware performs at the device-wide coherence
+// point (not in an XCD's private L2).  A publisher waits for its payload to be in
+// place (s_waitcnt) before it bumps the arrival counter; the last arriver reads
+// (and clears) the payloads after its counter RMW returned.  Where workgroups
+// exchange words without a counter (the split rows), no word is ever zero and
+// readers poll the words themselves, a bounded number of times; the counter that
+// decides who clears them is still bumped after the words.  Release/acquire fences
+// would instead write back and invalidate the whole L2 of the XCD on every arrival.
 // ---------------------------------------------------------------------------
 __device__ inline void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

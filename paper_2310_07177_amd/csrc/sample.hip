@@ -201,7 +201,7 @@ hipError_t launch_mode(const SampleLaunch& L, const SampleArgs& a) {
 }
 
 // sample_kernel with the rows streamed, U rounds of loads at a time: only the
-// chunk sums are held (59 VGPRs at 8 chunks per thread of a pair instead of 102,
+// chunk sums are held (63 VGPRs at 8 chunks per thread of a pair instead of 102,
 // so twice the waves hide the loads), and the winning wave reads its chunk
 // again.  Mixtures of 4096 row pairs of V = 32000 bf16: 131 -> 90 us (5.8 TB/s;
 // 32000 fp32 254 -> 160, 6.6 TB/s), of 2048 pairs of V = 128256: 346 -> 215 (the

@@ -71,10 +71,10 @@ __device__ inline chunk_t load_round(rsrc_t r, int n, const LastChunk<PART>& las
     return __builtin_bit_cast(chunk_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kStreamAux));
 }
 
-template <typename Fmt, int W, int CPT>
-__device__ inline void store_round(rsrc_t r, int n, const chunk_t& c, const LastChunk<true>& last) {
-    const int off = n == CPT - 1 ? last.off : (n * W + static_cast<int>(threadIdx.x)) * 16;
-    if (n < CPT - 1 || !last.ragged || last.lead == 0) {
+template <typename Fmt, int W, int CPT, bool PART>
+__device__ inline void store_round(rsrc_t r, int n, const chunk_t& c, const LastChunk<PART>& last) {
+    const int off = PART && n == CPT - 1 ? last.off : (n * W + static_cast<int>(threadIdx.x)) * 16;
+    if (!PART || n < CPT - 1 || !last.ragged || last.lead == 0) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) int, c), r, off,
                                                0, kStreamAux);
     } else if (last.lead < Fmt::kPerChunk) {  // the last chunk's own elements

@@ -15,8 +15,8 @@
 // finds the first mismatch, writes the outputs and clears words and counter.
 // (The wait for the word costs 0.2 to 0.3 us: B = 1, K = 4, V = 32000 bf16 5.1 -> 5.4, B = 64,
 // K = 8, V = 32128 9.6 -> 9.9.  The decision in a kernel of its own took the first of the
-// two 0.5 us longer than the variant without the wait.  With the counters of all sequences side by side the same
-// batch took 22.1 us: see VerifyRow.)
+// two 0.5 us longer than the variant without the wait.  With the counters of all
+// sequences side by side the larger batch took 22.1 us: see VerifyRow.)
 #include "osd.h"
 #include "osd_device.hpp"
 #include "osd_internal.hpp"

@@ -706,8 +706,7 @@ hipError_t launch_rows(const TreeLaunch& L, TreeArgs a) {
 }
 
 // Rows of whole chunks have a kernel of their own, without the handling of a row that
-// ends inside one: 16 trees of 64 nodes, V = 32000 bf16, 52.1 us against 52.7 (the
-// fused and the distillation kernel lose nothing by holding it).
+// ends inside one: 16 trees of 64 nodes, V = 32000 bf16, 52.1 us against 52.7.
 template <typename Fmt, int W, int CPT>
 hipError_t launch_stream(const TreeLaunch& L, const TreeArgs& a) {
     return L.V % Fmt::kPerChunk ? launch_rows<Fmt, W, CPT, true>(L, a) : launch_rows<Fmt, W, CPT, false>(L, a);
